@@ -3,7 +3,7 @@
 
 One bench "step" is one whole job of the hot path on resident synthetic
 input: seeded field, particle sample, potential grids (Fourier stage + 3-D
-C2R FFT), the full leapfrog schedule (one push launch per step), delta-f
+C2R FFT), the full leapfrog schedule, delta-f
 weights, and the CIC-deposit + binned cross power spectrum.  The default
 workload is the precision form: 512^3 neutrinos (m = 0.1 eV) on a 512^3
 bfloat16 gradient mesh in a 1 Gpc box, 1000 steps from z = 1e9 to z = 0,
@@ -53,9 +53,10 @@ def mesh_slots(cfg):
 
 
 def state_bytes(cfg, drift):
-    """Algorithmic state bytes of one particle-update: FP32 form read x, q0,
-    dq (36 B), write x, dq (24 B; 12 B on a kick-only launch); FP64 form read
-    x, q, q0 (72 B), write x, q (48 B; 24 B kick-only)."""
+    """Algorithmic state bytes of one particle in one push launch, however many
+    steps it carries out: FP32 form read x, q0, dq (36 B), write x, dq (24 B;
+    12 B on a kick-only launch); FP64 form read x, q, q0 (72 B), write x, q
+    (48 B; 24 B kick-only)."""
     if cfg["precision"] == "fp32":
         return 36 + (24 if drift else 12)
     return 72 + (48 if drift else 24)
@@ -129,6 +130,7 @@ def run_leg(cfg, steps, warmup, label, tuning=None):
     push_ms, launches = ctx.read_timing("push")
     ps_ms, ps_launches = ctx.read_timing("push_sort")
     work_push, work_ps = ctx.read_work("push"), ctx.read_work("push_sort")
+    pass_push, pass_ps = ctx.read_passes("push"), ctx.read_passes("push_sort")
     grid_ms, _ = ctx.read_timing("grid")
     sort_ms, sorts = ctx.read_timing("sort")
     out_ms, _ = ctx.read_timing("output")
@@ -139,25 +141,26 @@ def run_leg(cfg, steps, warmup, label, tuning=None):
     n = cfg["n_steps"]
     job_s = (t1 - t0) / steps
     # Algorithmic bytes from the library's own count of the work of the timed
-    # launches: particle-updates (with and without a drift) and mesh cells
-    # read (each field mesh a launch gathers from; with several species on
-    # their own re-sort cadence a plain launch may leave out the species a
-    # fused re-sort pushed).
+    # launches: particle states read and written (once per launch, however
+    # many steps it carries out, with and without a drift) and mesh cells read
+    # (each field mesh a launch gathers from).
     kernels = {}
-    wd, wk, mc = work_push
     kernels["k_push_f32" if cfg["precision"] == "fp32" else "k_push_f64"] = dict(
-        ms=push_ms, launches=launches,
-        bytes=wd * state_bytes(cfg, True) + wk * state_bytes(cfg, False) + mc * mesh_cell_bytes(cfg))
+        ms=push_ms, launches=launches, updates=sum(work_push[:2]),
+        bytes=pass_push[0] * state_bytes(cfg, True) + pass_push[1] * state_bytes(cfg, False)
+        + work_push[2] * mesh_cell_bytes(cfg))
     if ps_launches:
-        wd, _, mc = work_ps
-        kernels["k_push_sort_f32"] = dict(ms=ps_ms, launches=ps_launches,
-                                          bytes=wd * SORT_PUSH_STATE_BYTES + mc * mesh_cell_bytes(cfg))
+        kernels["k_push_sort_f32"] = dict(
+            ms=ps_ms, launches=ps_launches, updates=sum(work_ps[:2]),
+            bytes=pass_ps[0] * SORT_PUSH_STATE_BYTES + work_ps[2] * mesh_cell_bytes(cfg))
+    kernels = {name: k for name, k in kernels.items() if k["launches"]}
     for k in kernels.values():
         k["avg_launch_ms"] = k["ms"] / k["launches"]
         k["bytes_per_launch"] = k["bytes"] / k["launches"]
         k["achieved_gbs"] = k["bytes_per_launch"] / (k["avg_launch_ms"] * 1e-3) / 1e9
         k["ms_per_job"] = k["ms"] / steps
         k["launches_per_job"] = k["launches"] / steps
+        k["updates_per_s"] = k.pop("updates") / (k["ms"] * 1e-3)
     dominant = max(kernels, key=lambda name: kernels[name]["ms"])
     return dict(job_s=job_s, updates_per_s=n_total * n / job_s, kernels=kernels, dominant=dominant,
                 push_ms=push_ms, launches=launches, avg_launch_ms=kernels[dominant]["avg_launch_ms"],
@@ -391,8 +394,9 @@ def main():
             "sort": main_leg["sort_ms_per_job"],
             "sorts": main_leg["sorts_per_job"], "grid": main_leg["grid_ms_per_job"],
             "output": main_leg["output_ms_per_job"], "init": main_leg["init_ms_per_job"],
-            "note": "push = plain push launches (one step each); push_sort = push launches that "
-                    "also carry out a re-sort; sort = rank passes, scans and separate moves"},
+            "note": "push = plain push launches; push_sort = push launches that also carry out a "
+                    "re-sort (either carries out one or more steps); sort = rank passes, scans and "
+                    "separate moves"},
         "fp64_leg": fp64,
         "speedup_vs_fp64": (main_leg["updates_per_s"] / fp64["updates_per_s"]) if fp64 else None,
         "cpu_baseline": cpu,

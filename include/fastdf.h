@@ -108,7 +108,7 @@ enum {
 
 /* Kernel classes for fdf_read_timing */
 enum {
-  FDF_KERNEL_PUSH = 0,       /* gather + kick-drift-kick, one launch per step  */
+  FDF_KERNEL_PUSH = 0,       /* gather + kick-drift-kick, one or more steps     */
   FDF_KERNEL_SORT = 1,       /* spatial bucket sort of the particle state      */
   FDF_KERNEL_GRID = 2,       /* Fourier stage + 3-D C2R FFT of the potentials  */
   FDF_KERNEL_INIT = 3,       /* field generation and particle sampling          */
@@ -163,7 +163,8 @@ typedef struct fdf_info {
 /* Launch and sort parameters (picked by the autotuner or set by hand).  None
  * changes results: the push is per particle and the sort only permutes. */
 typedef struct fdf_tuning {
-  int32_t particles_per_thread;  /* push: 1, 2, 4 or 8 */
+  int32_t particles_per_thread;  /* FP32 separable push: at most 1, 2, 4 or 8 (fewer
+                                    when too few particles to fill the chip) */
   int32_t sort_tiles;            /* sort buckets per axis: a power of two <= min(G, 256);
                                     particles are ordered by the Morton index of
                                     their bucket, then of their cell inside it;
@@ -181,31 +182,32 @@ typedef struct fdf_tuning {
                                     a hipGraph (once per distinct starting state)
                                     and replays it; per-kernel timing is then off */
   int32_t sort_predict;          /* 1: order by the positions extrapolated to the
-                                    middle of the interval until the next re-sort
+                                    middle of the interval they are kept for
                                     (halves the spread of neighbours); 0: by the
                                     current positions */
   int32_t sort_fused;            /* 1: FP32 separable form -- a re-sort after the
-                                    first is carried out by the push of that step,
-                                    which writes the updated state in sorted order
-                                    (no separate move pass; results bit-identical;
-                                    the default); 0: rank + move passes, then
-                                    the push */
+                                    first is carried out by the push of the steps
+                                    before it, which writes the updated state in
+                                    sorted order (no separate move pass; results
+                                    bit-identical; the default); 0: rank + move
+                                    passes, then the push */
   int32_t push_waves;            /* plain push launch (not one that carries out a
                                     re-sort): at most this many resident waves per
                                     SIMD (2-8; enforced by reserving LDS per block),
                                     fewer waves keeping more of each block's mesh
                                     neighbourhood in cache; 0: as many as the
                                     registers allow */
-  int32_t sort_push_ppt;         /* push that carries out a re-sort: particles per
-                                    thread (1, 2 or 4; 0 selects 4) of its
-                                    1024-particle blocks */
-  int32_t sort_keys_push;        /* 1 (the default): with one species, CIC, no
-                                    super-steps and no graph, the plain push of the
-                                    step before a re-sort in the same fdf_step call
-                                    also writes the particles' sort keys, which the
-                                    rank pass then reads instead of the state (4
-                                    instead of 36 bytes per particle; results
-                                    bit-identical); 0: the rank pass computes them */
+  int32_t sort_push_ppt;         /* one-step push that carries out a re-sort:
+                                    particles per thread (1, 2 or 4; 0 selects 4)
+                                    of its 1024-particle blocks (pushes of
+                                    several steps take 4) */
+  int32_t sort_keys_push;        /* 1 (the default): FP32 separable form -- a push
+                                    that is followed by a re-sorting push in the
+                                    same fdf_step call also writes the particles'
+                                    sort keys, which the rank pass then reads
+                                    instead of the state (4 instead of 36 bytes per
+                                    particle; results bit-identical); 0: the rank
+                                    pass computes them */
 } fdf_tuning;
 
 /* ---- lifetime -------------------------------------------------------------- */
@@ -267,7 +269,9 @@ int fdf_build_potential_grids(struct fdf_ctx* ctx, int32_t field_id, double a);
 /* Advance every species n steps of the schedule (sec. 3.3 leapfrog; adjacent
  * half-kicks of consecutive steps are fused into one launch).  n < 0 walks
  * the same schedule backward.  Returns with positions and momenta at a
- * schedule point.  Errors: FDF_ERR_ARG when the step range leaves [0, n_steps]. */
+ * schedule point.  A launch carries a species through as many of the n steps
+ * as see the same grids and particle order.  Errors: FDF_ERR_ARG when the step
+ * range leaves [0, n_steps]. */
 int fdf_step(struct fdf_ctx* ctx, int32_t n);
 
 /* delta-f weights (sec. 2.2): w = 1 - fbar(|q|)/fbar(|p|), p the sampled
@@ -378,6 +382,13 @@ int fdf_timing_reset(struct fdf_ctx* ctx);
  * work[2] mesh cells read (one per cell of each field mesh a launch gathers
  * from, two with super-step blending).  Host pointer to 3 int64. */
 int fdf_read_work(struct fdf_ctx* ctx, int32_t kernel_class, int64_t* work);
+
+/* Particle-state passes of the timed launches of a push class since the last
+ * fdf_timing_reset: a launch that carries a species through several steps
+ * reads and writes its state once.  passes[0] particles whose positions and
+ * momenta a launch read and wrote, passes[1] the same for kick-only launches
+ * (positions read only).  Host pointer to 2 int64. */
+int fdf_read_passes(struct fdf_ctx* ctx, int32_t kernel_class, int64_t* passes);
 
 const char* fdf_status_string(int status);
 const char* fdf_last_error(const struct fdf_ctx* ctx);

@@ -149,7 +149,7 @@ int ilog2(int v) { int r = 0; while ((1 << r) < v) ++r; return r; }
 // ----------------------------------------------------------------- layout --
 struct Layout {
   size_t twiddle_d, twiddle_f, seg, bins, dep, scratch, dens, fields, parts, sort_count, sort_scan, sort_rank,
-      sort_bucket, sort_src, total;
+      sort_bucket, sort_src, sort_key, total;
   int64_t sort_keys_max;
   int grid_sets;
   size_t field_dk_bytes, field_grid_bytes, scratch_bytes, dens_bytes, parts_bytes;
@@ -233,6 +233,7 @@ Layout plan(const fdf_config& c) {
   L.sort_rank = off; off += sorting ? align_up((size_t)c.max_particles * 4) : 0;
   L.sort_bucket = off; off += sorting ? align_up((size_t)c.max_particles * 4) : 0;
   L.sort_src = off; off += sorting ? align_up((size_t)c.max_particles * 4) : 0;
+  L.sort_key = off; off += sorting ? align_up((size_t)c.max_particles * 4) : 0;
   L.total = off;
   return L;
 }
@@ -282,29 +283,25 @@ struct SpeciesRec {
   Segment seg[2];   // state buffers (second copy only with sorting)
   int cur = 0;
   bool pristine = false;   // state is exactly the sampled one (no pre-IC, not stepped)
-  double drift_cells = 0;  // typical drift since its last re-sort, in mesh cells
+  bool sorted = false;     // has been re-sorted since it was created
+  int order_time = -1;     // integer time from which its current order is meant to be used (-1: none)
+  double drift_cells = 0;  // typical drift since that time, in mesh cells
 };
 
 // A captured step sequence: the host state it was captured from and the host
 // state it leaves behind, so a replay can stand in for the enqueue.
 struct HostStepState {
   int step_index = 0;
-  bool sorted_once = false;
-  std::vector<int> cur;            // per species: the copy holding its state
+  std::vector<int> ints;           // per species: copy of its state, sorted, order time, pristine;
+                                   // per field: two super-step set tags
   std::vector<double> drift_cells; // per species
   std::vector<double> grid_a;      // per field; NaN = no grid
-  std::vector<int> tags;           // per field, two super-step set tags
-  std::vector<char> pristine;      // per species
   bool operator==(const HostStepState& o) const {
-    if (step_index != o.step_index || cur != o.cur || sorted_once != o.sorted_once || tags != o.tags ||
-        pristine != o.pristine || grid_a.size() != o.grid_a.size() ||
-        drift_cells.size() != o.drift_cells.size())
-      return false;
-    for (size_t i = 0; i < grid_a.size(); ++i)
-      if (std::memcmp(&grid_a[i], &o.grid_a[i], sizeof(double)) != 0) return false;
-    for (size_t i = 0; i < drift_cells.size(); ++i)
-      if (std::memcmp(&drift_cells[i], &o.drift_cells[i], sizeof(double)) != 0) return false;
-    return true;
+    auto same = [](const std::vector<double>& x, const std::vector<double>& y) {   // bitwise: NaN equals itself
+      return x.size() == y.size() && (x.empty() || std::memcmp(x.data(), y.data(), x.size() * sizeof(double)) == 0);
+    };
+    return step_index == o.step_index && ints == o.ints && same(drift_cells, o.drift_cells) &&
+           same(grid_a, o.grid_a);
   }
 };
 
@@ -322,6 +319,7 @@ struct TimingRec {
   double total_ms = 0;
   int64_t launches = 0;
   int64_t work[3] = {0, 0, 0};   // particle-updates with a drift, kick-only updates, mesh cells read
+  int64_t passes[2] = {0, 0};    // particles whose state launches read and wrote, with a drift and kick-only
 };
 
 }  // namespace
@@ -356,7 +354,6 @@ struct fdf_ctx {
   hipStream_t cap_stream = nullptr;   // private stream used only for graph capture
   hipStream_t launch_stream = nullptr;  // stream kernels are enqueued on right now
   std::vector<GraphRec> graphs;       // captured step sequences
-  bool sorted_once = false;
   std::string err;
   bool timing = false;
   TimingRec tim[FDF_KERNEL_COUNT];
@@ -410,11 +407,12 @@ void timing_end(fdf_ctx* c, int cls, std::pair<hipEvent_t, hipEvent_t>& ev) {
 }
 
 // Work done by the launches of a timed class (counted while timing is on).
-void timing_work(fdf_ctx* c, int cls, int64_t updates_drift, int64_t updates_kick, int64_t mesh_cells) {
+void timing_work(fdf_ctx* c, int cls, int64_t particles, const PushStep* step, int nsteps, int64_t mesh_cells) {
   if (!c->timing || c->launch_stream) return;
-  c->tim[cls].work[0] += updates_drift;
-  c->tim[cls].work[1] += updates_kick;
-  c->tim[cls].work[2] += mesh_cells;
+  TimingRec& t = c->tim[cls];
+  for (int s = 0; s < nsteps; ++s) t.work[step[s].do_drift ? 0 : 1] += particles;
+  t.work[2] += mesh_cells;
+  if (nsteps > 0) t.passes[step[0].do_drift ? 0 : 1] += particles;
 }
 
 void timing_collect(fdf_ctx* c) {
@@ -534,22 +532,17 @@ int build_grid(fdf_ctx* c, int field, double a, int buf = 0) {
   return launched(c, "grid build");
 }
 
-// Two device tables of segments: one per buffer copy (all species sort together,
-// so they always sit in the same copy).
+// Two device tables of segments, one per buffer copy.
 int upload_segments(fdf_ctx* c) {
   if (!c->seg_dirty) return FDF_OK;
-  const int64_t per = push_chunk_particles(c->ppt);
   const size_t table = align_up((size_t)c->cfg.max_species * sizeof(Segment));
   for (int copy = 0; copy < 2; ++copy) {
     std::vector<Segment> segs;
-    int64_t chunk = 0;
     for (auto& s : c->species) {
       Segment g = s.seg[copy];
       g.grid = c->fields[s.field].grid;
       g.grid2 = c->fields[s.field].grid2;
       g.m = s.m;
-      g.chunk_begin = chunk;
-      chunk += (s.n + per - 1) / per;
       segs.push_back(g);
     }
     int rc = hip_check(c, hipMemcpyAsync(c->ws + c->lay.seg + copy * table, segs.data(),
@@ -585,10 +578,6 @@ double typical_drift_cells(fdf_ctx* c, double dt, double a, double m) {
   return std::fabs(dt) * v * c->cfg.grid_n / c->cfg.box_mpc;
 }
 
-// Species sort on their own cadence (a mask of up to 64 species); more
-// species than that all sort together, at the cadence of the fastest.
-bool per_species_sorting(const fdf_ctx* c) { return c->species.size() <= 64; }
-
 // Prediction of a re-sort: order by x + v tau at scale factor a_mid.
 struct SortPrediction { double tau = 0, a_mid = 0; };
 
@@ -615,139 +604,282 @@ SortArgs sort_args(fdf_ctx* c, const SpeciesRec& s, double predict_tau, double a
   return a;
 }
 
-// resample: a species whose state is still the sampled one moves its ids
-// alone and is sampled again, by id, into the sorted slots (the same values
-// as moving the whole state from the random sampling order, at a fraction of
-// the scattered writes).
-int sort_species(fdf_ctx* c, const std::vector<SortPrediction>& pred, const std::vector<char>& due,
-                 bool resample) {
+// Rank and move passes of one species into its other buffer copy.  resample:
+// a species whose state is still the sampled one moves its ids alone and is
+// sampled again, by id, into the sorted slots (the same values as moving the
+// whole state from the random sampling order, at a fraction of the scattered
+// writes).
+int sort_species(fdf_ctx* c, SpeciesRec& s, const SortPrediction& pred, bool resample) {
   std::pair<hipEvent_t, hipEvent_t> ev;
   timing_begin(c, FDF_KERNEL_SORT, &ev);
-  for (size_t i = 0; i < c->species.size(); ++i) {
-    if (!due[i]) continue;
-    SpeciesRec& s = c->species[i];
-    SortArgs a = sort_args(c, s, pred[i].tau, pred[i].a_mid);
-    a.id_only = resample && s.pristine;
-    launch_sort(a, stream_of(c));
-    if (a.id_only) {
-      SampleArgs sa{};
-      sa.seg = s.seg[s.cur ^ 1];
-      sa.fp64 = c->cfg.precision == FDF_PREC_FP64;
-      sa.by_id = 1;
-      sa.seed = s.seed;
-      sa.box = c->cfg.box_mpc;
-      sa.t_nu = t_nu_ev();
-      launch_sample_species(sa, stream_of(c));
-    }
-    s.cur ^= 1;
+  SortArgs a = sort_args(c, s, pred.tau, pred.a_mid);
+  a.id_only = resample && s.pristine;
+  launch_sort(a, stream_of(c));
+  if (a.id_only) {
+    SampleArgs sa{};
+    sa.seg = s.seg[s.cur ^ 1];
+    sa.fp64 = c->cfg.precision == FDF_PREC_FP64;
+    sa.by_id = 1;
+    sa.seed = s.seed;
+    sa.box = c->cfg.box_mpc;
+    sa.t_nu = t_nu_ev();
+    launch_sample_species(sa, stream_of(c));
   }
+  s.cur ^= 1;
   timing_end(c, FDF_KERNEL_SORT, ev);
   return launched(c, "sort");
 }
 
-// A re-sort carried out by the push of the step: the due species in batches
-// of up to kMaxSortJobs (as many as the bucket-count buffer holds), each
-// batch ranked by one launch and scanned together, then pushed by one launch
-// that writes the updated state in sorted order into the other copy (pa
-// describes the step's push).  The rank passes are timed as sorting, the
-// pushes on their own.  keyed: the push of the previous step has written the
-// (single) due species' sort keys.
-int sort_push_species(fdf_ctx* c, const std::vector<SortPrediction>& pred, const std::vector<char>& due,
-                      const PushArgs& pa, size_t table, bool keyed) {
-  const size_t ns = c->species.size();
-  const int tiles = sort_tiles_of(c);
-  const int64_t nkeys = (int64_t)tiles * tiles * tiles;
-  const int64_t max_jobs = std::min<int64_t>(kMaxSortJobs, std::max<int64_t>(1, c->lay.sort_keys_max / nkeys));
-  const Segment* tables[2] = {(const Segment*)(c->ws + c->lay.seg), (const Segment*)(c->ws + c->lay.seg + table)};
-  size_t i = 0;
-  while (true) {
-    while (i < ns && !due[i]) ++i;
-    if (i >= ns) break;
-    SpeciesRec& s0 = c->species[i];
-    SortArgs a = sort_args(c, s0, pred[i].tau, pred[i].a_mid);
-    SortBatch& b = a.batch;
-    b = SortBatch{};
-    b.tables[0] = tables[0];
-    b.tables[1] = tables[1];
-    int64_t blocks = 0, base = 0;
-    std::vector<size_t> members;
-    std::vector<char> mesh(c->fields.size(), 0);
-    for (; i < ns && b.njobs < max_jobs; ++i) {
-      if (!due[i]) continue;
-      const SpeciesRec& s = c->species[i];
-      const int j = b.njobs++;
-      b.job_species[j] = (int32_t)i;
-      b.job_cur[j] = s.cur;
-      b.job_block[j] = blocks;
-      b.job_base[j] = base;
-      b.job_tau[j] = pred[i].tau;
-      b.job_ma[j] = s.m * pred[i].a_mid;
-      blocks += (s.n + kSortBlock - 1) / kSortBlock;
-      base += s.n;
-      members.push_back(i);
-      mesh[s.field] = 1;
+// The steps of one fdf_step call.  Launch index j in [0, n] stands for the
+// kick at integer time time(j) and (j < n) the drift to time(j + 1).
+struct StepPlan {
+  const fdf_ctx* c;
+  int k0, n;                 // first integer time and signed number of steps
+  int nabs() const { return std::abs(n); }
+  int time(int j) const { return n > 0 ? k0 + j : k0 - j; }
+  // drift from integer time u in the direction of the call (false past the schedule's end)
+  bool drift(int u, double* dr, double* ah) const {
+    if (n > 0 ? u >= c->cfg.n_steps : u <= 0) return false;
+    *dr = n > 0 ? c->drift[u] : -c->drift[u - 1];
+    *ah = n > 0 ? c->a_half[u] : c->a_half[u - 1];
+    return true;
+  }
+  PushStep step(int j) const {
+    PushStep s{};
+    const int t = time(j);
+    double kclose = 0, kopen = 0;   // half-kicks ending / starting at t
+    if (n > 0) {
+      if (j > 0) kclose = c->kick2[t - 1];
+      if (j < nabs()) kopen = c->kick1[t];
+    } else {
+      if (j > 0) kclose = -c->kick1[t];
+      if (j < nabs()) kopen = -c->kick2[t - 1];
     }
-    b.job_block[b.njobs] = blocks;
-    // keys written by the previous push (one species) sit in the rank array
-    // itself: each rank block reads its keys before it writes its ranks
-    if (keyed && b.njobs == 1) a.keys = a.rank;
-    std::pair<hipEvent_t, hipEvent_t> ev;
+    // the separable force does not depend on q: both halves as one kick
+    const bool sep = c->cfg.eom == FDF_EOM_SEPARABLE;
+    s.kick = sep ? kclose + kopen : kclose;
+    s.kick_open = sep ? 0.0 : kopen;
+    s.a_kick = c->a[t];
+    s.do_drift = j < nabs();
+    if (s.do_drift) drift(t, &s.drift, &s.a_drift);
+    s.dscale = (float)(s.drift * 4294967296.0 / c->cfg.box_mpc);
+    return s;
+  }
+};
+
+// The re-sort cadence of a species at integer time u: whether it is due, and
+// the steps until it is due next (from u; at least one).  Adaptive cadence:
+// once its typical drift since order_time reaches sort_cells (and at the
+// start); fixed cadence: at multiples of sort_every.
+struct SortCadence {
+  bool sorted;
+  int order_time;
+  double drift_cells;
+};
+constexpr int kNeverDue = 1 << 30;
+
+bool sort_due(const fdf_ctx* c, const SortCadence& s, int u) {
+  if (c->sort_cells > 0) return !s.sorted || s.drift_cells >= c->sort_cells;
+  return c->sort_every > 0 && u % c->sort_every == 0 && s.order_time != u;
+}
+
+int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
+  const int dir = p.n > 0 ? 1 : -1;
+  if (c->sort_cells > 0) {
+    double cells = s.drift_cells, dr, ah;
+    for (int k = 1; p.drift(u, &dr, &ah); ++k, u += dir) {
+      cells += typical_drift_cells(c, dr, ah, m);
+      if (cells >= c->sort_cells) return k;
+    }
+    return kNeverDue;
+  }
+  if (c->sort_every <= 0) return kNeverDue;
+  const int r = u % c->sort_every;
+  return dir > 0 ? c->sort_every - r : (r ? r : c->sort_every);
+}
+
+// Positions to order by for the interval that starts `lead` steps after u (as
+// long as the cadence will let it be): the state at u extrapolated to the
+// middle of the interval's gathers, which are made at the start of each of its
+// steps.
+SortPrediction sort_prediction(fdf_ctx* c, const StepPlan& p, int u, int lead, double m) {
+  const int dir = p.n > 0 ? 1 : -1, u0 = u + dir * lead;
+  const int len = steps_until_due(c, p, SortCadence{true, u0, 0.0}, u0, m);
+  double dr, ah, before = 0.0, span = 0.0;
+  for (int k = 0; k < lead && p.drift(u + dir * k, &dr, &ah); ++k) before += dr;
+  for (int k = 0; k + 1 < len && p.drift(u0 + dir * k, &dr, &ah); ++k) span += dr;
+  const double tau = before + 0.5 * span;
+  // scale factor half way along the extrapolation
+  SortPrediction r;
+  r.a_mid = c->a[u];
+  double done = 0.0;
+  for (int v = u; p.drift(v, &dr, &ah); v += dir) {
+    if (std::fabs(done) > 0.5 * std::fabs(tau)) break;
+    r.a_mid = ah;
+    done += dr;
+  }
+  r.tau = c->sort_predict ? tau : 0.0;
+  return r;
+}
+
+// What the next launch does for a species standing at launch index j.
+struct LaunchPlan {
+  int span = 1;              // steps carried out
+  bool sort_first = false;   // rank and move passes before it (sort_passes of them)
+  int sort_passes = 0;
+  bool fused = false;        // the push writes the state in sorted order for the interval after it
+  SortPrediction pred;       // of the rank pass before a fused push
+  SortPrediction pred_first; // of the rank and move passes
+};
+
+// limit: launch indices [j, limit) see the same grids.
+LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, double m, int j, int limit) {
+  LaunchPlan l;
+  const int u = p.time(j), rem = p.nabs() - j;   // drift steps left in the call
+  const int room = std::min(limit - j, kMaxSpan);
+  if (rem == 0) return l;                         // the closing kick
+  const int dir = p.n > 0 ? 1 : -1;
+  const bool fusable = c->sort_fused && c->cfg.precision == FDF_PREC_FP32 && c->cfg.eom == FDF_EOM_SEPARABLE;
+  double dr, ah;
+  SortCadence now = s;
+  if (sort_due(c, s, u)) {
+    // a first sort takes two passes (the second orders cells in buckets)
+    const bool first = !s.sorted;
+    const bool ride = fusable && p.drift(u + dir, &dr, &ah);   // steps follow that use the new order
+    l.sort_passes = (first ? 2 : 1) - (ride ? 1 : 0);
+    l.sort_first = l.sort_passes > 0;
+    if (l.sort_first) l.pred_first = sort_prediction(c, p, u, 0, m);
+    if (ride) {
+      l.fused = true;
+      l.pred = sort_prediction(c, p, u, 1, m);
+      return l;
+    }
+    now = SortCadence{true, u, 0.0};
+  }
+  const int d = steps_until_due(c, p, now, u, m);
+  if (d < rem) {               // due again within the call
+    l.span = std::min(d, room);
+    if (fusable && l.span == d) {
+      l.fused = true;
+      l.pred = sort_prediction(c, p, u, d, m);
+    }
+  } else {
+    l.span = std::min(rem + 1, room);   // to the end of the call, the closing kick included
+  }
+  return l;
+}
+
+// The species' cadence after the launch.
+SortCadence after_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, const LaunchPlan& l, double m, int j) {
+  const int dir = p.n > 0 ? 1 : -1, u = p.time(j);
+  SortCadence r = s;
+  if (l.sort_first) r = SortCadence{true, u, 0.0};
+  double dr, ah;
+  for (int k = 0; k < l.span && j + k < p.nabs(); ++k)
+    if (p.drift(u + dir * k, &dr, &ah)) r.drift_cells += typical_drift_cells(c, dr, ah, m);
+  if (l.fused) r = SortCadence{true, u + dir * l.span, 0.0};
+  return r;
+}
+
+// One species of a launch: what it does there, and the rank pass after it
+// for which the launch writes the sort keys.
+struct LaunchMember {
+  size_t species = 0;
+  LaunchPlan plan;
+  bool keyed = false;        // the species' previous push has written its sort keys
+  bool writes_keys = false;
+  SortPrediction next;
+};
+
+// A launch that would have fewer than this many blocks takes fewer particles
+// per thread: 256 CUs need several blocks each to hide their gathers (64^3
+// particles, 24 steps: 75 us with 256 blocks of 4 per thread, 46 us with 1024
+// of 1 per thread).
+constexpr int64_t kMinPushBlocks = 2048;
+// Particles per thread of a re-sorting push of several steps: the gathers of
+// the steps then outweigh the scatter, and more of them in flight per wave pay
+// (512^3 particles, 6.4 steps per launch: 9.73, 9.42 and 9.10 ms with 1, 2 and
+// 4; the one-step launch 4.04 ms with 1, slower with 4).
+constexpr int kSortPushPptSteps = 4;
+
+// One launch over the members (at most kMaxJobs), all standing at the same
+// launch index (pa.step[0]) and all fused or all plain.
+int run_launch(fdf_ctx* c, PushArgs& pa, const std::vector<LaunchMember>& members) {
+  const size_t table = align_up((size_t)c->cfg.max_species * sizeof(Segment));
+  const bool fused = members[0].plan.fused;
+  SpeciesBatch& b = pa.batch;
+  b = SpeciesBatch{};
+  b.tables[0] = (const Segment*)(c->ws + c->lay.seg);
+  b.tables[1] = (const Segment*)(c->ws + c->lay.seg + table);
+  int64_t total = 0;
+  for (auto& m : members) total += c->species[m.species].n;
+  int longest = 1;
+  for (auto& m : members) longest = std::max(longest, m.plan.span);
+  if (fused) pa.ppt = longest > 1 ? kSortPushPptSteps : c->sort_push_ppt;
+  else pa.ppt = pa.fp64 || pa.eom != FDF_EOM_SEPARABLE ? 1 : c->ppt;
+  while (pa.ppt > 1 && total < kMinPushBlocks * push_chunk_particles(pa.ppt)) pa.ppt /= 2;
+  const int64_t per = fused ? kSortBlock : push_chunk_particles(pa.ppt);
+  const SortArgs sa = sort_args(c, c->species[members[0].species], 0.0, 0.0);
+  pa.key_out = (uint32_t*)(c->ws + c->lay.sort_key);
+  pa.key_mask = 0;
+  pa.key_fine_bits = sa.fine_bits;
+  int64_t blocks = 0, base = 0;
+  std::vector<char> mesh(c->fields.size(), 0);
+  for (auto& m : members) {
+    const SpeciesRec& s = c->species[m.species];
+    const int j = b.njobs++;
+    b.job_species[j] = (int32_t)m.species;
+    b.job_cur[j] = s.cur;
+    b.job_block[j] = blocks;
+    b.job_base[j] = base;
+    for (size_t i = 0; i < m.species; ++i) b.job_slot[j] += c->species[i].n;
+    b.job_tau[j] = m.plan.pred.tau;
+    b.job_ma[j] = s.m * m.plan.pred.a_mid;
+    if (m.keyed) b.keyed_mask |= 1u << j;
+    if (m.writes_keys) pa.key_mask |= 1u << j;
+    pa.key_tau[j] = m.next.tau;
+    pa.key_ma[j] = s.m * m.next.a_mid;
+    pa.nsteps[j] = (int8_t)m.plan.span;
+    blocks += (s.n + per - 1) / per;
+    base += s.n;
+    mesh[s.field] = 1;
+  }
+  b.job_block[b.njobs] = blocks;
+  pa.grid_blocks = batch_grid(b);
+  std::pair<hipEvent_t, hipEvent_t> ev;
+  const int cls = fused ? FDF_KERNEL_PUSH_SORT : FDF_KERNEL_PUSH;
+  if (fused) {
+    SortArgs a = sa;
+    a.batch = b;
+    a.keys = (const uint32_t*)(c->ws + c->lay.sort_key);
     timing_begin(c, FDF_KERNEL_SORT, &ev);
     launch_sort_rank_batch(a, stream_of(c));
     timing_end(c, FDF_KERNEL_SORT, ev);
-    PushArgs p = pa;
-    p.seg = tables[0];
-    p.seg_alt = tables[1];
-    p.dseg = nullptr;
-    p.alt_mask = p.skip_mask = 0;
-    p.nseg = 1;
-    p.total_chunks = blocks;
-    p.xcd_blocks = 0;
-    p.persistent = 0;
-    p.ppt = c->sort_push_ppt;
-    p.lds_reserve = 0;   // the cap on resident waves is the plain push's; this kernel runs at full occupancy
-    p.sort_src = a.src;
-    p.sort_rank = a.rank;
-    p.sort_bucket = a.bucket;
-    p.sort_start = a.count;
-    p.sort_nkeys = nkeys;
-    p.sort_batch = b;
-    timing_begin(c, FDF_KERNEL_PUSH_SORT, &ev);
-    launch_push_sort(p, stream_of(c));
-    timing_end(c, FDF_KERNEL_PUSH_SORT, ev);
-    int64_t meshes = 0;
-    for (char r : mesh) meshes += r;
-    timing_work(c, FDF_KERNEL_PUSH_SORT, base, 0,
-                meshes * (int64_t)c->cfg.grid_n * c->cfg.grid_n * c->cfg.grid_n * (pa.blend ? 2 : 1));
-    for (size_t m : members) c->species[m].cur ^= 1;
-    const int rc = launched(c, "sort + push");
-    if (rc) return rc;
+    pa.lds_reserve = 0;   // the cap on resident waves is the plain push's; this kernel runs at full occupancy
+    pa.sort_src = a.src;
+    pa.sort_rank = a.rank;
+    pa.sort_bucket = a.bucket;
+    pa.sort_start = a.count;
+    pa.sort_nkeys = a.nkeys;
+    timing_begin(c, cls, &ev);
+    launch_push_sort(pa, stream_of(c));
+    timing_end(c, cls, ev);
+  } else {
+    pa.lds_reserve = push_lds_reserve(c->push_waves);
+    timing_begin(c, cls, &ev);
+    launch_push(pa, stream_of(c));
+    timing_end(c, cls, ev);
   }
-  return FDF_OK;
-}
-
-// Grid of the segment-balanced XCD mapping of a launch over every species
-// (8 times the largest share of an XCD), or 0 for a single species.
-int64_t xcd_blocks(fdf_ctx* c) {
-  if (c->species.size() < 2) return 0;
-  const int64_t per = push_chunk_particles(c->ppt);
-  int64_t most = 0;
-  for (int64_t x = 0; x < 8; ++x) {
-    int64_t share = 0;
-    for (auto& s : c->species) {
-      const int64_t n = (s.n + per - 1) / per;
-      share += n * (x + 1) / 8 - n * x / 8;
-    }
-    most = std::max(most, share);
+  int64_t meshes = 0;
+  for (char r : mesh) meshes += r;
+  timing_work(c, cls, 0, pa.step, 0, meshes * (int64_t)c->cfg.grid_n * c->cfg.grid_n * c->cfg.grid_n * (pa.blend ? 2 : 1));
+  for (auto& m : members) {
+    SpeciesRec& s = c->species[m.species];
+    timing_work(c, cls, s.n, pa.step, m.plan.span, 0);
+    if (fused) s.cur ^= 1;
+    s.pristine = false;
   }
-  return 8 * most;
-}
-
-int64_t total_chunks(fdf_ctx* c) {
-  const int64_t per = push_chunk_particles(c->ppt);
-  int64_t t = 0;
-  for (auto& s : c->species) t += (s.n + per - 1) / per;
-  return t;
+  return launched(c, fused ? "sort + push" : "push");
 }
 
 OutputArgs output_args(fdf_ctx* c, const SpeciesRec& s) {
@@ -975,7 +1107,6 @@ int fdf_reset(fdf_ctx* c) {
   c->stepped = false;
   c->seg_dirty = true;
   c->have_density = false;
-  c->sorted_once = false;
   return FDF_OK;
 }
 
@@ -1126,112 +1257,59 @@ int fdf_build_potential_grids(fdf_ctx* c, int32_t field_id, double a) {
 namespace {
 
 // Enqueue the launches of n steps (grid rebuilds, re-sorts, pushes) on the
-// current launch stream and advance the host-side state.
+// current launch stream and advance the host-side state.  Particles are
+// independent given the grids, so a launch carries a species through every
+// step up to its next re-sort, the next change of the grids, the end of the
+// call or kMaxSpan steps with its state in registers, and species with
+// different cadences advance in launches of their own.
 int enqueue_steps(fdf_ctx* c, int32_t n) {
-  const int k0 = c->step_index, nabs = std::abs(n);
+  const StepPlan plan{c, c->step_index, n};
+  const int nabs = plan.nabs();
   const bool tdep = c->cfg.potential_model == FDF_MODEL_RADMAT;
   int rc = FDF_OK;
   std::vector<int> used(c->fields.size(), 0);
   for (auto& s : c->species) used[s.field] = 1;
-  const size_t table = align_up((size_t)c->cfg.max_species * sizeof(Segment));
-  const int sort_every = c->sort_every;
   PushArgs pa{};
-  pa.nseg = (int)c->species.size();
-  pa.total_chunks = total_chunks(c);
-  pa.xcd_blocks = xcd_blocks(c);
   pa.fp64 = c->cfg.precision == FDF_PREC_FP64;
   pa.nslot = c->lay.nslot;
   pa.G = c->cfg.grid_n;
   pa.log2g = ilog2(c->cfg.grid_n);
   pa.box = c->cfg.box_mpc;
-  pa.ppt = c->ppt;
   pa.persistent = c->persistent;
-  pa.do_kick = 1;
   pa.eom = c->cfg.eom;
   pa.tsc = c->cfg.interp_order == 2;
-  pa.lds_reserve = push_lds_reserve(c->push_waves);
-  // The species the launch at integer time u re-sorts first.  Adaptive
-  // cadence: each species once its own typical drift since its last sort
-  // reaches sort_cells (all of them at the first sort, and all together when
-  // there are too many species for the per-species masks); fixed cadence:
-  // every sort_every steps.
   const size_t ns = c->species.size();
-  double m_fast = 1e300;
-  for (auto& sp : c->species) m_fast = std::min(m_fast, sp.m);
-  auto cadence_mass = [&](size_t i) { return per_species_sorting(c) ? c->species[i].m : m_fast; };
-  auto sorts_due = [&](int u, std::vector<char>* due) {
-    bool any = false;
-    for (size_t i = 0; i < ns; ++i) {
-      bool d;
-      if (c->sort_cells > 0) {
-        const double dc = per_species_sorting(c) ? c->species[i].drift_cells : c->species[0].drift_cells;
-        d = !c->sorted_once || dc >= c->sort_cells;
-      } else {
-        d = sort_every > 0 && u % sort_every == 0;
-      }
-      (*due)[i] = d;
-      any = any || d;
-    }
-    if (any && !per_species_sorting(c)) std::fill(due->begin(), due->end(), 1);
-    return any;
+  const int tiles = sort_tiles_of(c);
+  const int64_t sort_jobs = std::min<int64_t>(kMaxJobs, std::max<int64_t>(1, c->lay.sort_keys_max /
+                                                                                ((int64_t)tiles * tiles * tiles)));
+  std::vector<int> at(ns, 0);          // launch index each species stands at
+  std::vector<char> keyed(ns, 0);      // its sort keys are written
+  // anchors of the super-step interval that holds integer time t
+  auto anchor_interval = [&](int t) {
+    const auto& an = c->anchors;
+    size_t iv = 0;
+    while (iv + 2 < an.size() && an[iv + 1] <= t) ++iv;
+    return iv;
   };
-  // the interval until the species' next re-sort after one at u0 (as the
-  // cadence will decide it): half its conformal time and the scale factor at
-  // its middle
-  auto sort_prediction = [&](int u0, double m) {
-    double span = 0.0, cells = 0.0;
-    int steps = 0;
-    std::vector<std::pair<double, double>> iv;   // (drift, a) of the steps in the interval
-    const bool fwd = n > 0;
-    for (int u = u0; ; u += fwd ? 1 : -1) {
-      if (fwd ? u >= c->cfg.n_steps : u <= 0) break;
-      const double dr = fwd ? c->drift[u] : -c->drift[u - 1];
-      const double ah = fwd ? c->a_half[u] : c->a_half[u - 1];
-      iv.push_back({dr, ah});
-      span += dr;
-      cells += typical_drift_cells(c, dr, ah, m);
-      ++steps;
-      if (c->sort_cells > 0 ? cells >= c->sort_cells : steps >= std::max(sort_every, 1)) break;
+  // end of the launch indices from j on that see the same grids
+  auto same_grids_end = [&](int j) {
+    if (!tdep) return nabs + 1;
+    int e = j + 1;
+    if (!c->anchors.empty()) {
+      const size_t iv = anchor_interval(plan.time(j));
+      while (e <= nabs && anchor_interval(plan.time(e)) == iv) ++e;
     }
-    SortPrediction p;
-    p.a_mid = c->a[u0];
-    double half = 0.0;
-    for (const auto& e : iv) {
-      if (std::fabs(half + e.first) > 0.5 * std::fabs(span)) { p.a_mid = e.second; break; }
-      half += e.first;
-      p.a_mid = e.second;
-    }
-    p.tau = c->sort_predict ? 0.5 * span : 0.0;
-    return p;
+    return e;
   };
-  std::vector<char> due(ns, 0), due_next(ns, 0);
-  std::vector<SortPrediction> pred(ns);
-  // the plain push before a re-sort may write the sort keys (one species)
-  const bool key_fusable = c->sort_keys_push && c->sort_fused && !pa.fp64 && pa.eom == FDF_EOM_SEPARABLE &&
-                           !pa.tsc && c->anchors.empty() && !c->use_graph && ns == 1 && n > 0;
-  bool keyed = false;           // this step's re-sort reads keys written by the previous push
-  for (int j = 0; j <= nabs; ++j) {
-    int t;            // integer time of this launch's kick
-    double kclose = 0, kopen = 0, drift = 0, a_drift = 0;   // half-kicks ending / starting at t
-    if (n > 0) {
-      t = k0 + j;
-      if (j > 0) kclose = c->kick2[t - 1];
-      if (j < nabs) { kopen = c->kick1[t]; drift = c->drift[t]; a_drift = c->a_half[t]; }
-    } else {
-      t = k0 - j;
-      if (j > 0) kclose = -c->kick1[t];
-      if (j < nabs) { kopen = -c->kick2[t - 1]; drift = -c->drift[t - 1]; a_drift = c->a_half[t - 1]; }
-    }
-    // the separable force does not depend on q: both halves as one kick
-    const double kick = pa.eom == FDF_EOM_SEPARABLE ? kclose + kopen : kclose;
-    const double a_kick = c->a[t];
+  for (int j0 = 0; j0 <= nabs;) {
+    const int j1 = same_grids_end(j0);
     pa.blend = 0;
+    int kA = 0, kB = 0;
     if (!c->anchors.empty()) {
       // super-steps: grids at the anchors around t, interpolated linearly in a
-      const auto& an = c->anchors;
-      size_t iv = 0;
-      while (iv + 2 < an.size() && an[iv + 1] <= t) ++iv;
-      const int kA = an[iv], kB = an[iv + 1];
+      const size_t iv = anchor_interval(plan.time(j0));
+      kA = c->anchors[iv];
+      kB = c->anchors[iv + 1];
       int fsel_all = -1;
       for (size_t f = 0; f < c->fields.size(); ++f) {
         if (!used[f]) continue;
@@ -1256,8 +1334,8 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
       }
       pa.blend = 1;
       pa.grid_sel = fsel_all < 0 ? 0 : fsel_all;
-      pa.blend_t = (a_kick - c->a[kA]) / (c->a[kB] - c->a[kA]);
     } else {
+      const double a_kick = c->a[plan.time(j0)];
       for (size_t f = 0; f < c->fields.size(); ++f) {
         if (!used[f]) continue;
         if (!c->fields[f].has_grid || (tdep && c->fields[f].grid_a != a_kick)) {
@@ -1266,84 +1344,52 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
         }
       }
     }
-    bool fused_sort = false;    // this step's push also performs the re-sort of the due species
-    std::fill(due.begin(), due.end(), 0);
-    if (j < nabs) {
-      if (sorts_due(t, &due)) {
-        for (size_t i = 0; i < ns; ++i)
-          if (due[i]) pred[i] = sort_prediction(t, cadence_mass(i));
-        // the first sort takes two passes (the second orders cells in buckets)
-        const int passes = c->sorted_once ? 1 : 2;
-        fused_sort = c->sort_fused && !pa.fp64 && pa.eom == FDF_EOM_SEPARABLE;
-        for (int pass = 0; pass < passes - (fused_sort ? 1 : 0) && !rc; ++pass)
-          rc = sort_species(c, pred, due, pass == 0);
-        if (rc) return rc;
-        c->sorted_once = true;
-        for (size_t i = 0; i < ns; ++i)
-          if (due[i]) c->species[i].drift_cells = 0;
+    while (true) {
+      // the species furthest behind share a launch, with steps of their own each
+      int j = j1;
+      for (size_t i = 0; i < ns; ++i) j = std::min(j, at[i]);
+      if (j >= j1) break;
+      std::vector<LaunchMember> members;
+      int longest = 0;
+      for (size_t i = 0; i < ns; ++i) {
+        if (at[i] != j) continue;
+        SpeciesRec& s = c->species[i];
+        const SortCadence cad{s.sorted, s.order_time, s.drift_cells};
+        LaunchMember m;
+        m.species = i;
+        m.plan = plan_launch(c, plan, cad, s.m, j, j1);
+        if (!members.empty() && m.plan.fused != members[0].plan.fused) continue;
+        if (members.size() >= (size_t)(m.plan.fused ? sort_jobs : kMaxJobs)) break;
+        const SortCadence after = after_launch(c, plan, cad, m.plan, s.m, j);
+        const int jn = j + m.plan.span;
+        if (c->sort_keys_push && jn < nabs && !pa.fp64 && pa.eom == FDF_EOM_SEPARABLE) {
+          const LaunchPlan ln = plan_launch(c, plan, after, s.m, jn, jn < j1 ? j1 : same_grids_end(jn));
+          m.writes_keys = ln.fused && !ln.sort_first;
+          m.next = ln.pred;
+        }
+        m.keyed = m.plan.fused && !m.plan.sort_first && keyed[i];
+        for (int pass = 0; pass < m.plan.sort_passes; ++pass) {
+          rc = sort_species(c, s, m.plan.pred_first, pass == 0);
+          if (rc) return rc;
+        }
+        s.sorted = after.sorted;
+        s.order_time = after.order_time;
+        s.drift_cells = after.drift_cells;
+        keyed[i] = m.writes_keys;
+        at[i] = jn;
+        longest = std::max(longest, m.plan.span);
+        members.push_back(m);
       }
-      for (size_t i = 0; i < ns; ++i)
-        c->species[i].drift_cells += typical_drift_cells(c, drift, a_drift, cadence_mass(i));
-    }
-    // each species' state sits in its own copy: table 0 or 1 per species
-    pa.seg = (const Segment*)(c->ws + c->lay.seg);
-    pa.seg_alt = (const Segment*)(c->ws + c->lay.seg + table);
-    pa.alt_mask = 0;
-    pa.skip_mask = 0;
-    if (per_species_sorting(c)) {
-      for (size_t i = 0; i < ns; ++i) if (c->species[i].cur) pa.alt_mask |= 1ull << i;
-    } else {
-      pa.seg = (const Segment*)(c->ws + c->lay.seg + c->species[0].cur * table);
-    }
-    pa.kick = kick;
-    pa.kick_open = pa.eom == FDF_EOM_SEPARABLE ? 0.0 : kopen;
-    pa.a_kick = a_kick;
-    pa.do_drift = j < nabs;
-    pa.drift = drift;
-    pa.a_drift = a_drift;
-    int64_t pushed = 0;           // particles of the plain launch, and the meshes it reads
-    std::vector<char> mesh_read(c->fields.size(), 0);
-    if (fused_sort) {
-      rc = sort_push_species(c, pred, due, pa, table, keyed && due[0]);
-      if (rc) return rc;
-      for (size_t i = 0; i < ns; ++i) if (due[i]) pa.skip_mask |= 1ull << i;   // pushed already
-    }
-    keyed = false;
-    // write the sort keys in this push when the next launch of this call
-    // re-sorts the species and this launch pushes it (the keys are those of
-    // the state the rank pass would read)
-    pa.key_out = nullptr;
-    if (key_fusable && c->sorted_once && j + 1 < nabs && !(fused_sort && due[0]) &&
-        sorts_due(t + 1, &due_next) && due_next[0]) {
-      const SortPrediction pn = sort_prediction(t + 1, cadence_mass(0));
-      const SortArgs sa = sort_args(c, c->species[0], pn.tau, pn.a_mid);
-      pa.key_out = sa.rank;
-      pa.key_fine_bits = sa.fine_bits;
-      pa.key_tau = pn.tau;
-      pa.key_ma = sa.ma;
-      keyed = true;
-    }
-    for (size_t i = 0; i < ns; ++i) {
-      if (fused_sort && due[i]) continue;
-      pushed += c->species[i].n;
-      mesh_read[c->species[i].field] = 1;
-    }
-    if (pushed > 0) {
-      std::pair<hipEvent_t, hipEvent_t> ev;
-      timing_begin(c, FDF_KERNEL_PUSH, &ev);
-      launch_push(pa, stream_of(c));
-      timing_end(c, FDF_KERNEL_PUSH, ev);
-      int64_t meshes = 0;
-      for (char r : mesh_read) meshes += r;
-      timing_work(c, FDF_KERNEL_PUSH, pa.do_drift ? pushed : 0, pa.do_drift ? 0 : pushed,
-                  meshes * (int64_t)c->cfg.grid_n * c->cfg.grid_n * c->cfg.grid_n * (pa.blend ? 2 : 1));
-      rc = launched(c, "push");
+      for (int k = 0; k < longest; ++k) {
+        pa.step[k] = plan.step(j + k);
+        if (pa.blend) pa.step[k].blend_t = (pa.step[k].a_kick - c->a[kA]) / (c->a[kB] - c->a[kA]);
+      }
+      rc = run_launch(c, pa, members);
       if (rc) return rc;
     }
-    pa.key_out = nullptr;
-    for (auto& s : c->species) s.pristine = false;
+    j0 = j1;
   }
-  c->step_index = k0 + n;
+  c->step_index = c->step_index + n;
   c->stepped = true;
   return FDF_OK;
 }
@@ -1366,33 +1412,33 @@ std::vector<double> layout_signature(fdf_ctx* c) {
 HostStepState host_state(fdf_ctx* c) {
   HostStepState h;
   h.step_index = c->step_index;
-  h.sorted_once = c->sorted_once;
   for (auto& s : c->species) {
-    h.cur.push_back(s.cur);
+    h.ints.insert(h.ints.end(), {s.cur, s.sorted ? 1 : 0, s.order_time, s.pristine ? 1 : 0});
     h.drift_cells.push_back(s.drift_cells);
-    h.pristine.push_back(s.pristine ? 1 : 0);
   }
   for (auto& f : c->fields) {
     h.grid_a.push_back(f.has_grid ? f.grid_a : NAN);
-    h.tags.push_back(f.tag[0]);
-    h.tags.push_back(f.tag[1]);
+    h.ints.push_back(f.tag[0]);
+    h.ints.push_back(f.tag[1]);
   }
   return h;
 }
 
 void apply_state(fdf_ctx* c, const HostStepState& h) {
   c->step_index = h.step_index;
-  c->sorted_once = h.sorted_once;
-  for (size_t i = 0; i < c->species.size() && i < h.cur.size(); ++i) {
-    c->species[i].cur = h.cur[i];
+  const int* v = h.ints.data();
+  for (size_t i = 0; i < c->species.size(); ++i, v += 4) {
+    c->species[i].cur = v[0];
+    c->species[i].sorted = v[1] != 0;
+    c->species[i].order_time = v[2];
+    c->species[i].pristine = v[3] != 0;
     c->species[i].drift_cells = h.drift_cells[i];
-    c->species[i].pristine = h.pristine[i];
   }
-  for (size_t i = 0; i < c->fields.size() && i < h.grid_a.size(); ++i) {
+  for (size_t i = 0; i < c->fields.size(); ++i, v += 2) {
     c->fields[i].has_grid = !std::isnan(h.grid_a[i]);
     c->fields[i].grid_a = h.grid_a[i];
-    c->fields[i].tag[0] = h.tags[2 * i];
-    c->fields[i].tag[1] = h.tags[2 * i + 1];
+    c->fields[i].tag[0] = v[0];
+    c->fields[i].tag[1] = v[1];
   }
   c->stepped = true;
 }
@@ -1892,7 +1938,6 @@ int fdf_set_tuning(fdf_ctx* c, const fdf_tuning* t) {
   if (t->sort_push_ppt != 0 && t->sort_push_ppt != 1 && t->sort_push_ppt != 2 && t->sort_push_ppt != 4)
     return fail(c, FDF_ERR_ARG, "sort_push_ppt must be 0, 1, 2 or 4");
   if (t->sort_keys_push != 0 && t->sort_keys_push != 1) return fail(c, FDF_ERR_ARG, "sort_keys_push must be 0 or 1");
-  if (p != c->ppt) c->seg_dirty = true;   // chunk boundaries depend on the block size
   clear_graphs(c);
   c->persistent = t->persistent_blocks;
   c->use_graph = t->use_graph != 0;
@@ -1931,7 +1976,7 @@ int fdf_read_timing(fdf_ctx* c, int32_t cls, double* ms, int64_t* launches) {
 int fdf_timing_reset(fdf_ctx* c) {
   if (!c) return FDF_ERR_ARG;
   timing_collect(c);
-  for (auto& t : c->tim) { t.total_ms = 0; t.launches = 0; t.work[0] = t.work[1] = t.work[2] = 0; }
+  for (auto& t : c->tim) { t.total_ms = 0; t.launches = 0; t.work[0] = t.work[1] = t.work[2] = t.passes[0] = t.passes[1] = 0; }
   return FDF_OK;
 }
 
@@ -1939,6 +1984,13 @@ int fdf_read_work(fdf_ctx* c, int32_t cls, int64_t* work) {
   if (!c || !work) return FDF_ERR_ARG;
   if (cls < 0 || cls >= FDF_KERNEL_COUNT) return fail(c, FDF_ERR_ARG, "bad kernel class");
   for (int k = 0; k < 3; ++k) work[k] = c->tim[cls].work[k];
+  return FDF_OK;
+}
+
+int fdf_read_passes(fdf_ctx* c, int32_t cls, int64_t* passes) {
+  if (!c || !passes) return FDF_ERR_ARG;
+  if (cls < 0 || cls >= FDF_KERNEL_COUNT) return fail(c, FDF_ERR_ARG, "bad kernel class");
+  for (int k = 0; k < 2; ++k) passes[k] = c->tim[cls].passes[k];
   return FDF_OK;
 }
 

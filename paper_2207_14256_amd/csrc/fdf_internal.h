@@ -100,36 +100,44 @@ struct Segment {
   const void* grid2;       // second grid set (super-steps), or null
   double m;                // mass [eV]
   int64_t n;               // particles
-  int64_t chunk_begin;     // first chunk of this segment in the launch
 };
 
 // Particles per block of the sort's rank pass.
 constexpr int kSortBlock = 1024;
 
-// A batched re-sort (FP32 separable form): the species due at one step are
-// ranked by one launch, scanned together and moved by one fused push launch.
-// Job j is species job_species[j], whose current state is in copy
-// job_cur[j] of the segment tables; its rank blocks (kSortBlock particles
-// each) are [job_block[j], job_block[j + 1]); its bucket counts are
+// The species of one launch (plain push, rank pass, or a push that carries
+// out a re-sort).  Job j is species job_species[j], whose current state is in
+// copy job_cur[j] of the segment tables; its blocks are
+// [job_block[j], job_block[j + 1]).  A rank pass or a re-sorting push uses
+// blocks of kSortBlock particles; the bucket counts of job j are
 // count + j nkeys, scanned together with the other jobs' so that its bucket
-// starts are offset by job_base[j] (the particles of the jobs before it), and
-// its rank-pass outputs are rank, bucket and src + job_base[j].
-constexpr int kMaxSortJobs = 16;
-struct SortBatch {
+// starts are offset by job_base[j] (the particles of the jobs before it), its
+// rank-pass outputs are rank, bucket and src + job_base[j], and its sort keys
+// keys + job_slot[j] (the particles of the species before it), if keyed_mask
+// says that they are written.
+constexpr int kMaxJobs = 32;
+struct SpeciesBatch {
   int32_t njobs;           // 0: not batched (SortArgs.seg, one species)
-  int32_t job_species[kMaxSortJobs];
-  int32_t job_cur[kMaxSortJobs];
-  int64_t job_block[kMaxSortJobs + 1];
-  int64_t job_base[kMaxSortJobs];
-  double job_tau[kMaxSortJobs];   // predict_tau of the job's species
-  double job_ma[kMaxSortJobs];    // m a of the job's species
-  const Segment* tables[2];       // device segment tables, copies 0 and 1
+  uint32_t keyed_mask;     // rank pass: jobs whose sort keys the previous push has written
+  int32_t job_species[kMaxJobs];
+  int32_t job_cur[kMaxJobs];
+  int64_t job_block[kMaxJobs + 1];
+  int64_t job_base[kMaxJobs];
+  int64_t job_slot[kMaxJobs];
+  double job_tau[kMaxJobs];   // predict_tau of the job's species
+  double job_ma[kMaxJobs];    // m a of the job's species
+  const Segment* tables[2];   // device segment tables, copies 0 and 1
 };
 
-// Block b of a batched launch: each XCD (b mod 8) takes a contiguous eighth
-// of every job's blocks.  Returns the job and (*local) the block inside it,
-// or -1 for a block past its XCD's share (the grid is 8 times the largest).
-__device__ inline int batch_block(const SortBatch& sb, int64_t b, int64_t* local) {
+// Block b of a batched launch: each XCD (b mod 8; consecutive block ids are
+// dealt round-robin to the 8 XCDs) takes a contiguous eighth of every job's
+// blocks, so that it (own L2) walks compact regions of sorted particles.  A
+// contiguous eighth of the whole launch would give whole species to single
+// XCDs, and species whose particles cost more (sparse seeds, whose gathers
+// share few mesh lines) would hold the launch there.  Returns the job and
+// (*local) the block inside it, or -1 for a block past its XCD's share (the
+// grid is 8 times the largest).
+__device__ inline int batch_block(const SpeciesBatch& sb, int64_t b, int64_t* local) {
   const int64_t x = b & 7;
   int64_t l = b >> 3;
   for (int j = 0; j < sb.njobs; ++j) {
@@ -142,7 +150,7 @@ __device__ inline int batch_block(const SortBatch& sb, int64_t b, int64_t* local
 }
 
 // Grid of a batched launch (host).
-inline int64_t batch_grid(const SortBatch& sb) {
+inline int64_t batch_grid(const SpeciesBatch& sb) {
   int64_t most = 0;
   for (int64_t x = 0; x < 8; ++x) {
     int64_t share = 0;
@@ -155,50 +163,55 @@ inline int64_t batch_grid(const SortBatch& sb) {
   return 8 * most;
 }
 
-struct PushArgs {
-  const Segment* seg;      // device array: each species' segment in copy 0 of its state
-  const Segment* seg_alt;  // the same in copy 1 (the other buffer of a sorting species)
-  uint64_t alt_mask;       // species whose current state is in copy 1 (species index < 64)
-  uint64_t skip_mask;      // species this launch leaves alone (pushed by a fused re-sort)
-  int32_t nseg;
-  int64_t total_chunks;
-  int32_t fp64;
-  int32_t nslot;
-  int32_t log2g;
-  int32_t G;
-  int32_t do_kick, do_drift;
-  int32_t eom;             // 0: separable form (fdf_config.eom), else a form of fdf_push_eom.hip
+// One leapfrog step of a launch: the kick at its time point and the drift to
+// the next one (do_drift = 0: a kick alone, the last step of a call).
+struct PushStep {
   double kick;             // separable: fused kick coefficient [Mpc]; other forms: closing half-kick
   double kick_open;        // other forms: opening half-kick of the next step (applied second)
   double a_kick;           // a at the kick
   double drift;            // Delta tau of the drift [Mpc]
   double a_drift;          // a_{k+1/2}
+  double blend_t;          // super-steps: interpolation weight of the later anchor
+  float dscale;            // drift in units of 2^-32 L
+  int32_t do_drift;
+};
+
+// Steps one launch carries out at most with the particle state in registers
+// (they travel in the kernel arguments, which stay below 4 KB).
+constexpr int kMaxSpan = 24;
+
+struct PushArgs {
+  SpeciesBatch batch;      // the species pushed and their blocks
+  PushStep step[kMaxSpan];
+  int8_t nsteps[kMaxJobs]; // consecutive steps of each job, from step[0] on, >= 1
+  int32_t fp64;
+  int32_t nslot;
+  int32_t log2g;
+  int32_t G;
+  int32_t eom;             // 0: separable form (fdf_config.eom), else a form of fdf_push_eom.hip
   double box;              // L
-  int32_t ppt;             // particles per thread (fused re-sort push: 1, 2 or 4)
+  int32_t ppt;             // particles per thread (re-sorting push: 1, 2 or 4)
   int32_t persistent;      // 0: one block per chunk; > 0: this many blocks (a multiple of 8) loop
+  int64_t grid_blocks;     // batch_grid of the batch
   int32_t tsc;             // 1: TSC (r = 2) force interpolation, 0: CIC
   int32_t blend;           // 1: interpolate two grid sets (super-steps)
   int32_t grid_sel;        // which set holds the earlier anchor: 0 = grid, 1 = grid2
-  double blend_t;          // interpolation weight of the later anchor
   int32_t lds_reserve;     // bytes of LDS reserved per block (caps resident waves), or 0
-  int64_t xcd_blocks;      // > 0: grid of the segment-balanced XCD mapping (several segments)
-  // push fused with the move of a re-sort (launch_push_sort; FP32 separable
-  // form, one species: seg and dseg point at its entry in the two tables,
-  // total_chunks counts its kSortBlock-particle rank blocks)
-  const Segment* dseg;     // destination copy
+  // push that carries out a re-sort (launch_push_sort; FP32 separable form)
   const uint32_t* sort_src;     // rank pass outputs (SortArgs::src, rank, bucket)
   const uint32_t* sort_rank;
   const uint32_t* sort_bucket;
   const uint32_t* sort_start;   // bucket starts (the scanned counts)
-  int64_t sort_nkeys;           // buckets per job (batched re-sort)
-  SortBatch sort_batch;         // batched re-sort: njobs > 0 (seg / seg_alt are the two tables)
-  // sort keys of the next step's re-sort, written by this (plain, FP32,
-  // one-species) push from the state it leaves: key_out[i] for particle slot i
-  uint32_t* key_out;            // or null
+  int64_t sort_nkeys;           // buckets per job
+  // sort keys of the next rank pass of the jobs in key_mask, written by this
+  // push (FP32) from the state it leaves: key_out[job_slot + i] for slot i
+  uint32_t* key_out;
+  uint32_t key_mask;
   int32_t key_fine_bits;        // log2 of the bucket tile side in cells
-  double key_tau;               // predict_tau of the next re-sort
-  double key_ma;                // m a at the middle of its interval
+  double key_tau[kMaxJobs];     // predict_tau of the next rank pass, per job
+  double key_ma[kMaxJobs];      // m a of that prediction
 };
+static_assert(sizeof(PushArgs) <= 4096, "kernel arguments");
 
 struct SortArgs {
   Segment seg;             // source copy
@@ -217,8 +230,8 @@ struct SortArgs {
   uint32_t* bucket;        // [n] per sorted element: bucket
   uint32_t* src;           // [n] per sorted element: source slot inside the block
   int32_t id_only;         // move pass: move the ids alone (the caller re-samples the state by id)
-  SortBatch batch;         // rank pass over several species (batch.njobs > 0; seg, dst unused)
-  const uint32_t* keys;    // rank pass: keys written by the previous push (one species), or null
+  SpeciesBatch batch;      // rank pass over several species (batch.njobs > 0; seg, dst unused)
+  const uint32_t* keys;    // rank pass: keys written by previous pushes (batch.keyed_mask)
 };
 
 struct SampleArgs {
@@ -308,7 +321,7 @@ void launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
 int push_chunk_particles(int ppt);
 void launch_sort(const SortArgs& a, hipStream_t s);
 void launch_sort_rank(const SortArgs& a, hipStream_t s);   // counts, rank pass and scan, no move
-void launch_sort_rank_batch(const SortArgs& a, hipStream_t s);   // the same over a SortBatch
+void launch_sort_rank_batch(const SortArgs& a, hipStream_t s);   // the same over a SpeciesBatch
 void launch_push_sort(const PushArgs& a, hipStream_t s);
 size_t sort_scan_scratch_words(int64_t nkeys);
 

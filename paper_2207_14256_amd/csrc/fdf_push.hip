@@ -1,10 +1,17 @@
 // Gather + kick-drift-kick push of the neutrino tracers (sec. 3.3), gfx950.
 //
-// One launch advances every species by one leapfrog step: the kick of the
-// closing half of step k-1 and the opening half of step k are evaluated at the
-// same (x_k, a_k), so they are applied as one kick with the summed Delta tau;
-// then the drift.  The last launch of a call is a kick alone, leaving q at a
-// schedule point.
+// A launch carries its species through consecutive leapfrog steps with the
+// particle state in registers: particles are independent given the grids, so
+// every step up to the next change of the grids or of the particle order fits
+// in one launch.  The kick of the closing half of step k-1 and the opening
+// half of step k are evaluated at the same (x_k, a_k), so they are applied as
+// one kick with the summed Delta tau; then the drift.  The last step of a call
+// is a kick alone, leaving q at a schedule point.
+// A launch of one step is bound by HBM (60 B of state per particle); each
+// further step costs its gathers and arithmetic alone: at 134 M particles with
+// 8 per cell (FP32, CIC) 0.93 ms against 1.9 ms for a launch of its own, with
+// the vector ALU issuing in 78 % and the address unit busy in 85 % of the
+// cycles.
 //
 // Per particle: CIC (trilinear; or TSC, 27 points, when PushArgs::tsc is set)
 // interpolation of the gradient grids at x,
@@ -20,11 +27,10 @@
 // CIC corner.
 // FP64 form: everything binary64; 8 slots = four 16-byte loads per corner.
 //
-// Blocks take contiguous chunks of one species, in an XCD-aware order (with
-// several species, every XCD takes an eighth of each).  On a step that begins
-// with a re-sort, k_push_sort_f32 pushes the species due (one launch for all
-// of them) and writes their updated state straight to their sorted slots; the
-// plain push of the step before can also write their sort keys.
+// Blocks take contiguous chunks of one species, every XCD an eighth of each.
+// The push of the steps before a re-sort, k_push_sort_f32, writes its updated
+// state straight to its sorted slots; any push can also write the sort keys of
+// the rank pass that follows it.
 //
 // The separable form is the one implemented here; the other equations of
 // motion (fdf_push_eom.hip) take over when PushArgs::eom is set.
@@ -109,21 +115,21 @@ struct ConstF32 {
 };
 
 template <bool BLEND>
-__device__ __forceinline__ ConstF32 const_f32(const PushArgs& a, const Segment& sg) {
+__device__ __forceinline__ ConstF32 const_f32(const PushArgs& a, const PushStep& st, const Segment& sg) {
   ConstF32 k;
   k.shift = 32 - a.log2g;
   k.gmask = (uint32_t)a.G - 1u;
   k.G = (uint32_t)a.G;
   k.finv = __uint_as_float((uint32_t)(127 - k.shift) << 23);   // 2^-shift
-  k.kick = (float)a.kick;
-  const float ma = (float)(sg.m * a.a_kick);
-  const float mah = (float)(sg.m * a.a_drift);
+  k.kick = (float)st.kick;
+  const float ma = (float)(sg.m * st.a_kick);
+  const float mah = (float)(sg.m * st.a_drift);
   k.ma2 = ma * ma;
   k.mah2 = mah * mah;
-  k.dscale = (float)(a.drift * 4294967296.0 / a.box);
+  k.dscale = st.dscale;
   k.gridA = (BLEND && a.grid_sel) ? sg.grid2 : sg.grid;
   k.gridB = (BLEND && a.grid_sel) ? sg.grid : sg.grid2;
-  k.tb = (float)a.blend_t;
+  k.tb = (float)st.blend_t;
   k.ta = 1.0f - k.tb;
   return k;
 }
@@ -228,14 +234,42 @@ __device__ __forceinline__ void update_group_f32(const ConstF32& k, bool drift, 
 // Particles per gather group of a PPT-particle thread.
 template <int PPT> struct GatherGroup { static constexpr int N = PPT < 4 ? PPT : 4; };
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32, bool KEY>
-__device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t chunk) {
-  bool skip;
-  const Segment& sg = chunk_segment(a, chunk, &skip);
-  if (skip) return;
-  const int64_t first = (chunk - sg.chunk_begin) * (int64_t)(kBlock * PPT) + threadIdx.x;
+// All steps of a launch for the N particles of a thread, in registers.
+template <int NSLOT, int N, bool BLEND, bool TSC, bool OFF32>
+__device__ __forceinline__ void run_steps_f32(const PushArgs& a, const Segment& sg, int job, uint32_t (*xu)[3],
+                                              const float (*q0)[3], float (*dq)[3]) {
+#pragma unroll 1
+  for (int s = 0, n = a.nsteps[job]; s < n; ++s) {
+    const ConstF32 k = const_f32<BLEND>(a, a.step[s], sg);
+    const bool drift = a.step[s].do_drift != 0;
+    if constexpr (!BLEND && !TSC) {
+      constexpr int GRP = GatherGroup<N>::N;
+#pragma unroll
+      for (int p = 0; p < N; p += GRP) update_group_f32<NSLOT, GRP, OFF32>(k, drift, xu + p, q0 + p, dq + p);
+    } else {
+#pragma unroll
+      for (int p = 0; p < N; ++p) update_f32<NSLOT, BLEND, TSC, OFF32>(k, drift, xu[p], q0[p], dq[p]);
+    }
+  }
+}
+
+// Sort key of a particle for the next rank pass of job j.
+__device__ __forceinline__ uint32_t next_key(const PushArgs& a, int j, const uint32_t (&xu)[3], const float* q0,
+                                             const float* dq) {
+  const float ma = (float)a.key_ma[j], ts = (float)(a.key_tau[j] * 4294967296.0 / a.box);
+  const float q[3] = {q0[0] + dq[0], q0[1] + dq[1], q0[2] + dq[2]};
+  return sort_key::key_f32(xu, q, ma, ts, a.key_tau[j] != 0.0, 32 - a.log2g, a.key_fine_bits);
+}
+
+template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32>
+__device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t b) {
+  const Segment* sgp;
+  int job;
+  int64_t chunk;
+  if (!block_chunk(a, b, &sgp, &job, &chunk)) return;
+  const Segment& sg = *sgp;
   // chunk-relative arrays: a uniform base and a 32-bit lane index
-  const int64_t c0 = first - threadIdx.x;
+  const int64_t c0 = chunk * (int64_t)(kBlock * PPT);
   const int64_t left = sg.n - c0;
   uint32_t* X[3];
   const float* Q0[3];
@@ -247,7 +281,6 @@ __device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t chunk)
   // together (a store between them would pin the next loads behind it).
   // Slots past the end of the species load its last particle and are not
   // stored, so the loads and updates are straight-line code.
-  const ConstF32 k = const_f32<BLEND>(a, sg);
   uint32_t xu[PPT][3];
   float dq[PPT][3], q0[PPT][3];
   const uint32_t last = (uint32_t)min<int64_t>(left - 1, (int64_t)(PPT * kBlock - 1));
@@ -261,42 +294,32 @@ __device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t chunk)
       dq[p][d] = ldnt(&DQ[d][i]);
     }
   }
-  if constexpr (!BLEND && !TSC) {
-    constexpr int GRP = GatherGroup<PPT>::N;
-#pragma unroll
-    for (int p = 0; p < PPT; p += GRP)
-      update_group_f32<NSLOT, GRP, OFF32>(k, a.do_drift != 0, xu + p, q0 + p, dq + p);
-  } else {
-#pragma unroll
-    for (int p = 0; p < PPT; ++p) update_f32<NSLOT, BLEND, TSC, OFF32>(k, a.do_drift != 0, xu[p], q0[p], dq[p]);
-  }
+  run_steps_f32<NSLOT, PPT, BLEND, TSC, OFF32>(a, sg, job, xu, q0, dq);
+  const bool moved = a.step[0].do_drift != 0;   // only the last step may be a kick alone
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
     const uint32_t i = threadIdx.x + (uint32_t)(p * kBlock);
     if ((int64_t)i >= left) break;
-    if (a.do_drift) {
+    if (moved) {
 #pragma unroll
       for (int d = 0; d < 3; ++d) stnt(xu[p][d], &X[d][i]);
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) stnt(dq[p][d], &DQ[d][i]);
   }
-  if constexpr (KEY) {   // sort keys of the next step's re-sort, from the state just stored
-    const float ma = (float)a.key_ma, ts = (float)(a.key_tau * 4294967296.0 / a.box);
-    uint32_t* K = a.key_out + c0;
+  if ((a.key_mask >> job) & 1u) {   // sort keys of the next rank pass, from the state just stored
+    uint32_t* K = a.key_out + a.batch.job_slot[job] + c0;
 #pragma unroll
     for (int p = 0; p < PPT; ++p) {
       const uint32_t i = threadIdx.x + (uint32_t)(p * kBlock);
       if ((int64_t)i >= left) break;
-      const float q[3] = {q0[p][0] + dq[p][0], q0[p][1] + dq[p][1], q0[p][2] + dq[p][2]};
-      K[i] = sort_key::key_f32(xu[p], q, ma, ts, a.key_tau != 0.0, k.shift, a.key_fine_bits);
+      K[i] = next_key(a, job, xu[p], q0[p], dq[p]);
     }
   }
 }
 
-// A push that also performs the re-sort of the species whose rank pass has
-// run (one, or the jobs of a batch): one block per rank block of kSortBlock
-// particles.  The block reads its
+// A push that also performs the re-sort of its species, whose rank pass has
+// run: one block per rank block of kSortBlock particles.  The block reads its
 // particles in place (coalesced), updates them, stages the whole new state in
 // LDS and writes it out in sorted order, element e of the sorted run to
 // start[bucket[e]] + rank[e] of the other buffer copy, so consecutive threads
@@ -308,25 +331,16 @@ template <int NSLOT, bool BLEND, bool TSC, bool OFF32, int PER>
 __global__ void __launch_bounds__(kSortBlock / PER) k_push_sort_f32(PushArgs a) {
   constexpr int kPer = PER;
   constexpr int kFusedThreads = kSortBlock / PER;
-  __shared__ uint32_t st[10][kSortBlock];
-  // one species (sort_batch.njobs == 0: seg and dseg point at its entries),
-  // or one job of a batched re-sort (seg and seg_alt are the two tables)
-  const SortBatch& sb = a.sort_batch;
-  int64_t blk = xcd_chunk(blockIdx.x, gridDim.x), base = 0;
-  const Segment* sgp = a.seg;
-  const Segment* dsp = a.dseg;
-  const uint32_t* start = a.sort_start;
-  if (sb.njobs > 0) {
-    const int j = batch_block(sb, blockIdx.x, &blk);
-    if (j < 0) return;
-    const int cur = sb.job_cur[j], sp = sb.job_species[j];
-    sgp = (cur ? a.seg_alt : a.seg) + sp;
-    dsp = (cur ? a.seg : a.seg_alt) + sp;
-    base = sb.job_base[j];
-    start = a.sort_start + j * a.sort_nkeys;
-  }
+  __shared__ uint32_t st[11][kSortBlock];
+  const Segment* sgp;
+  int job;
+  int64_t blk;
+  if (!block_chunk(a, blockIdx.x, &sgp, &job, &blk)) return;
   const Segment& sg = *sgp;
-  const Segment& ds = *dsp;
+  const Segment& ds = a.batch.tables[a.batch.job_cur[job] ^ 1][a.batch.job_species[job]];
+  const int64_t base = a.batch.job_base[job];
+  const bool keys = (a.key_mask >> job) & 1u;
+  const uint32_t* start = a.sort_start + job * a.sort_nkeys;
   const uint32_t* sort_src = a.sort_src + base;
   const uint32_t* sort_bucket = a.sort_bucket + base;
   const uint32_t* sort_rank = a.sort_rank + base;
@@ -361,13 +375,7 @@ __global__ void __launch_bounds__(kSortBlock / PER) k_push_sort_f32(PushArgs a) 
   int64_t dst[kPer];
 #pragma unroll
   for (int r = 0; r < kPer; ++r) dst[r] = (int64_t)start[bucket[r]] - base + rank[r];
-  const ConstF32 k = const_f32<BLEND>(a, sg);
-  if constexpr (!BLEND && !TSC) {
-    update_group_f32<NSLOT, kPer, OFF32>(k, true, xu, q0, dq);
-  } else {
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) update_f32<NSLOT, BLEND, TSC, OFF32>(k, true, xu[r], q0[r], dq[r]);
-  }
+  run_steps_f32<NSLOT, kPer, BLEND, TSC, OFF32>(a, sg, job, xu, q0, dq);
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
     const int e = threadIdx.x + r * kFusedThreads;
@@ -379,20 +387,23 @@ __global__ void __launch_bounds__(kSortBlock / PER) k_push_sort_f32(PushArgs a) 
       st[6 + d][e] = __float_as_uint(dq[r][d]);
     }
     st[9][e] = id[r];
+    if (keys) st[10][e] = next_key(a, job, xu[r], q0[r], dq[r]);
   }
   __syncthreads();
   // one array at a time, with cached stores: the fragments that neighbouring
   // blocks write into a bucket merge into whole lines in L2
   uint32_t* out[10] = {ds.xu[0], ds.xu[1], ds.xu[2], (uint32_t*)ds.q0f[0], (uint32_t*)ds.q0f[1],
                        (uint32_t*)ds.q0f[2], (uint32_t*)ds.dqf[0], (uint32_t*)ds.dqf[1], (uint32_t*)ds.dqf[2], ds.id};
-#pragma unroll
-  for (int k = 0; k < 10; ++k) {
+  auto put = [&](uint32_t* to, int k) {
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
       const int e = threadIdx.x + r * kFusedThreads;
-      if (e < cnt) out[k][dst[r]] = st[k][src[r]];
+      if (e < cnt) ((FDF_GLOBAL uint32_t*)to)[dst[r]] = st[k][src[r]];
     }
-  }
+  };
+#pragma unroll
+  for (int k = 0; k < 10; ++k) put(out[k], k);
+  if (keys) put(a.key_out + a.batch.job_slot[job], 10);
 }
 
 // 16-byte piece j of the NSLOT-double cell `cell`.
@@ -445,48 +456,51 @@ __device__ __forceinline__ void gather_stencil_f64(const void* grid, const uint3
   }
 }
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32>
-__device__ __forceinline__ void push_chunk_f64(const PushArgs& a, int64_t chunk) {
+template <int NSLOT, bool BLEND, bool TSC, bool OFF32>
+__device__ __forceinline__ void push_chunk_f64(const PushArgs& a, int64_t b) {
 #pragma clang fp contract(off)
   constexpr int NP = Stencil<TSC>::N;
-  bool skip;
-  const Segment& sg = chunk_segment(a, chunk, &skip);
-  if (skip) return;
-  const int64_t n = sg.n;
-  const int64_t first = (chunk - sg.chunk_begin) * (int64_t)(kBlock * PPT) + threadIdx.x;
+  const Segment* sgp;
+  int job;
+  int64_t chunk;
+  if (!block_chunk(a, b, &sgp, &job, &chunk)) return;
+  const Segment& sg = *sgp;
   const int gm = a.G - 1;
   const double ginv = (double)a.G / a.box;
-  const double ma = sg.m * a.a_kick;
-  const double mah = sg.m * a.a_drift;
   const uint32_t G = (uint32_t)a.G;
   const void* gridA = (BLEND && a.grid_sel) ? sg.grid2 : sg.grid;
   const void* gridB = (BLEND && a.grid_sel) ? sg.grid : sg.grid2;
-  const double tb = a.blend_t, ta = 1.0 - tb;
   // chunk-relative arrays: a uniform base and a 32-bit lane index
-  const int64_t c0 = first - threadIdx.x;
-  const int64_t left = n - c0;
+  const int64_t c0 = chunk * (int64_t)kBlock;
+  const int64_t left = sg.n - c0;
   double* X[3];
   double* Q[3];
   const double* Q0[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) { X[d] = sg.xd[d] + c0; Q[d] = sg.qd[d] + c0; Q0[d] = sg.q0d[d] + c0; }
+  const bool moved = a.step[0].do_drift != 0;   // only the last step may be a kick alone
 
+  const uint32_t i = threadIdx.x;
+  if ((int64_t)i >= left) return;
+  double x[3], q[3], q0[3];
 #pragma unroll
-  for (int p = 0; p < PPT; ++p) {
-    const uint32_t i = threadIdx.x + (uint32_t)(p * kBlock);
-    if ((int64_t)i >= left) break;
-    double x[3], q[3], q0[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      x[d] = ldnt(&X[d][i]);
-      q[d] = ldnt(&Q[d][i]);
-      q0[d] = ldnt(&Q0[d][i]);
-    }
+  for (int d = 0; d < 3; ++d) {
+    x[d] = ldnt(&X[d][i]);
+    q[d] = ldnt(&Q[d][i]);
+    q0[d] = ldnt(&Q0[d][i]);
+  }
+  const double q0sq = fma(q0[0], q0[0], fma(q0[1], q0[1], q0[2] * q0[2]));
+#pragma unroll 1
+  for (int s = 0, n = a.nsteps[job]; s < n; ++s) {
+    const PushStep& st = a.step[s];
+    const double ma = sg.m * st.a_kick;
+    const double mah = sg.m * st.a_drift;
     uint32_t cell[NP];
     double w[NP];
     stencil_f64<TSC>(x, ginv, gm, G, cell, w);
     double g[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (BLEND) {
+      const double tb = st.blend_t, ta = 1.0 - tb;
       double wa[NP], wb[NP];
 #pragma unroll
       for (int cc = 0; cc < NP; ++cc) { wa[cc] = ta * w[cc]; wb[cc] = tb * w[cc]; }
@@ -496,104 +510,80 @@ __device__ __forceinline__ void push_chunk_f64(const PushArgs& a, int64_t chunk)
       gather_stencil_f64<NSLOT, TSC, OFF32>(gridA, cell, w, g);
     }
     if (NSLOT == 4) { g[3] = g[0]; g[4] = g[1]; g[5] = g[2]; }
-    const double q0sq = fma(q0[0], q0[0], fma(q0[1], q0[1], q0[2] * q0[2]));
     const double e0 = sqrt(q0sq + ma * ma);
     const double qg = fma(q0[0], g[3], fma(q0[1], g[4], q0[2] * g[5])) / e0 + g[6];
     const double cphi = q0sq / e0;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const double F = fma(q0[d], qg, fma(-cphi, g[3 + d], -(e0 * g[d])));
-      q[d] = fma(a.kick, F, q[d]);
+      q[d] = fma(st.kick, F, q[d]);
     }
-    if (a.do_drift) {
+    if (st.do_drift) {
       const double e = sqrt(fma(q[0], q[0], fma(q[1], q[1], q[2] * q[2])) + mah * mah);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        double xn = fmod(fma(a.drift, q[d] / e, x[d]), a.box);   // floor-mod as numpy.mod
-        if (xn < 0.0) xn += a.box;
-        stnt(xn, &X[d][i]);
-      }
+      for (int d = 0; d < 3; ++d) x[d] = wrap_box(fma(st.drift, q[d] / e, x[d]), a.box);
     }
+  }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) stnt(q[d], &Q[d][i]);
+  for (int d = 0; d < 3; ++d) {
+    if (moved) stnt(x[d], &X[d][i]);
+    stnt(q[d], &Q[d][i]);
   }
 }
 
 // Chunk loop.  One block per chunk, or (persistent) a fixed grid whose
 // blocks stride over the chunks; either way each XCD (block id mod 8) walks a
-// contiguous eighth of the chunk range.
-template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32, bool KEY = false>
+// contiguous eighth of every species' chunks.
+template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32>
 __global__ void __launch_bounds__(kBlock) k_push_f32(PushArgs a) {
-  if (!a.persistent) {
-    const int64_t c = launch_chunk(a);
-    if (c >= 0) push_chunk_f32<NSLOT, PPT, BLEND, TSC, OFF32, KEY>(a, c);
-    return;
-  }
-  const int64_t per = (a.total_chunks + 7) / 8, x = blockIdx.x % 8, stride = gridDim.x / 8;
-  const int64_t end = min((x + 1) * per, a.total_chunks);
-  for (int64_t c = x * per + blockIdx.x / 8; c < end; c += stride)
-    push_chunk_f32<NSLOT, PPT, BLEND, TSC, OFF32, KEY>(a, c);
+  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x) push_chunk_f32<NSLOT, PPT, BLEND, TSC, OFF32>(a, b);
 }
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32>
+template <int NSLOT, bool BLEND, bool TSC, bool OFF32>
 __global__ void __launch_bounds__(kBlock) k_push_f64(PushArgs a) {
-  if (!a.persistent) {
-    const int64_t c = launch_chunk(a);
-    if (c >= 0) push_chunk_f64<NSLOT, PPT, BLEND, TSC, OFF32>(a, c);
-    return;
-  }
-  const int64_t per = (a.total_chunks + 7) / 8, x = blockIdx.x % 8, stride = gridDim.x / 8;
-  const int64_t end = min((x + 1) * per, a.total_chunks);
-  for (int64_t c = x * per + blockIdx.x / 8; c < end; c += stride) push_chunk_f64<NSLOT, PPT, BLEND, TSC, OFF32>(a, c);
+  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x) push_chunk_f64<NSLOT, BLEND, TSC, OFF32>(a, b);
 }
+
+// Block count and LDS reserve of a plain push; byte offsets of the mesh fit 32 bits?
+struct PushLaunch {
+  dim3 grid, block;
+  bool off32;
+  explicit PushLaunch(const PushArgs& a)
+      : grid((unsigned)(a.persistent ? a.persistent : a.grid_blocks)), block(kBlock),
+        off32((uint64_t)a.G * a.G * a.G * (uint64_t)(a.nslot * (a.fp64 ? 8 : 2)) <= (1ull << 32)) {}
+};
 
 template <int PPT, bool BLEND, bool TSC>
 void push_launch(const PushArgs& a, hipStream_t s) {
-  const int64_t grid_blocks = a.persistent ? a.persistent : (a.xcd_blocks > 0 ? a.xcd_blocks : a.total_chunks);
-  const dim3 grid((unsigned)grid_blocks), block(kBlock);
-  // byte offsets of the mesh fit 32 bits?
-  const bool off32 = (uint64_t)a.G * a.G * a.G * (uint64_t)(a.nslot * (a.fp64 ? 8 : 2)) <= (1ull << 32);
-  if (a.fp64) {
-    if (off32) {
-      if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, PPT, BLEND, TSC, true>), grid, block, a.lds_reserve, s, a);
-      else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, PPT, BLEND, TSC, true>), grid, block, a.lds_reserve, s, a);
-      else hipLaunchKernelGGL((k_push_f64<4, PPT, BLEND, TSC, true>), grid, block, a.lds_reserve, s, a);
-    } else {
-      if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, PPT, BLEND, TSC, false>), grid, block, a.lds_reserve, s, a);
-      else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, PPT, BLEND, TSC, false>), grid, block, a.lds_reserve, s, a);
-      else hipLaunchKernelGGL((k_push_f64<4, PPT, BLEND, TSC, false>), grid, block, a.lds_reserve, s, a);
-    }
+  const PushLaunch l(a);
+  if (l.off32) {
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f32<4, PPT, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
   } else {
-    if constexpr (!BLEND && !TSC) {
-      if (a.key_out) {   // this push also writes the sort keys of the next step's re-sort
-        if (off32) {
-          if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, false, false, true, true>), grid, block, a.lds_reserve, s, a);
-          else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, false, false, true, true>), grid, block, a.lds_reserve, s, a);
-          else hipLaunchKernelGGL((k_push_f32<4, PPT, false, false, true, true>), grid, block, a.lds_reserve, s, a);
-        } else {
-          if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, false, false, false, true>), grid, block, a.lds_reserve, s, a);
-          else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, false, false, false, true>), grid, block, a.lds_reserve, s, a);
-          else hipLaunchKernelGGL((k_push_f32<4, PPT, false, false, false, true>), grid, block, a.lds_reserve, s, a);
-        }
-        return;
-      }
-    }
-    if (off32) {
-      if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, BLEND, TSC, true>), grid, block, a.lds_reserve, s, a);
-      else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, BLEND, TSC, true>), grid, block, a.lds_reserve, s, a);
-      else hipLaunchKernelGGL((k_push_f32<4, PPT, BLEND, TSC, true>), grid, block, a.lds_reserve, s, a);
-    } else {
-      if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, BLEND, TSC, false>), grid, block, a.lds_reserve, s, a);
-      else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, BLEND, TSC, false>), grid, block, a.lds_reserve, s, a);
-      else hipLaunchKernelGGL((k_push_f32<4, PPT, BLEND, TSC, false>), grid, block, a.lds_reserve, s, a);
-    }
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f32<4, PPT, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
+  }
+}
+
+template <bool BLEND, bool TSC>
+void push_launch_f64(const PushArgs& a, hipStream_t s) {
+  const PushLaunch l(a);
+  if (l.off32) {
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f64<4, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
+  } else {
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f64<4, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
   }
 }
 
 template <bool BLEND, bool TSC, int PER>
 void push_sort_launch_per(const PushArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)(a.sort_batch.njobs > 0 ? batch_grid(a.sort_batch) : a.total_chunks)),
-      block(kSortBlock / PER);
+  const dim3 grid((unsigned)a.grid_blocks), block(kSortBlock / PER);
   const bool off32 = (uint64_t)a.G * a.G * a.G * (uint64_t)(a.nslot * 2) <= (1ull << 32);
   if (off32) {
     if (a.nslot == 8) hipLaunchKernelGGL((k_push_sort_f32<8, BLEND, TSC, true, PER>), grid, block, a.lds_reserve, s, a);
@@ -624,6 +614,16 @@ void push_ppt(const PushArgs& a, hipStream_t s) {
   }
 }
 
+void push_f64(const PushArgs& a, hipStream_t s) {
+  if (a.tsc) {
+    if (a.blend) push_launch_f64<true, true>(a, s);
+    else push_launch_f64<false, true>(a, s);
+  } else {
+    if (a.blend) push_launch_f64<true, false>(a, s);
+    else push_launch_f64<false, false>(a, s);
+  }
+}
+
 }  // namespace
 
 int push_chunk_particles(int ppt) { return kBlock * ppt; }
@@ -640,6 +640,7 @@ void launch_push_sort(const PushArgs& a, hipStream_t s) {
 
 void launch_push(const PushArgs& a, hipStream_t s) {
   if (a.eom != 0) { launch_push_eom(a, s); return; }
+  if (a.fp64) { push_f64(a, s); return; }
   switch (a.ppt) {
     case 1: push_ppt<1>(a, s); break;
     case 2: push_ppt<2>(a, s); break;

@@ -1,5 +1,5 @@
-// Pieces shared by the push kernels: block size, the XCD-aware chunk order,
-// segment lookup and non-temporal particle-state access.
+// Pieces shared by the push kernels: block size, segment lookup, stencils and
+// non-temporal particle-state access.
 #pragma once
 #include "fdf_device.h"
 #include "fdf_internal.h"
@@ -9,54 +9,15 @@ namespace push_detail {
 
 constexpr int kBlock = 256;
 
-// Consecutive block ids are dealt round-robin to the 8 XCDs; remap so each
-// XCD (own L2) walks a contiguous range of chunks, i.e. a compact region of
-// sorted particles.
-__device__ __forceinline__ int64_t xcd_chunk(int64_t b, int64_t nb) {
-  const int64_t full = nb - nb % 8;
-  if (b >= full) return b;
-  const int64_t per = full / 8;
-  return (b % 8) * per + b / 8;
-}
-
-// Several segments (species) in one launch: each XCD takes the same share of
-// every segment, a contiguous eighth of its chunks, and walks its shares in
-// segment order.  A contiguous eighth of the whole chunk range would give
-// whole species to single XCDs, and species whose particles cost more (sparse
-// seeds, whose gathers share few mesh lines) would hold the launch on those
-// XCDs.  -1: a block past its XCD's share (the grid is 8 times the largest).
-__device__ __forceinline__ int64_t xcd_segment_chunk(const PushArgs& a, int64_t b) {
-  const int64_t x = b & 7;
-  int64_t l = b >> 3;
-  for (int s = 0; s < a.nseg; ++s) {
-    const int64_t cb = a.seg[s].chunk_begin;
-    const int64_t n = (s + 1 < a.nseg ? a.seg[s + 1].chunk_begin : a.total_chunks) - cb;
-    const int64_t lo = n * x / 8, hi = n * (x + 1) / 8;
-    if (l < hi - lo) return cb + lo + l;
-    l -= hi - lo;
-  }
-  return -1;
-}
-
-// The chunk of this block in a non-persistent launch, or -1.
-__device__ __forceinline__ int64_t launch_chunk(const PushArgs& a) {
-  return a.xcd_blocks > 0 ? xcd_segment_chunk(a, blockIdx.x) : xcd_chunk(blockIdx.x, gridDim.x);
-}
-
-__device__ __forceinline__ int find_segment(const Segment* seg, int nseg, int64_t chunk) {
-  int s = 0;
-  while (s + 1 < nseg && seg[s + 1].chunk_begin <= chunk) ++s;
-  return s;
-}
-
-// The segment of a chunk in the copy that holds its species' current state
-// (both copies list the same chunk ranges); *skip: the species is left alone
-// by this launch.
-__device__ __forceinline__ const Segment& chunk_segment(const PushArgs& a, int64_t chunk, bool* skip) {
-  const int s = find_segment(a.seg, a.nseg, chunk);
-  const bool low = s < 64;
-  *skip = low && ((a.skip_mask >> s) & 1ull);
-  return (low && ((a.alt_mask >> s) & 1ull)) ? a.seg_alt[s] : a.seg[s];
+// The species (its segment in the copy that holds its state), job and
+// block-sized chunk of block b of a launch; false: a block without work.
+__device__ __forceinline__ bool block_chunk(const PushArgs& a, int64_t b, const Segment** sg, int* job,
+                                            int64_t* chunk) {
+  const int j = batch_block(a.batch, b, chunk);
+  if (j < 0) return false;
+  *job = j;
+  *sg = a.batch.tables[a.batch.job_cur[j]] + a.batch.job_species[j];
+  return true;
 }
 
 // The state arrays live in device global memory.  Their pointers come from a
@@ -225,6 +186,14 @@ __device__ __forceinline__ void stencil_f64(const double* x, double ginv, int gm
           w[9 * a + 3 * b + c] = (wt[0][a] * wt[1][b]) * wt[2][c];
         }
   }
+}
+
+// x in [0, L) after a drift of less than L, as numpy.mod(x, L) (floor-mod):
+// fmod(x, L) is x below L and the exact difference x - L from L to 2 L.
+__device__ __forceinline__ double wrap_box(double x, double L) {
+  double r = fabs(x) < L ? x : x - L;
+  if (!(x > -L && x < 2.0 * L)) r = fmod(x, L);
+  return r < 0.0 ? r + L : r;
 }
 
 }  // namespace push_detail

@@ -131,46 +131,47 @@ __device__ __forceinline__ R eom_drift_factor(int eom, R q2, R ie2, const R* g) 
   return (R)0;
 }
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC>
-__device__ __forceinline__ void push_chunk_eom_f32(const PushArgs& a, int64_t chunk) {
+template <int NSLOT, bool BLEND, bool TSC>
+__device__ __forceinline__ void push_chunk_eom_f32(const PushArgs& a, int64_t b) {
 #pragma clang fp contract(off)
   constexpr int NP = Stencil<TSC>::N;
-  bool skip;
-  const Segment& sg = chunk_segment(a, chunk, &skip);
-  if (skip) return;
-  const int64_t n = sg.n;
-  const int64_t first = (chunk - sg.chunk_begin) * (int64_t)(kBlock * PPT) + threadIdx.x;
+  const Segment* sgp;
+  int job;
+  int64_t chunk;
+  if (!block_chunk(a, b, &sgp, &job, &chunk)) return;
+  const Segment& sg = *sgp;
+  const int64_t i = chunk * (int64_t)kBlock + threadIdx.x;
+  if (i >= sg.n) return;
   const int shift = 32 - a.log2g;
   const uint32_t gmask = (uint32_t)a.G - 1u;
   const float finv = __uint_as_float((uint32_t)(127 - shift) << 23);   // 2^-shift
-  const float kicks[2] = {(float)a.kick, (float)a.kick_open};
-  const float ma = (float)(sg.m * a.a_kick);
-  const float mah = (float)(sg.m * a.a_drift);
-  const float ma2 = ma * ma, mah2 = mah * mah;
-  const float dscale = (float)(a.drift * 4294967296.0 / a.box);
   const size_t G = (size_t)a.G;
   const void* gridA = (BLEND && a.grid_sel) ? sg.grid2 : sg.grid;
   const void* gridB = (BLEND && a.grid_sel) ? sg.grid : sg.grid2;
-  const float tb = (float)a.blend_t, ta = 1.0f - tb;
+  const bool moved = a.step[0].do_drift != 0;   // only the last step may be a kick alone
 
+  uint32_t xu[3];
+  float q0[3], dq[3], q[3];
 #pragma unroll
-  for (int p = 0; p < PPT; ++p) {
-    const int64_t i = first + (int64_t)p * kBlock;
-    if (i >= n) break;
-    uint32_t xu[3];
-    float q0[3], dq[3], q[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      xu[d] = ldnt(&sg.xu[d][i]);
-      q0[d] = ldnt(&sg.q0f[d][i]);
-      dq[d] = ldnt(&sg.dqf[d][i]);
-      q[d] = q0[d] + dq[d];
-    }
+  for (int d = 0; d < 3; ++d) {
+    xu[d] = ldnt(&sg.xu[d][i]);
+    q0[d] = ldnt(&sg.q0f[d][i]);
+    dq[d] = ldnt(&sg.dqf[d][i]);
+    q[d] = q0[d] + dq[d];
+  }
+#pragma unroll 1
+  for (int s = 0, n = a.nsteps[job]; s < n; ++s) {
+    const PushStep& st = a.step[s];
+    const float kicks[2] = {(float)st.kick, (float)st.kick_open};
+    const float ma = (float)(sg.m * st.a_kick);
+    const float mah = (float)(sg.m * st.a_drift);
+    const float ma2 = ma * ma, mah2 = mah * mah;
     size_t cell[NP];
     float w[NP];
     stencil_u32<TSC>(xu, shift, gmask, finv, G, cell, w);
     float g[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
     if (BLEND) {
+      const float tb = (float)st.blend_t, ta = 1.0f - tb;
       float wa[NP], wb[NP];
 #pragma unroll
       for (int cc = 0; cc < NP; ++cc) { wa[cc] = ta * w[cc]; wb[cc] = tb * w[cc]; }
@@ -190,7 +191,7 @@ __device__ __forceinline__ void push_chunk_eom_f32(const PushArgs& a, int64_t ch
         q[d] = q0[d] + dq[d];
       }
     }
-    if (a.do_drift) {
+    if (st.do_drift) {
       const float qq = fmaf(q[0], q[0], fmaf(q[1], q[1], q[2] * q[2]));
       const float e2 = qq + mah2;
       const float ie = 1.0f / sqrtf(e2);
@@ -198,49 +199,53 @@ __device__ __forceinline__ void push_chunk_eom_f32(const PushArgs& a, int64_t ch
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         const float v = q[d] * ie;
-        const int disp = __float2int_rn(dscale * fmaf(v, sf, v));
-        stnt(xu[d] + (uint32_t)disp, &sg.xu[d][i]);
+        xu[d] += (uint32_t)__float2int_rn(st.dscale * fmaf(v, sf, v));
       }
     }
+  }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) stnt(dq[d], &sg.dqf[d][i]);
+  for (int d = 0; d < 3; ++d) {
+    if (moved) stnt(xu[d], &sg.xu[d][i]);
+    stnt(dq[d], &sg.dqf[d][i]);
   }
 }
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC>
-__device__ __forceinline__ void push_chunk_eom_f64(const PushArgs& a, int64_t chunk) {
+template <int NSLOT, bool BLEND, bool TSC>
+__device__ __forceinline__ void push_chunk_eom_f64(const PushArgs& a, int64_t b) {
 #pragma clang fp contract(off)
   constexpr int NP = Stencil<TSC>::N;
-  bool skip;
-  const Segment& sg = chunk_segment(a, chunk, &skip);
-  if (skip) return;
-  const int64_t n = sg.n;
-  const int64_t first = (chunk - sg.chunk_begin) * (int64_t)(kBlock * PPT) + threadIdx.x;
+  const Segment* sgp;
+  int job;
+  int64_t chunk;
+  if (!block_chunk(a, b, &sgp, &job, &chunk)) return;
+  const Segment& sg = *sgp;
+  const int64_t i = chunk * (int64_t)kBlock + threadIdx.x;
+  if (i >= sg.n) return;
   const int gm = a.G - 1;
   const double ginv = (double)a.G / a.box;
-  const double kicks[2] = {a.kick, a.kick_open};
-  const double ma = sg.m * a.a_kick;
-  const double mah = sg.m * a.a_drift;
   const size_t G = (size_t)a.G;
   const void* gridA = (BLEND && a.grid_sel) ? sg.grid2 : sg.grid;
   const void* gridB = (BLEND && a.grid_sel) ? sg.grid : sg.grid2;
-  const double tb = a.blend_t, ta = 1.0 - tb;
+  const bool moved = a.step[0].do_drift != 0;   // only the last step may be a kick alone
 
+  double x[3], q[3];
 #pragma unroll
-  for (int p = 0; p < PPT; ++p) {
-    const int64_t i = first + (int64_t)p * kBlock;
-    if (i >= n) break;
-    double x[3], q[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      x[d] = ldnt(&sg.xd[d][i]);
-      q[d] = ldnt(&sg.qd[d][i]);
-    }
+  for (int d = 0; d < 3; ++d) {
+    x[d] = ldnt(&sg.xd[d][i]);
+    q[d] = ldnt(&sg.qd[d][i]);
+  }
+#pragma unroll 1
+  for (int s = 0, n = a.nsteps[job]; s < n; ++s) {
+    const PushStep& st = a.step[s];
+    const double kicks[2] = {st.kick, st.kick_open};
+    const double ma = sg.m * st.a_kick;
+    const double mah = sg.m * st.a_drift;
     size_t cell[NP];
     double w[NP];
     stencil_f64<TSC>(x, ginv, gm, G, cell, w);
     double g[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (BLEND) {
+      const double tb = st.blend_t, ta = 1.0 - tb;
       double wa[NP], wb[NP];
 #pragma unroll
       for (int cc = 0; cc < NP; ++cc) { wa[cc] = ta * w[cc]; wb[cc] = tb * w[cc]; }
@@ -257,7 +262,7 @@ __device__ __forceinline__ void push_chunk_eom_f64(const PushArgs& a, int64_t ch
 #pragma unroll
       for (int d = 0; d < 3; ++d) q[d] = fma(kicks[h], F[d], q[d]);
     }
-    if (a.do_drift) {
+    if (st.do_drift) {
       const double qq = fma(q[0], q[0], fma(q[1], q[1], q[2] * q[2]));
       const double e2 = qq + mah * mah;
       const double e = sqrt(e2);
@@ -265,72 +270,48 @@ __device__ __forceinline__ void push_chunk_eom_f64(const PushArgs& a, int64_t ch
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         const double v = q[d] / e;
-        double xn = fmod(fma(a.drift, fma(v, sf, v), x[d]), a.box);   // floor-mod as numpy.mod
-        if (xn < 0.0) xn += a.box;
-        stnt(xn, &sg.xd[d][i]);
+        x[d] = wrap_box(fma(st.drift, fma(v, sf, v), x[d]), a.box);
       }
     }
+  }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) stnt(q[d], &sg.qd[d][i]);
+  for (int d = 0; d < 3; ++d) {
+    if (moved) stnt(x[d], &sg.xd[d][i]);
+    stnt(q[d], &sg.qd[d][i]);
   }
 }
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC>
+template <int NSLOT, bool BLEND, bool TSC>
 __global__ void __launch_bounds__(kBlock) k_push_eom_f32(PushArgs a) {
-  if (!a.persistent) {
-    const int64_t c = launch_chunk(a);
-    if (c >= 0) push_chunk_eom_f32<NSLOT, PPT, BLEND, TSC>(a, c);
-    return;
-  }
-  const int64_t per = (a.total_chunks + 7) / 8, x = blockIdx.x % 8, stride = gridDim.x / 8;
-  const int64_t end = min((x + 1) * per, a.total_chunks);
-  for (int64_t c = x * per + blockIdx.x / 8; c < end; c += stride) push_chunk_eom_f32<NSLOT, PPT, BLEND, TSC>(a, c);
+  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x) push_chunk_eom_f32<NSLOT, BLEND, TSC>(a, b);
 }
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC>
+template <int NSLOT, bool BLEND, bool TSC>
 __global__ void __launch_bounds__(kBlock) k_push_eom_f64(PushArgs a) {
-  if (!a.persistent) {
-    const int64_t c = launch_chunk(a);
-    if (c >= 0) push_chunk_eom_f64<NSLOT, PPT, BLEND, TSC>(a, c);
-    return;
-  }
-  const int64_t per = (a.total_chunks + 7) / 8, x = blockIdx.x % 8, stride = gridDim.x / 8;
-  const int64_t end = min((x + 1) * per, a.total_chunks);
-  for (int64_t c = x * per + blockIdx.x / 8; c < end; c += stride) push_chunk_eom_f64<NSLOT, PPT, BLEND, TSC>(a, c);
+  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x) push_chunk_eom_f64<NSLOT, BLEND, TSC>(a, b);
 }
 
-template <int PPT, bool BLEND, bool TSC>
+template <bool BLEND, bool TSC>
 void eom_launch(const PushArgs& a, hipStream_t s) {
-  const int64_t grid_blocks = a.persistent ? a.persistent : (a.xcd_blocks > 0 ? a.xcd_blocks : a.total_chunks);
-  const dim3 grid((unsigned)grid_blocks), block(kBlock);
+  const dim3 grid((unsigned)(a.persistent ? a.persistent : a.grid_blocks)), block(kBlock);
   if (a.fp64) {
-    if (a.nslot == 8) hipLaunchKernelGGL((k_push_eom_f64<8, PPT, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
-    else hipLaunchKernelGGL((k_push_eom_f64<4, PPT, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_eom_f64<8, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_eom_f64<4, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
   } else {
-    if (a.nslot == 8) hipLaunchKernelGGL((k_push_eom_f32<8, PPT, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
-    else hipLaunchKernelGGL((k_push_eom_f32<4, PPT, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
-  }
-}
-
-template <int PPT>
-void eom_ppt(const PushArgs& a, hipStream_t s) {
-  if (a.tsc) {
-    if (a.blend) eom_launch<PPT, true, true>(a, s);
-    else eom_launch<PPT, false, true>(a, s);
-  } else {
-    if (a.blend) eom_launch<PPT, true, false>(a, s);
-    else eom_launch<PPT, false, false>(a, s);
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_eom_f32<8, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_eom_f32<4, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
   }
 }
 
 }  // namespace
 
 void launch_push_eom(const PushArgs& a, hipStream_t s) {
-  switch (a.ppt) {
-    case 1: eom_ppt<1>(a, s); break;
-    case 2: eom_ppt<2>(a, s); break;
-    case 4: eom_ppt<4>(a, s); break;
-    default: eom_ppt<8>(a, s); break;
+  if (a.tsc) {
+    if (a.blend) eom_launch<true, true>(a, s);
+    else eom_launch<false, true>(a, s);
+  } else {
+    if (a.blend) eom_launch<true, false>(a, s);
+    else eom_launch<false, false>(a, s);
   }
 }
 

@@ -312,17 +312,17 @@ __device__ __forceinline__ void rank_block(const SortArgs& a, const RankView& g,
 // One species (batch.njobs == 0), or one block of a batched re-sort.
 __global__ void __launch_bounds__(kRankThreads) k_sort_rank(SortArgs a) {
   if (a.batch.njobs == 0) {
-    rank_block(a, view_of(a.seg, a.predict_tau, a.ma, a.keys, a.count, a.rank, a.bucket, a.src),
+    rank_block(a, view_of(a.seg, a.predict_tau, a.ma, nullptr, a.count, a.rank, a.bucket, a.src),
                xcd_block(blockIdx.x, gridDim.x));
     return;
   }
   int64_t local;
   const int j = batch_block(a.batch, blockIdx.x, &local);
   if (j < 0) return;
-  const SortBatch& b = a.batch;
+  const SpeciesBatch& b = a.batch;
   const Segment& g = b.tables[b.job_cur[j]][b.job_species[j]];
   const int64_t base = b.job_base[j];
-  rank_block(a, view_of(g, b.job_tau[j], b.job_ma[j], a.keys ? a.keys + base : nullptr, a.count + j * a.nkeys,
+  rank_block(a, view_of(g, b.job_tau[j], b.job_ma[j], (b.keyed_mask >> j) & 1u ? a.keys + b.job_slot[j] : nullptr, a.count + j * a.nkeys,
                         a.rank + base, a.bucket + base, a.src + base), local);
 }
 

@@ -33,6 +33,7 @@ EXPORTS = [
     "fdf_read_schedule", "fdf_get_info", "fdf_sync", "fdf_timing_enable",
     "fdf_read_timing", "fdf_timing_reset", "fdf_status_string", "fdf_last_error",
     "fdf_get_tuning", "fdf_set_tuning", "fdf_power_spectrum_noalloc", "fdf_read_work",
+    "fdf_read_passes",
 ]
 
 
@@ -120,6 +121,7 @@ def load():
         "fdf_read_timing": [P, I32, PD, ctypes.POINTER(I64)],
         "fdf_timing_reset": [P],
         "fdf_read_work": [P, I32, ctypes.POINTER(I64)],
+        "fdf_read_passes": [P, I32, ctypes.POINTER(I64)],
         "fdf_get_tuning": [P, ctypes.POINTER(Tuning)],
         "fdf_set_tuning": [P, ctypes.POINTER(Tuning)],
     }
@@ -402,6 +404,14 @@ class Context:
         w = (ctypes.c_int64 * 3)()
         self._check(self.lib.fdf_read_work(self.ctx, KERNEL_CLASSES[kernel_class], w), "fdf_read_work")
         return int(w[0]), int(w[1]), int(w[2])
+
+    def read_passes(self, kernel_class):
+        """(particles whose state the timed launches of a push class read and
+        wrote, the same for kick-only launches); a launch of several steps
+        counts once."""
+        w = (ctypes.c_int64 * 2)()
+        self._check(self.lib.fdf_read_passes(self.ctx, KERNEL_CLASSES[kernel_class], w), "fdf_read_passes")
+        return int(w[0]), int(w[1])
 
     def timing_reset(self):
         self._check(self.lib.fdf_timing_reset(self.ctx), "fdf_timing_reset")

@@ -1,0 +1,56 @@
+"""Launches that carry the particles through several steps: states by id equal
+those of one-step launches bit for bit, at the edges of the longest span (24
+steps) and with species on cadences of their own."""
+import numpy as np
+import pytest
+
+from paper_2207_14256_amd import fastdf, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _states(cfg, n, **tuning):
+    ctx, _, species = fastdf.setup_workload(cfg, tuning=tuning)
+    ctx.timing()
+    ctx.step(n)
+    out = [ctx.read_state(s) for s in species]
+    work = [ctx.read_work(k) for k in ("push", "push_sort")]
+    passes = [ctx.read_passes(k) for k in ("push", "push_sort")]
+    ctx.close()
+    return out, np.sum(work, axis=0), np.sum(passes, axis=0)
+
+
+def _cfg(prec, eom="separable", order=1, **kw):
+    cfg = workloads.small("c3", grid_n=16, n_side=13, n_steps=60, precision=prec, box_mpc=400.0, z_begin=1e5,
+                          z_end=500.0, sort_every=1, sort_cells=0.0, eom=eom, interp_order=order, **kw)
+    cfg["species"].append(dict(field=0, m=0.02, n_side=11, seed=77))
+    return cfg
+
+
+@pytest.mark.parametrize("n", [1, 2, 23, 24, 25, 49])
+@pytest.mark.parametrize("prec,eom,order", [("fp32", "separable", 1), ("fp32", "separable", 2),
+                                            ("fp64", "separable", 1), ("fp64", "exact", 2),
+                                            ("fp32", "exact", 1)])
+def test_spans_bit_identical_to_single_steps(prec, eom, order, n):
+    cfg = _cfg(prec, eom, order)
+    total = 13 ** 3 + 11 ** 3
+    one, w1, p1 = _states(cfg, n, sort_every=1)      # every launch carries out one step
+    many, w, p = _states(cfg, n, sort_every=0)       # spans of up to 24 steps
+    for (xa, qa), (xb, qb) in zip(one, many):
+        assert np.array_equal(xa, xb) and np.array_equal(qa, qb)
+    assert tuple(w1[:2]) == tuple(w[:2]) == (n * total, total)
+    # n + 1 kicks in launches of at most 24
+    assert sum(p) == total * -(-(n + 1) // 24)
+
+
+@pytest.mark.parametrize("model,tol", [("radmat", 0.0), ("radmat", 0.01)])
+def test_spans_with_time_dependent_grids(model, tol):
+    """A launch ends where the grids change; the states do not depend on the
+    re-sort cadence that cuts the spans further."""
+    cfg = _cfg("fp32", model=model, omega_r=1e-4, superstep_tol=tol)
+    ref, _, _ = _states(cfg, 40, sort_every=0)
+    for tuning in (dict(sort_every=1), dict(sort_every=7), dict(sort_every=7, sort_fused=0),
+                   dict(sort_every=7, sort_keys_push=0), dict(sort_cells=1.5)):
+        got, _, _ = _states(cfg, 40, **tuning)
+        for (xa, qa), (xb, qb) in zip(ref, got):
+            assert np.array_equal(xa, xb) and np.array_equal(qa, qb)
