@@ -283,7 +283,8 @@ struct SpeciesRec {
   Segment seg[2];   // state buffers (second copy only with sorting)
   int cur = 0;
   bool pristine = false;   // state is exactly the sampled one (no pre-IC, not stepped)
-  bool sorted = false;     // has been re-sorted since it was created
+  bool sorted = false;     // in spatial order
+  bool placed = false;     // that order is the one of its creation, without a prediction
   int order_time = -1;     // integer time from which its current order is meant to be used (-1: none)
   double drift_cells = 0;  // typical drift since that time, in mesh cells
 };
@@ -292,8 +293,8 @@ struct SpeciesRec {
 // state it leaves behind, so a replay can stand in for the enqueue.
 struct HostStepState {
   int step_index = 0;
-  std::vector<int> ints;           // per species: copy of its state, sorted, order time, pristine;
-                                   // per field: two super-step set tags
+  std::vector<int> ints;           // per species: copy of its state, sorted, placed, order time,
+                                   // pristine; per field: two super-step set tags
   std::vector<double> drift_cells; // per species
   std::vector<double> grid_a;      // per field; NaN = no grid
   bool operator==(const HostStepState& o) const {
@@ -675,13 +676,9 @@ struct SortCadence {
   bool sorted;
   int order_time;
   double drift_cells;
+  bool placed = false;
 };
 constexpr int kNeverDue = 1 << 30;
-
-bool sort_due(const fdf_ctx* c, const SortCadence& s, int u) {
-  if (c->sort_cells > 0) return !s.sorted || s.drift_cells >= c->sort_cells;
-  return c->sort_every > 0 && u % c->sort_every == 0 && s.order_time != u;
-}
 
 int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
   const int dir = p.n > 0 ? 1 : -1;
@@ -696,6 +693,24 @@ int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, 
   if (c->sort_every <= 0) return kNeverDue;
   const int r = u % c->sort_every;
   return dir > 0 ? c->sort_every - r : (r ? r : c->sort_every);
+}
+
+// A species in the order of its creation is due at once if its particles will
+// drift further than this (in cells) over the gathers of the first interval: a
+// re-sort orders by the positions at the middle of the interval, creation by
+// those at its start.
+constexpr double kPlacedDrift = 3.0;
+
+bool sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
+  if (s.placed && (c->sort_cells > 0 || c->sort_every > 0)) {
+    const int dir = p.n > 0 ? 1 : -1, len = steps_until_due(c, p, s, u, m);
+    double dr, ah, cells = 0.0;
+    for (int k = 0; k + 1 < len && cells <= kPlacedDrift && p.drift(u + dir * k, &dr, &ah); ++k)
+      cells += typical_drift_cells(c, dr, ah, m);
+    if (cells > kPlacedDrift) return true;
+  }
+  if (c->sort_cells > 0) return !s.sorted || s.drift_cells >= c->sort_cells;
+  return c->sort_every > 0 && u % c->sort_every == 0 && s.order_time != u;
 }
 
 // Positions to order by for the interval that starts `lead` steps after u (as
@@ -742,7 +757,7 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
   const bool fusable = c->sort_fused && c->cfg.precision == FDF_PREC_FP32 && c->cfg.eom == FDF_EOM_SEPARABLE;
   double dr, ah;
   SortCadence now = s;
-  if (sort_due(c, s, u)) {
+  if (sort_due(c, p, s, u, m)) {
     // a first sort takes two passes (the second orders cells in buckets)
     const bool first = !s.sorted;
     const bool ride = fusable && p.drift(u + dir, &dr, &ah);   // steps follow that use the new order
@@ -773,6 +788,7 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
 SortCadence after_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, const LaunchPlan& l, double m, int j) {
   const int dir = p.n > 0 ? 1 : -1, u = p.time(j);
   SortCadence r = s;
+  r.placed = false;
   if (l.sort_first) r = SortCadence{true, u, 0.0};
   double dr, ah;
   for (int k = 0; k < l.span && j + k < p.nabs(); ++k)
@@ -960,6 +976,47 @@ int new_species(fdf_ctx* c, int32_t field_id, double m, int64_t n, uint64_t seed
   c->seg_dirty = true;
   *sid = (int32_t)c->species.size() - 1;
   return FDF_OK;
+}
+
+// Puts the ids of a new species in the spatial order of its sampled positions
+// (its state is then sampled by id).  Every gather and deposit runs on that
+// order until the particles have drifted out of it, which a context that
+// never re-sorts has no other way to get, and it stands in for a first sort.
+// Not done for a mesh that one XCD's L2 holds in a context without re-sorts
+// (the gathers hit there in any order), when the temporaries (8 B per
+// particle and the tile counts, in the sort's arrays or else in the FFT
+// scratch) do not fit, or when they would overwrite a density that can still
+// be read.  Returns whether the ids are in order.
+constexpr size_t kL2Bytes = (size_t)4 << 20;   // L2 of one XCD
+
+bool place_species(fdf_ctx* c, SpeciesRec& s) {
+  const int G = c->cfg.grid_n, tiles = std::min(G, 256);
+  const bool sorting = c->cfg.sort_every > 0;
+  if (!sorting && (c->lay.field_grid_bytes <= kL2Bytes || c->have_density)) return false;
+  PlaceArgs a{};
+  a.seg = s.seg[0];
+  a.seed = s.seed;
+  a.cell_shift = 32 - ilog2(G);
+  a.fine_bits = ilog2(G / tiles);
+  a.nkeys = (int64_t)tiles * tiles * tiles;
+  if (sorting) {
+    a.count = (uint32_t*)(c->ws + c->lay.sort_count);
+    a.scan_scratch = (uint32_t*)(c->ws + c->lay.sort_scan);
+    a.key = (uint32_t*)(c->ws + c->lay.sort_bucket);
+    a.rank = (uint32_t*)(c->ws + c->lay.sort_rank);
+  } else {
+    // the FFT scratch and the density halves behind it
+    const size_t count = align_up((size_t)a.nkeys * 4), scan = align_up(sort_scan_scratch_words(a.nkeys) * 4);
+    const size_t list = align_up((size_t)s.n * 4);
+    if (count + scan + 2 * list > c->lay.scratch_bytes + c->lay.dens_bytes) return false;
+    char* p = c->ws + c->lay.scratch;
+    a.count = (uint32_t*)p;
+    a.scan_scratch = (uint32_t*)(p + count);
+    a.key = (uint32_t*)(p + count + scan);
+    a.rank = (uint32_t*)(p + count + scan + list);
+  }
+  launch_place_species(a, c->stream);
+  return true;
 }
 
 }  // namespace
@@ -1188,6 +1245,11 @@ int fdf_init_species(fdf_ctx* c, int32_t field_id, double m, int64_t n, uint64_t
   sa.t_nu = t_nu_ev();
   std::pair<hipEvent_t, hipEvent_t> ev;
   timing_begin(c, FDF_KERNEL_INIT, &ev);
+  if (place_species(c, s)) {
+    sa.by_id = 1;
+    s.sorted = s.placed = true;
+    s.order_time = c->step_index;
+  }
   launch_sample_species(sa, c->stream);
   if (flags & FDF_SPECIES_PRE_IC) {
     c->have_density = false;
@@ -1354,7 +1416,7 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
       for (size_t i = 0; i < ns; ++i) {
         if (at[i] != j) continue;
         SpeciesRec& s = c->species[i];
-        const SortCadence cad{s.sorted, s.order_time, s.drift_cells};
+        const SortCadence cad{s.sorted, s.order_time, s.drift_cells, s.placed};
         LaunchMember m;
         m.species = i;
         m.plan = plan_launch(c, plan, cad, s.m, j, j1);
@@ -1373,6 +1435,7 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
           if (rc) return rc;
         }
         s.sorted = after.sorted;
+        s.placed = after.placed;
         s.order_time = after.order_time;
         s.drift_cells = after.drift_cells;
         keyed[i] = m.writes_keys;
@@ -1413,7 +1476,7 @@ HostStepState host_state(fdf_ctx* c) {
   HostStepState h;
   h.step_index = c->step_index;
   for (auto& s : c->species) {
-    h.ints.insert(h.ints.end(), {s.cur, s.sorted ? 1 : 0, s.order_time, s.pristine ? 1 : 0});
+    h.ints.insert(h.ints.end(), {s.cur, s.sorted ? 1 : 0, s.placed ? 1 : 0, s.order_time, s.pristine ? 1 : 0});
     h.drift_cells.push_back(s.drift_cells);
   }
   for (auto& f : c->fields) {
@@ -1427,11 +1490,12 @@ HostStepState host_state(fdf_ctx* c) {
 void apply_state(fdf_ctx* c, const HostStepState& h) {
   c->step_index = h.step_index;
   const int* v = h.ints.data();
-  for (size_t i = 0; i < c->species.size(); ++i, v += 4) {
+  for (size_t i = 0; i < c->species.size(); ++i, v += 5) {
     c->species[i].cur = v[0];
     c->species[i].sorted = v[1] != 0;
-    c->species[i].order_time = v[2];
-    c->species[i].pristine = v[3] != 0;
+    c->species[i].placed = v[2] != 0;
+    c->species[i].order_time = v[3];
+    c->species[i].pristine = v[4] != 0;
     c->species[i].drift_cells = h.drift_cells[i];
   }
   for (size_t i = 0; i < c->fields.size(); ++i, v += 2) {

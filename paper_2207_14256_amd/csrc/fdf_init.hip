@@ -2,6 +2,7 @@
 // pre-initial-condition transform (sec. 2.1).
 #include "fdf_device.h"
 #include "fdf_internal.h"
+#include "fdf_key.h"
 
 namespace fdf {
 namespace {
@@ -52,6 +53,31 @@ __global__ void k_field_gen(FieldGenArgs a) {
     }
     ((cplx<R>*)a.out)[e] = val;
   }
+}
+
+// Spatial order at creation.  Sampling is a function of seed and id, so the
+// ids alone are ordered, by a counting sort over the tiles of the sampled
+// positions, before any state is written: no particle is moved.  The positions
+// are random, so every atomic and every id write goes to a line of its own,
+// which bounds both passes (134 M particles on 512^3: 6.9 ms, 19 G atomics/s,
+// and 4.7 ms; sampling first and moving the ids of a first sort took 6.1 ms
+// more).
+__global__ void __launch_bounds__(256) k_place_count(PlaceArgs a) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.seg.n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const u64x4 wp = philox4x64((uint64_t)i, 0, 0, 0, a.seed, kStreamPosition);
+    uint32_t c[3];
+    for (int d = 0; d < 3; ++d) c[d] = (uint32_t)(wp.v[d] >> 32) >> a.cell_shift;
+    const uint32_t k = sort_key::morton_key(c, a.fine_bits) >> (3 * a.fine_bits);
+    a.key[i] = k;
+    a.rank[i] = atomicAdd(&a.count[k], 1u);
+  }
+}
+
+__global__ void __launch_bounds__(256) k_place_ids(PlaceArgs a) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.seg.n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    a.seg.id[(size_t)a.count[a.key[i]] + a.rank[i]] = (uint32_t)i;
 }
 
 // Particle sample: uniform positions on the 2^-32 L lattice, |q| from
@@ -147,6 +173,13 @@ void launch_field_gen(const FieldGenArgs& a, hipStream_t s) {
 
 void launch_sample_species(const SampleArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_sample, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
+}
+
+void launch_place_species(const PlaceArgs& a, hipStream_t s) {
+  launch_fill_zero(a.count, ((size_t)a.nkeys * 4 + 15) / 16 * 16, s);
+  hipLaunchKernelGGL(k_place_count, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
+  launch_scan_exclusive(a.count, a.nkeys, a.scan_scratch, s);
+  hipLaunchKernelGGL(k_place_ids, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
 }
 
 void launch_pre_ic(const PreIcArgs& a, hipStream_t s) {

@@ -243,6 +243,20 @@ struct SampleArgs {
   double t_nu;             // k_B T [eV]
 };
 
+// Spatial order of a species that is about to be sampled: ids written to
+// seg.id in the Morton order of their (sampled) positions' tiles.
+struct PlaceArgs {
+  Segment seg;
+  uint64_t seed;
+  int32_t cell_shift;      // 32 - log2(G)
+  int32_t fine_bits;       // log2 of the tile side in cells
+  int64_t nkeys;           // number of tiles
+  uint32_t* count;         // [nkeys]
+  uint32_t* scan_scratch;  // sort_scan_scratch_words(nkeys) words
+  uint32_t* key;           // [n]
+  uint32_t* rank;          // [n]
+};
+
 struct FieldGenArgs {
   int32_t G;
   int32_t fp64;
@@ -306,6 +320,7 @@ struct TermArgs {
 void launch_field_gen(const FieldGenArgs& a, hipStream_t s);
 void launch_force_terms(const TermArgs& a, hipStream_t s);
 void launch_sample_species(const SampleArgs& a, hipStream_t s);
+void launch_place_species(const PlaceArgs& a, hipStream_t s);
 void launch_pre_ic(const PreIcArgs& a, hipStream_t s);
 void launch_build_grids(const GridBuildArgs& a, hipStream_t s);
 void launch_push(const PushArgs& a, hipStream_t s);
@@ -324,5 +339,6 @@ void launch_sort_rank(const SortArgs& a, hipStream_t s);   // counts, rank pass 
 void launch_sort_rank_batch(const SortArgs& a, hipStream_t s);   // the same over a SpeciesBatch
 void launch_push_sort(const PushArgs& a, hipStream_t s);
 size_t sort_scan_scratch_words(int64_t nkeys);
+void launch_scan_exclusive(uint32_t* data, int64_t n, uint32_t* scratch, hipStream_t s);
 
 }  // namespace fdf

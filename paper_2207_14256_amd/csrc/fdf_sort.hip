@@ -471,6 +471,10 @@ size_t sort_scan_scratch_words(int64_t nkeys) {
   return words + 16;
 }
 
+void launch_scan_exclusive(uint32_t* data, int64_t n, uint32_t* scratch, hipStream_t s) {
+  scan_exclusive(data, n, scratch, s);
+}
+
 void launch_sort_rank(const SortArgs& a, hipStream_t s) {
   const int64_t n = a.seg.n;
   launch_fill_zero(a.count, ((size_t)a.nkeys * 4 + 15) / 16 * 16, s);
