@@ -66,6 +66,22 @@ __device__ __forceinline__ cplx<R> cadd(cplx<R> a, cplx<R> b) { return {a.x + b.
 template <typename R>
 __device__ __forceinline__ cplx<R> csub(cplx<R> a, cplx<R> b) { return {a.x - b.x, a.y - b.y}; }
 
+// Maximum of v >= 0 over a block of 256 threads and then over the grid, in the
+// binary32 bits *out (zeroed before).  One atomic per block, and only from
+// blocks that raise the value they read: atomics on one address run at about
+// 85 M/s, so one per wave of a large grid took 0.4 ms by itself.
+__device__ __forceinline__ void block_max_bits(float v, uint32_t* out) {
+  __shared__ float wave[4];
+  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+  if ((threadIdx.x & 63) == 0) wave[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    v = fmaxf(fmaxf(wave[0], wave[1]), fmaxf(wave[2], wave[3]));
+    const uint32_t seen = __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (v > __uint_as_float(seen)) atomicMax(out, __float_as_uint(v));
+  }
+}
+
 // Canonical momentum of particle id (sec. 2.1 sampling): |q| with pdf
 // proportional to q^2 fbar(q), drawn by a Gamma(3, T) proposal
 // q = -T ln(u0 u1 u2) kept when u3 (1 + e^{-q/T}) < 1 (first kept trial of at

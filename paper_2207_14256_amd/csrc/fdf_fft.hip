@@ -502,8 +502,7 @@ __global__ void __launch_bounds__(256) k_bin_max(PkArgs a) {
     if (mode_bin(gi, G, a.nbins, &n2, &nz) < 0) continue;
     m = fmaxf(m, __double2float_ru(fabs(mode_power<R, G>(a, gi))));
   }
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & 63) == 0 && m > 0.0f) atomicMax(a.max_bits, __float_as_uint(m));
+  block_max_bits(m, a.max_bits);
 }
 
 // 128-bit add of a signed 64-bit value into (lo, hi) words.

@@ -10,20 +10,25 @@ namespace fdf {
 namespace {
 
 // Current momentum (binary64) and the sampled momentum p of particle i.
+// PRE: the species has pre-initial conditions (a.pre_ic).
+template <bool PRE>
 __device__ __forceinline__ void momenta(const OutputArgs& a, int64_t i, uint32_t id,
                                         double* q, double* p) {
   if (a.fp64) {
+#pragma unroll
     for (int d = 0; d < 3; ++d) { q[d] = a.seg.qd[d][i]; p[d] = a.seg.q0d[d][i]; }
   } else {
     // q = q0 + dq, exact in binary64
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
       p[d] = (double)a.seg.q0f[d][i];
       q[d] = p[d] + (double)a.seg.dqf[d][i];
     }
   }
-  if (a.pre_ic) {  // q0 carries the transformed momentum; p is the raw sample
+  if constexpr (PRE) {  // q0 carries the transformed momentum; p is the raw sample
     float pf[3];
     sample_momentum(a.seed, (uint64_t)id, a.t_nu, pf);
+#pragma unroll
     for (int d = 0; d < 3; ++d) p[d] = (double)pf[d];
   }
 }
@@ -32,6 +37,7 @@ __device__ __forceinline__ void momenta(const OutputArgs& a, int64_t i, uint32_t
 // D = |q| - |p| = (2 p.d + d.d) / (|q| + |p|), d = q - p: no cancellation.
 __device__ __forceinline__ double deltaf_weight(const double* q, const double* p, double T) {
   double d[3], pd = 0.0, dd = 0.0, qq = 0.0, pp = 0.0;
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
     d[k] = q[k] - p[k];
     pd += p[k] * d[k];
@@ -45,12 +51,13 @@ __device__ __forceinline__ double deltaf_weight(const double* q, const double* p
   return expm1(D / T) / (exp(-pn / T) + exp(D / T));
 }
 
-__global__ void k_weights(OutputArgs a) {
+template <bool PRE>
+__global__ void __launch_bounds__(256) k_weights(OutputArgs a) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.seg.n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const uint32_t id = a.seg.id[i];
     double q[3], p[3];
-    momenta(a, i, id, q, p);
+    momenta<PRE>(a, i, id, q, p);
     a.w_out[id] = deltaf_weight(q, p, a.t_nu);
   }
 }
@@ -58,26 +65,30 @@ __global__ void k_weights(OutputArgs a) {
 // Value deposited by particle i: w eps (energy density) or w q_axis = w eps
 // v_axis (momentum density), times the per-half normalisation
 // G^3 / (N_half <eps>); *half receives the half (even / odd id).
+template <bool PRE>
 __device__ __forceinline__ double deposit_value(const OutputArgs& a, int64_t i, int* half) {
   const uint32_t id = a.seg.id[i];
   double q[3], p[3];
-  momenta(a, i, id, q, p);
+  momenta<PRE>(a, i, id, q, p);
   const double w = deltaf_weight(q, p, a.t_nu);
-  const double eps = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + (a.m * a.a) * (a.m * a.a));
   *half = a.auto_mode ? 0 : (int)(id & 1u);
-  return (a.quantity < 0 ? w * eps : w * q[a.quantity]) * a.norm[*half];
+  const double norm = *half ? a.norm[1] : a.norm[0];
+  if (a.quantity >= 0) return (w * (a.quantity == 0 ? q[0] : a.quantity == 1 ? q[1] : q[2])) * norm;
+  const double eps = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + (a.m * a.a) * (a.m * a.a));
+  return (w * eps) * norm;
 }
 
 // CIC cell and weights of particle i on the G^3 deposit mesh (vertex-centred
 // mesh points, periodic): x-major cell index, or (bricked) the 4^3-brick
 // index of the gradient meshes, so that a wave of sorted particles adds into
-// a few contiguous kilobytes.
+// a few contiguous kilobytes (G <= 1024: cell indices fit 32 bits).
 template <bool BRICKED>
-__device__ __forceinline__ void deposit_cic(const OutputArgs& a, int64_t i, size_t* cell, double* wc) {
+__device__ __forceinline__ void deposit_cic(const OutputArgs& a, int64_t i, uint32_t* cell, double* wc) {
   const int G = a.G;
   const double ginv = (double)G / a.box;
   int i0[3], i1[3];
   double t[3];
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
     const double x = a.fp64 ? a.seg.xd[d][i] : (double)a.seg.xu[d][i] * (a.box * 0x1p-32);
     const double u = x * ginv;
@@ -86,14 +97,15 @@ __device__ __forceinline__ void deposit_cic(const OutputArgs& a, int64_t i, size
     i0[d] = ((int)fl) & (G - 1);
     i1[d] = (i0[d] + 1) & (G - 1);
   }
+#pragma unroll
   for (int c = 0; c < 8; ++c) {
     const int cx = c >> 2, cy = (c >> 1) & 1, cz = c & 1;
     wc[c] = (cx ? t[0] : 1 - t[0]) * (cy ? t[1] : 1 - t[1]) * (cz ? t[2] : 1 - t[2]);
     const int jx = cx ? i1[0] : i0[0], jy = cy ? i1[1] : i0[1], jz = cz ? i1[2] : i0[2];
     if constexpr (BRICKED)
-      cell[c] = (size_t)mesh_x((uint32_t)jx, (uint32_t)G) + mesh_y((uint32_t)jy, (uint32_t)G) + mesh_z((uint32_t)jz);
+      cell[c] = mesh_x((uint32_t)jx, (uint32_t)G) + mesh_y((uint32_t)jy, (uint32_t)G) + mesh_z((uint32_t)jz);
     else
-      cell[c] = ((size_t)jx * G + jy) * G + jz;
+      cell[c] = ((uint32_t)jx * (uint32_t)G + (uint32_t)jy) * (uint32_t)G + (uint32_t)jz;
   }
 }
 
@@ -111,84 +123,98 @@ __device__ __forceinline__ double fixed_inv_quantum(uint32_t max_bits, int bits)
   return ldexp(1.0, bits - e);
 }
 
+template <bool PRE>
 __global__ void __launch_bounds__(256) k_deposit_max(OutputArgs a) {
   float m = 0.0f;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.seg.n;
        i += (int64_t)gridDim.x * blockDim.x) {
     int half;
-    const double v = fabs(deposit_value(a, i, &half));
+    const double v = fabs(deposit_value<PRE>(a, i, &half));
     m = fmaxf(m, __double2float_ru(v));
   }
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & 63) == 0 && m > 0.0f) atomicMax(a.max_bits, __float_as_uint(m));
+  block_max_bits(m, a.max_bits);
 }
 
-// Deposit with the additions gathered first in a workgroup hash table in
-// LDS (key = 2 cell + half, linear probing), so that the sums of a block's
-// 1024 particles reach the mesh with one global atomic per distinct cell and
-// half instead of one per corner.  Global atomics are carried out past the
-// per-XCD L2 caches, one memory transaction each, and dominate the plain
-// kernels' time; sorted particles share most corners (about 8 contributions
-// per particle become 2 to 3 global atomics).  A contribution that finds no
-// slot within kProbe probes goes to the mesh directly.  V = unsigned long
-// long: the fixed-point form, whose integer sums do not depend on how the
-// additions are grouped or ordered; V = double: the FP64 form.
-template <typename V>
-__global__ void __launch_bounds__(256) k_deposit_lds(OutputArgs a) {
-  constexpr int R = 4, LOGH = 12;
-  constexpr uint32_t H = 1u << LOGH, kEmpty = 0xFFFFFFFFu;
-  constexpr int kProbe = 32;
+// Deposit with the additions gathered first in a workgroup hash table of
+// lines in LDS (a line: eight consecutive cells of the mesh, 64 bytes; key = 2
+// line + half, linear probing), so that the sums of a block's particles reach
+// the mesh with one global atomic per touched cell and half, eight lanes to a
+// line.  Global atomics are carried out past the per-XCD L2 caches, one memory
+// transaction per 64-byte line of an instruction: 19 G/s on scattered cells,
+// 145 G/s when eight lanes share a line, which is why the table holds lines
+// and not cells.  A contribution whose line finds no slot within kProbe probes
+// goes to the mesh directly.  V = unsigned long long: the fixed-point form,
+// whose integer sums do not depend on how the additions are grouped or
+// ordered; V = double: the FP64 form.
+// 134 M sorted particles, one per cell (cross spectrum): 22 ms with a table of
+// cells and 256 threads of 4 particles, 13 ms with lines, 7.8 ms with barriers
+// that do not wait for the mesh atomics, 6.4 ms with 1024 threads of one
+// particle (8 waves per SIMD hide the binary64 weights' and the table's
+// latencies; a bigger table with one block per CU: 7.9 ms).
+
+// Workgroup barrier that orders LDS alone: the mesh atomics still in flight
+// need no order against it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <typename V, bool PRE, int NT, int R, int LOGS>
+__global__ void __launch_bounds__(NT, 4) k_deposit_lds(OutputArgs a) {
+  constexpr uint32_t S = 1u << LOGS, kEmpty = 0xFFFFFFFFu;
+  constexpr int kProbe = 16;
   constexpr bool kFixed = std::is_same<V, unsigned long long>::value;
-  __shared__ uint32_t key[H];
-  __shared__ V val[H];
+  __shared__ uint32_t key[S];
+  __shared__ V val[S * 8];
+  for (uint32_t s = threadIdx.x; s < S; s += NT) key[s] = kEmpty;
+  for (uint32_t s = threadIdx.x; s < S * 8; s += NT) val[s] = (V)0;
   const double scale = kFixed ? fixed_inv_quantum(*a.max_bits, a.fixed_bits) : 1.0;
-  constexpr int64_t per = 256 * R;
-  const int64_t nchunk = (a.seg.n + per - 1) / per;
-  for (int64_t ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
-    for (uint32_t s = threadIdx.x; s < H; s += 256) { key[s] = kEmpty; val[s] = (V)0; }
-    __syncthreads();
-    for (int r = 0; r < R; ++r) {
-      const int64_t i = ch * per + r * 256 + threadIdx.x;
-      if (i >= a.seg.n) break;
-      int half;
-      const double v0 = deposit_value(a, i, &half) * scale;
-      size_t cell[8];
-      double wc[8];
-      deposit_cic<kFixed>(a, i, cell, wc);
-      for (int c = 0; c < 8; ++c) {
-        V v;
-        if constexpr (kFixed) v = (V)__double2ll_rn(wc[c] * v0);
-        else v = wc[c] * v0;
-        if (v == (V)0) continue;
-        const uint32_t k = (uint32_t)(cell[c] * 2 + half);
-        uint32_t h = (k * 0x9E3779B1u) >> (32 - LOGH);
-        bool done = false;
+  lds_barrier();
+  auto to_mesh = [&](int half, size_t cell, V v) {
+    V* const d = (V*)(half ? a.dens[1] : a.dens[0]) + cell;
+    if constexpr (kFixed) atomicAdd(d, v);
+    else unsafeAtomicAdd(d, v);
+  };
+  const int64_t i0 = (int64_t)blockIdx.x * (NT * R) + threadIdx.x;
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    const int64_t i = i0 + r * NT;
+    if (i >= a.seg.n) break;
+    int half;
+    const double v0 = deposit_value<PRE>(a, i, &half) * scale;
+    uint32_t cell[8];
+    double wc[8];
+    deposit_cic<kFixed>(a, i, cell, wc);
+    // the slots the lines hash to, read together; most hold their line
+    uint32_t h[8], have[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      h[c] = (((cell[c] >> 3) * 2 + half) * 0x9E3779B1u) >> (32 - LOGS);
+      have[c] = ((volatile uint32_t*)key)[h[c]];
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const uint32_t k = (cell[c] >> 3) * 2 + half;
+      V v;
+      if constexpr (kFixed) v = (V)__double2ll_rn(wc[c] * v0);
+      else v = wc[c] * v0;
+      if (v == (V)0) continue;
+      bool found = have[c] == k;
+      if (!found) {
+#pragma unroll 1
         for (int p = 0; p < kProbe; ++p) {
-          const uint32_t prev = atomicCAS(&key[h], kEmpty, k);
-          if (prev == kEmpty || prev == k) {
-            atomicAdd(&val[h], v);
-            done = true;
-            break;
-          }
-          h = (h + 1) & (H - 1);
-        }
-        if (!done) {
-          V* const d = (V*)a.dens[half] + cell[c];
-          if constexpr (kFixed) atomicAdd(d, v);
-          else unsafeAtomicAdd(d, v);
+          const uint32_t prev = atomicCAS(&key[h[c]], kEmpty, k);
+          found = prev == kEmpty || prev == k;
+          if (found) break;
+          h[c] = (h[c] + 1) & (S - 1);
         }
       }
+      if (found) atomicAdd(&val[h[c] * 8 + (cell[c] & 7u)], v);
+      else to_mesh(half, cell[c], v);
     }
-    __syncthreads();
-    for (uint32_t s = threadIdx.x; s < H; s += 256) {
-      const uint32_t k = key[s];
-      const V v = val[s];
-      if (k == kEmpty || v == (V)0) continue;
-      V* const d = (V*)a.dens[k & 1u] + (k >> 1);
-      if constexpr (kFixed) atomicAdd(d, v);
-      else unsafeAtomicAdd(d, v);
-    }
-    __syncthreads();
+  }
+  lds_barrier();
+  for (uint32_t s = threadIdx.x; s < S * 8; s += NT) {
+    const uint32_t k = key[s >> 3];
+    const V v = val[s];
+    if (k != kEmpty && v != (V)0) to_mesh((int)(k & 1u), (size_t)(k >> 1) * 8 + (s & 7u), v);
   }
 }
 
@@ -303,19 +329,28 @@ int grid_for(size_t n, int block) {
 }  // namespace
 
 void launch_weights(const OutputArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_weights, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
+  const dim3 grid(grid_for((size_t)a.seg.n, 256));
+  if (a.pre_ic) hipLaunchKernelGGL(k_weights<true>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(k_weights<false>, grid, dim3(256), 0, s, a);
 }
 
 void launch_force_terms(const TermArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_force_terms, dim3(std::min(grid_for((size_t)a.seg.n, 256), 4096)), dim3(256), 0, s, a);
 }
 
+template <typename V>
+void deposit(const OutputArgs& a, hipStream_t s) {
+  constexpr int NT = 1024, R = 1, LOGS = 10;
+  const dim3 grid((unsigned)((a.seg.n + NT * R - 1) / (NT * R)));
+  if (a.pre_ic) hipLaunchKernelGGL((k_deposit_lds<V, true, NT, R, LOGS>), grid, dim3(NT), 0, s, a);
+  else hipLaunchKernelGGL((k_deposit_lds<V, false, NT, R, LOGS>), grid, dim3(NT), 0, s, a);
+}
+
 void launch_deposit(const OutputArgs& a, hipStream_t s) {
-  // grid_n <= 1024 (checked at creation): the keys 2 cell + half stay below
+  // grid_n <= 1024 (checked at creation): the keys 2 line + half stay below
   // the empty key in 32 bits
-  const int grid = grid_for((size_t)a.seg.n, 1024);
-  if (a.fp64) hipLaunchKernelGGL(k_deposit_lds<double>, dim3(grid), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_deposit_lds<unsigned long long>, dim3(grid), dim3(256), 0, s, a);
+  if (a.fp64) deposit<double>(a, s);
+  else deposit<unsigned long long>(a, s);
 }
 
 void launch_bins_finalize(const double* bins, int nbins, double* out, hipStream_t s) {
@@ -323,7 +358,9 @@ void launch_bins_finalize(const double* bins, int nbins, double* out, hipStream_
 }
 
 void launch_deposit_max(const OutputArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_deposit_max, dim3(std::min(grid_for((size_t)a.seg.n, 256), 8192)), dim3(256), 0, s, a);
+  const dim3 grid(std::min(grid_for((size_t)a.seg.n, 256), 4096));
+  if (a.pre_ic) hipLaunchKernelGGL(k_deposit_max<true>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(k_deposit_max<false>, grid, dim3(256), 0, s, a);
 }
 
 void launch_fixed_to_real(const FixedToRealArgs& a, hipStream_t s) {
