@@ -131,7 +131,10 @@ typedef struct fdf_config {
   int32_t eom;             /* FDF_EOM_* */
   double slip_amp, slip_k; /* psi = phi (1 - slip_amp exp(-k/slip_k)); slip_k in 1/Mpc */
   double ns, sigma8, gamma;/* P(k) = A k^ns T_BBKS(k/(gamma h))^2, sigma(8 Mpc/h) = sigma8 */
-  int32_t sort_every;      /* spatial re-sort of particles every this many steps (0: never) */
+  int32_t sort_every;      /* spatial re-sort of particles every this many steps, into a second
+                              copy of their state (0: no second copy and no cadence of the
+                              caller's; the library re-orders the state in place, through the
+                              FFT scratch, where that pays).  The order changes no result */
   int32_t max_fields;      /* capacity: number of seeded fields (each owns one grid set) */
   int32_t max_species;     /* capacity: number of species */
   int32_t interp_order;    /* force interpolation order r (sec. 4): 0 or 1 CIC (8 points),

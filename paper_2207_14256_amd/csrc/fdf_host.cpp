@@ -605,28 +605,131 @@ SortArgs sort_args(fdf_ctx* c, const SpeciesRec& s, double predict_tau, double a
   return a;
 }
 
-// Rank and move passes of one species into its other buffer copy.  resample:
-// a species whose state is still the sampled one moves its ids alone and is
-// sampled again, by id, into the sorted slots (the same values as moving the
-// whole state from the random sampling order, at a fraction of the scattered
-// writes).
+// Byte offset in the FFT scratch of the FP32 form's binary32 density halves:
+// behind the four transform planes of the largest mesh (two halves and the
+// momentum spectrum's two accumulators), 8 G^3 bytes, inside the scratch's
+// 28 G^3 bytes.
+size_t density_copy_offset(const fdf_ctx* c) {
+  const size_t G = (size_t)c->cfg.grid_n;
+  return 4 * (G * G * (G / 2)) * 8;
+}
+
+// Sampling of a species by the ids its segment g holds.
+SampleArgs resample_args(fdf_ctx* c, const SpeciesRec& s, const Segment& g) {
+  SampleArgs sa{};
+  sa.seg = g;
+  sa.fp64 = c->cfg.precision == FDF_PREC_FP64;
+  sa.by_id = 1;
+  sa.seed = s.seed;
+  sa.box = c->cfg.box_mpc;
+  sa.t_nu = t_nu_ev();
+  return sa;
+}
+
+// A context without a second copy of the state re-orders it in place, through
+// the FFT scratch, which is free between grid builds and spectra: the sort's
+// lists and as many state arrays at a time as fit.  FP32: the lists lie in the
+// fixed-point density halves and the arrays below the binary32 density copy, so
+// that a density stays readable.
+struct InPlaceRoom {
+  char* lists = nullptr;
+  size_t list_bytes = 0;
+  char* arrays = nullptr;
+  size_t array_bytes = 0;    // for state arrays at a time
+};
+
+// L2 of one XCD: a mesh it holds is gathered from at the same rate in any order.
+constexpr size_t kL2Bytes = (size_t)4 << 20;
+
+bool in_place_room(fdf_ctx* c, int64_t n, InPlaceRoom* r) {
+  if (c->cfg.sort_every > 0 || c->lay.field_grid_bytes <= kL2Bytes) return false;
+  const int64_t tiles = sort_tiles_of(c), nkeys = tiles * tiles * tiles;
+  r->list_bytes = align_up(nkeys * 4) + align_up(sort_scan_scratch_words(nkeys) * 4) + 3 * align_up(n * 4);
+  if (c->cfg.precision == FDF_PREC_FP64) {
+    if (r->list_bytes > c->lay.scratch_bytes) return false;
+    r->lists = c->ws + c->lay.scratch;
+    r->arrays = r->lists + r->list_bytes;
+    r->array_bytes = c->lay.scratch_bytes - r->list_bytes;
+    return r->array_bytes >= align_up(n * 8);
+  }
+  if (r->list_bytes > c->lay.dens_bytes) return false;
+  r->lists = c->ws + c->lay.dens;
+  r->arrays = c->ws + c->lay.scratch;
+  r->array_bytes = density_copy_offset(c);
+  return r->array_bytes >= align_up(n * 4);
+}
+
+int sort_in_place(fdf_ctx* c, SpeciesRec& s, const SortPrediction& pred, const InPlaceRoom& room) {
+  const bool f64 = c->cfg.precision == FDF_PREC_FP64;
+  SortArgs a = sort_args(c, s, pred.tau, pred.a_mid);
+  char* p = room.lists;
+  auto list = [&](size_t words) { uint32_t* q = (uint32_t*)p; p += align_up(words * 4); return q; };
+  a.count = list(a.nkeys);
+  a.scan_scratch = list(sort_scan_scratch_words(a.nkeys));
+  a.rank = list(s.n);
+  a.bucket = list(s.n);
+  a.src = list(s.n);
+  launch_sort_rank(a, stream_of(c));
+  // the state arrays by move-mask bit
+  Segment& g = s.seg[0];
+  void** home[10];
+  for (int d = 0; d < 3; ++d) {
+    home[d] = f64 ? (void**)&g.xd[d] : (void**)&g.xu[d];
+    home[3 + d] = f64 ? (void**)&g.qd[d] : (void**)&g.q0f[d];
+    home[6 + d] = f64 ? (void**)&g.q0d[d] : (void**)&g.dqf[d];
+  }
+  home[9] = (void**)&g.id;
+  const bool resample = s.pristine;   // the ids alone; sampled again into the new order
+  for (int k = resample ? 9 : 0; k < 10;) {
+    Segment& t = a.dst;
+    t = g;
+    void** there[10];
+    for (int d = 0; d < 3; ++d) {
+      there[d] = f64 ? (void**)&t.xd[d] : (void**)&t.xu[d];
+      there[3 + d] = f64 ? (void**)&t.qd[d] : (void**)&t.q0f[d];
+      there[6 + d] = f64 ? (void**)&t.q0d[d] : (void**)&t.dqf[d];
+    }
+    there[9] = (void**)&t.id;
+    CopyArgs cp{};
+    size_t used = 0;
+    a.move_mask = 0;
+    for (; k < 10; ++k) {
+      const size_t bytes = (size_t)s.n * (f64 && k < 9 ? 8 : 4);
+      if (used + align_up(bytes) > room.array_bytes) break;
+      *there[k] = room.arrays + used;
+      used += align_up(bytes);
+      a.move_mask |= 1u << k;
+      cp.src[cp.n] = (const uint32_t*)*there[k];
+      cp.dst[cp.n] = (uint32_t*)*home[k];
+      cp.words[cp.n++] = (int64_t)(bytes / 4);
+    }
+    launch_sort_move(a, stream_of(c));
+    launch_copy(cp, stream_of(c));
+  }
+  if (resample) launch_sample_species(resample_args(c, s, g), stream_of(c));
+  return launched(c, "sort in place");
+}
+
+// Rank and move passes of one species into its other buffer copy (or in
+// place).  resample: a species whose state is still the sampled one moves its
+// ids alone and is sampled again, by id, into the sorted slots (the same
+// values as moving the whole state from the random sampling order, at a
+// fraction of the scattered writes).
 int sort_species(fdf_ctx* c, SpeciesRec& s, const SortPrediction& pred, bool resample) {
   std::pair<hipEvent_t, hipEvent_t> ev;
   timing_begin(c, FDF_KERNEL_SORT, &ev);
-  SortArgs a = sort_args(c, s, pred.tau, pred.a_mid);
-  a.id_only = resample && s.pristine;
-  launch_sort(a, stream_of(c));
-  if (a.id_only) {
-    SampleArgs sa{};
-    sa.seg = s.seg[s.cur ^ 1];
-    sa.fp64 = c->cfg.precision == FDF_PREC_FP64;
-    sa.by_id = 1;
-    sa.seed = s.seed;
-    sa.box = c->cfg.box_mpc;
-    sa.t_nu = t_nu_ev();
-    launch_sample_species(sa, stream_of(c));
+  InPlaceRoom room;
+  if (in_place_room(c, s.n, &room)) {
+    const int rc = sort_in_place(c, s, pred, room);
+    if (rc) return rc;
+  } else {
+    SortArgs a = sort_args(c, s, pred.tau, pred.a_mid);
+    const bool ids = resample && s.pristine;
+    a.move_mask = ids ? kMoveIds : kMoveAll;
+    launch_sort(a, stream_of(c));
+    if (ids) launch_sample_species(resample_args(c, s, s.seg[s.cur ^ 1]), stream_of(c));
+    s.cur ^= 1;
   }
-  s.cur ^= 1;
   timing_end(c, FDF_KERNEL_SORT, ev);
   return launched(c, "sort");
 }
@@ -674,25 +777,28 @@ struct StepPlan {
 // start); fixed cadence: at multiples of sort_every.
 struct SortCadence {
   bool sorted;
+  bool placed;
   int order_time;
   double drift_cells;
-  bool placed = false;
+  double cells;              // adaptive threshold (0: fixed cadence)
+  int every;                 // fixed cadence (0: never)
+  SortCadence restart(int time) const { return SortCadence{true, false, time, 0.0, cells, every}; }
 };
 constexpr int kNeverDue = 1 << 30;
 
 int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
   const int dir = p.n > 0 ? 1 : -1;
-  if (c->sort_cells > 0) {
+  if (s.cells > 0) {
     double cells = s.drift_cells, dr, ah;
     for (int k = 1; p.drift(u, &dr, &ah); ++k, u += dir) {
       cells += typical_drift_cells(c, dr, ah, m);
-      if (cells >= c->sort_cells) return k;
+      if (cells >= s.cells) return k;
     }
     return kNeverDue;
   }
-  if (c->sort_every <= 0) return kNeverDue;
-  const int r = u % c->sort_every;
-  return dir > 0 ? c->sort_every - r : (r ? r : c->sort_every);
+  if (s.every <= 0) return kNeverDue;
+  const int r = u % s.every;
+  return dir > 0 ? s.every - r : (r ? r : s.every);
 }
 
 // A species in the order of its creation is due at once if its particles will
@@ -702,24 +808,38 @@ int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, 
 constexpr double kPlacedDrift = 3.0;
 
 bool sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
-  if (s.placed && (c->sort_cells > 0 || c->sort_every > 0)) {
+  if (s.placed && (s.cells > 0 || s.every > 0)) {
     const int dir = p.n > 0 ? 1 : -1, len = steps_until_due(c, p, s, u, m);
     double dr, ah, cells = 0.0;
     for (int k = 0; k + 1 < len && cells <= kPlacedDrift && p.drift(u + dir * k, &dr, &ah); ++k)
       cells += typical_drift_cells(c, dr, ah, m);
     if (cells > kPlacedDrift) return true;
   }
-  if (c->sort_cells > 0) return !s.sorted || s.drift_cells >= c->sort_cells;
-  return c->sort_every > 0 && u % c->sort_every == 0 && s.order_time != u;
+  if (s.cells > 0) return !s.sorted || s.drift_cells >= s.cells;
+  return s.every > 0 && u % s.every == 0 && s.order_time != u;
+}
+
+// Adaptive threshold of the re-sorts in place.  They cost two passes more than
+// a re-sort into a second copy, so they wait longer: 16.8 M particles on 256^3,
+// 40 steps, FP64 72, 63, 60 and 58 ms at 3, 6, 9 and 14 cells (102 ms without
+// them), 2 M TSC 13.0, 12.8, 13.2 and 14.7 ms (22); FP32 23.7, 21.9 and 20.7 ms
+// at 6, 9 and 14 cells (27 ms).
+constexpr double kInPlaceCells = 10.0;
+
+SortCadence cadence_of(fdf_ctx* c, const SpeciesRec& s) {
+  SortCadence r{s.sorted, s.placed, s.order_time, s.drift_cells, c->sort_cells, c->sort_every};
+  InPlaceRoom room;
+  if (in_place_room(c, s.n, &room)) r.cells = kInPlaceCells;
+  return r;
 }
 
 // Positions to order by for the interval that starts `lead` steps after u (as
 // long as the cadence will let it be): the state at u extrapolated to the
 // middle of the interval's gathers, which are made at the start of each of its
 // steps.
-SortPrediction sort_prediction(fdf_ctx* c, const StepPlan& p, int u, int lead, double m) {
+SortPrediction sort_prediction(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, int lead, double m) {
   const int dir = p.n > 0 ? 1 : -1, u0 = u + dir * lead;
-  const int len = steps_until_due(c, p, SortCadence{true, u0, 0.0}, u0, m);
+  const int len = steps_until_due(c, p, s.restart(u0), u0, m);
   double dr, ah, before = 0.0, span = 0.0;
   for (int k = 0; k < lead && p.drift(u + dir * k, &dr, &ah); ++k) before += dr;
   for (int k = 0; k + 1 < len && p.drift(u0 + dir * k, &dr, &ah); ++k) span += dr;
@@ -754,7 +874,8 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
   const int room = std::min(limit - j, kMaxSpan);
   if (rem == 0) return l;                         // the closing kick
   const int dir = p.n > 0 ? 1 : -1;
-  const bool fusable = c->sort_fused && c->cfg.precision == FDF_PREC_FP32 && c->cfg.eom == FDF_EOM_SEPARABLE;
+  const bool fusable = c->cfg.sort_every > 0 && c->sort_fused && c->cfg.precision == FDF_PREC_FP32 &&
+                       c->cfg.eom == FDF_EOM_SEPARABLE;
   double dr, ah;
   SortCadence now = s;
   if (sort_due(c, p, s, u, m)) {
@@ -763,20 +884,20 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
     const bool ride = fusable && p.drift(u + dir, &dr, &ah);   // steps follow that use the new order
     l.sort_passes = (first ? 2 : 1) - (ride ? 1 : 0);
     l.sort_first = l.sort_passes > 0;
-    if (l.sort_first) l.pred_first = sort_prediction(c, p, u, 0, m);
+    if (l.sort_first) l.pred_first = sort_prediction(c, p, s, u, 0, m);
     if (ride) {
       l.fused = true;
-      l.pred = sort_prediction(c, p, u, 1, m);
+      l.pred = sort_prediction(c, p, s, u, 1, m);
       return l;
     }
-    now = SortCadence{true, u, 0.0};
+    now = s.restart(u);
   }
   const int d = steps_until_due(c, p, now, u, m);
   if (d < rem) {               // due again within the call
     l.span = std::min(d, room);
     if (fusable && l.span == d) {
       l.fused = true;
-      l.pred = sort_prediction(c, p, u, d, m);
+      l.pred = sort_prediction(c, p, s, u, d, m);
     }
   } else {
     l.span = std::min(rem + 1, room);   // to the end of the call, the closing kick included
@@ -789,11 +910,11 @@ SortCadence after_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, co
   const int dir = p.n > 0 ? 1 : -1, u = p.time(j);
   SortCadence r = s;
   r.placed = false;
-  if (l.sort_first) r = SortCadence{true, u, 0.0};
+  if (l.sort_first) r = s.restart(u);
   double dr, ah;
   for (int k = 0; k < l.span && j + k < p.nabs(); ++k)
     if (p.drift(u + dir * k, &dr, &ah)) r.drift_cells += typical_drift_cells(c, dr, ah, m);
-  if (l.fused) r = SortCadence{true, u + dir * l.span, 0.0};
+  if (l.fused) r = s.restart(u + dir * l.span);
   return r;
 }
 
@@ -912,15 +1033,6 @@ OutputArgs output_args(fdf_ctx* c, const SpeciesRec& s) {
   return o;
 }
 
-// Byte offset in the FFT scratch of the FP32 form's binary32 density halves:
-// behind the four transform planes of the largest mesh (two halves and the
-// momentum spectrum's two accumulators), 8 G^3 bytes, inside the scratch's
-// 28 G^3 bytes.
-size_t density_copy_offset(const fdf_ctx* c) {
-  const size_t G = (size_t)c->cfg.grid_n;
-  return 4 * (G * G * (G / 2)) * 8;
-}
-
 // First complex entry of the n-point table in the twiddle regions.
 size_t twiddle_entry(int G, int n) { return 2 * (size_t)(G - n); }
 
@@ -987,8 +1099,6 @@ int new_species(fdf_ctx* c, int32_t field_id, double m, int64_t n, uint64_t seed
 // particle and the tile counts, in the sort's arrays or else in the FFT
 // scratch) do not fit, or when they would overwrite a density that can still
 // be read.  Returns whether the ids are in order.
-constexpr size_t kL2Bytes = (size_t)4 << 20;   // L2 of one XCD
-
 bool place_species(fdf_ctx* c, SpeciesRec& s) {
   const int G = c->cfg.grid_n, tiles = std::min(G, 256);
   const bool sorting = c->cfg.sort_every > 0;
@@ -1416,7 +1526,7 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
       for (size_t i = 0; i < ns; ++i) {
         if (at[i] != j) continue;
         SpeciesRec& s = c->species[i];
-        const SortCadence cad{s.sorted, s.order_time, s.drift_cells, s.placed};
+        const SortCadence cad = cadence_of(c, s);
         LaunchMember m;
         m.species = i;
         m.plan = plan_launch(c, plan, cad, s.m, j, j1);

@@ -229,9 +229,20 @@ struct SortArgs {
   uint32_t* rank;          // [n] per sorted element of each 1024-block: rank inside its bucket
   uint32_t* bucket;        // [n] per sorted element: bucket
   uint32_t* src;           // [n] per sorted element: source slot inside the block
-  int32_t id_only;         // move pass: move the ids alone (the caller re-samples the state by id)
+  uint32_t move_mask;      // move pass: state arrays to move (bits 0-9: x, q (FP64) or q0 (FP32), q0
+                           // (FP64) or dq (FP32), three axes each, then the ids)
   SpeciesBatch batch;      // rank pass over several species (batch.njobs > 0; seg, dst unused)
   const uint32_t* keys;    // rank pass: keys written by previous pushes (batch.keyed_mask)
+};
+
+constexpr uint32_t kMoveAll = 0x3FFu, kMoveIds = 0x200u;
+
+// Arrays copied by one launch (4-byte words).
+struct CopyArgs {
+  int32_t n;
+  const uint32_t* src[10];
+  uint32_t* dst[10];
+  int64_t words[10];
 };
 
 struct SampleArgs {
@@ -334,7 +345,9 @@ void launch_power_spectrum(const PkArgs& a, hipStream_t s);
 void launch_bin(const PkArgs& a, hipStream_t s);   // bins planes bin_plane (and + 1) into a.bins
 void launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
 int push_chunk_particles(int ppt);
-void launch_sort(const SortArgs& a, hipStream_t s);
+void launch_sort(const SortArgs& a, hipStream_t s);        // rank pass, scan and move pass
+void launch_sort_move(const SortArgs& a, hipStream_t s);   // the move pass alone
+void launch_copy(const CopyArgs& a, hipStream_t s);
 void launch_sort_rank(const SortArgs& a, hipStream_t s);   // counts, rank pass and scan, no move
 void launch_sort_rank_batch(const SortArgs& a, hipStream_t s);   // the same over a SpeciesBatch
 void launch_push_sort(const PushArgs& a, hipStream_t s);

@@ -383,16 +383,15 @@ __global__ void __launch_bounds__(256) k_sort_move(SortArgs a) {
   }
   const Segment& s = a.seg;
   const Segment& d = a.dst;
-  if (a.id_only) {
-    move_array(s.id, d.id, (uint32_t*)lds_raw, i0, cnt, sidx, pos);
-  } else if (a.fp64) {
+  const uint32_t mask = a.move_mask;
+  if (a.fp64) {
     double* l = (double*)lds_raw;
     for (int k = 0; k < 3; ++k) {
-      move_array(s.xd[k], d.xd[k], l, i0, cnt, sidx, pos);
-      move_array(s.qd[k], d.qd[k], l, i0, cnt, sidx, pos);
-      move_array(s.q0d[k], d.q0d[k], l, i0, cnt, sidx, pos);
+      if ((mask >> k) & 1u) move_array(s.xd[k], d.xd[k], l, i0, cnt, sidx, pos);
+      if ((mask >> (3 + k)) & 1u) move_array(s.qd[k], d.qd[k], l, i0, cnt, sidx, pos);
+      if ((mask >> (6 + k)) & 1u) move_array(s.q0d[k], d.q0d[k], l, i0, cnt, sidx, pos);
     }
-    move_array(s.id, d.id, (uint32_t*)lds_raw, i0, cnt, sidx, pos);
+    if (mask & kMoveIds) move_array(s.id, d.id, (uint32_t*)lds_raw, i0, cnt, sidx, pos);
   } else {
     uint32_t* l = (uint32_t*)lds_raw;
     const uint32_t* sa[10] = {s.xu[0], s.xu[1], s.xu[2],
@@ -401,8 +400,24 @@ __global__ void __launch_bounds__(256) k_sort_move(SortArgs a) {
     uint32_t* da[10] = {d.xu[0], d.xu[1], d.xu[2], (uint32_t*)d.q0f[0], (uint32_t*)d.q0f[1],
                         (uint32_t*)d.q0f[2], (uint32_t*)d.dqf[0], (uint32_t*)d.dqf[1], (uint32_t*)d.dqf[2], d.id};
 #pragma unroll
-    for (int k = 0; k < 10; k += 2) move_pair(sa[k], da[k], sa[k + 1], da[k + 1], l, i0, cnt, sidx, pos);
+    for (int k = 0; k < 10; k += 2) {
+      const uint32_t two = (mask >> k) & 3u;
+      if (two == 3u) move_pair(sa[k], da[k], sa[k + 1], da[k + 1], l, i0, cnt, sidx, pos);
+      else if (two == 1u) move_array(sa[k], da[k], l, i0, cnt, sidx, pos);
+      else if (two == 2u) move_array(sa[k + 1], da[k + 1], l, i0, cnt, sidx, pos);
+    }
   }
+}
+
+__global__ void __launch_bounds__(256) k_copy(CopyArgs a) {
+  const int k = blockIdx.y;
+  const int64_t n4 = a.words[k] / 4;   // 16-byte words, then the rest
+  const uint4* src = (const uint4*)a.src[k];
+  uint4* dst = (uint4*)a.dst[k];
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n4; i += (int64_t)gridDim.x * blockDim.x)
+    dst[i] = src[i];
+  const int64_t i = 4 * n4 + threadIdx.x;
+  if (blockIdx.x == 0 && i < a.words[k]) a.dst[k][i] = a.src[k][i];
 }
 
 // ------------------------------------------------- exclusive scan (uint32) --
@@ -490,9 +505,22 @@ void launch_sort_rank_batch(const SortArgs& a, hipStream_t s) {
   scan_exclusive(a.count, keys, a.scan_scratch, s);
 }
 
+// The arrays start on 256-byte boundaries.
+void launch_copy(const CopyArgs& a, hipStream_t s) {
+  int64_t most = 0;
+  for (int k = 0; k < a.n; ++k) most = a.words[k] > most ? a.words[k] : most;
+  const int64_t blocks = (most / 4 + 1023) / 1024;
+  hipLaunchKernelGGL(k_copy, dim3((unsigned)(blocks < 1 ? 1 : blocks > 4096 ? 4096 : blocks), (unsigned)a.n), dim3(256),
+                     0, s, a);
+}
+
 void launch_sort(const SortArgs& a, hipStream_t s) {
-  const int64_t n = a.seg.n;
   launch_sort_rank(a, s);
+  launch_sort_move(a, s);
+}
+
+void launch_sort_move(const SortArgs& a, hipStream_t s) {
+  const int64_t n = a.seg.n;
   hipLaunchKernelGGL(k_sort_move, dim3((unsigned)((n + kRankBlock - 1) / kRankBlock)), dim3(256), 0, s, a);
 }
 

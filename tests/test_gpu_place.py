@@ -35,3 +35,20 @@ def test_created_state_is_the_canonical_sample(prec, grid_n, n, sort_every):
         x, q = ctx.read_state(s)
         assert np.array_equal(x, xa) and np.array_equal(q, qa)
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_density_stays_readable_across_reordering(prec):
+    """Re-orders in place work in the FFT scratch and leave the last density alone."""
+    cfg = workloads.small("c3", grid_n=128, n_side=64, n_steps=40, precision=prec, box_mpc=500.0, z_begin=300.0,
+                          z_end=20.0, sort_every=0, sort_cells=0.0)
+    ctx, _, species = fastdf.setup_workload(cfg)
+    ctx.step(4)
+    ctx.power_spectrum(species, 8)
+    before = [ctx.read_density(h) for h in (0, 1)]
+    ctx.timing()
+    ctx.step(36)
+    assert ctx.read_timing("sort")[1] >= 2
+    for h in (0, 1):
+        assert np.array_equal(before[h], ctx.read_density(h))
+    ctx.close()
