@@ -122,12 +122,21 @@ double power_amplitude(double sigma8, double ns, double gamma, double h) {
   return sigma8 * sigma8 / s2;
 }
 
+// int_0^64 f(x) dx over panels that double in width from 2^-12: an integrand
+// like x^2 sqrt(x^2 + s^2) / (1 + e^x) varies on the scale of x (or of 1) for
+// every s, so 16 points on each of the 19 panels leave binary64 rounding alone.
+template <class F> double integrate_doubling(F f) {
+  double sum = gl16().integrate(f, 0.0, 0x1p-12, 1);
+  for (double lo = 0x1p-12; lo < 64.0; lo *= 2.0) sum += gl16().integrate(f, lo, 2.0 * lo, 1);
+  return sum;
+}
+
 // <eps>(a) = int q^2 sqrt(q^2 + m^2 a^2) fbar / int q^2 fbar  (eq. rho_def normalisation)
 double mean_energy(double m, double a) {
   const double T = t_nu_ev(), ma = m * a;
-  auto num = [&](double x) { return x * x * std::sqrt(x * x * T * T + ma * ma) / (1.0 + std::exp(x)); };
-  auto den = [&](double x) { return x * x / (1.0 + std::exp(x)); };
-  return gl16().integrate(num, 0.0, 200.0, 800) / gl16().integrate(den, 0.0, 200.0, 800);
+  static const double den = integrate_doubling([](double x) { return x * x / (1.0 + std::exp(x)); });
+  return integrate_doubling([&](double x) { return x * x * std::sqrt(x * x * T * T + ma * ma) / (1.0 + std::exp(x)); }) /
+         den;
 }
 
 // Radiation-to-matter potential factor g(a) = (10/9) Phi(y)/Phi(0), y = a/a_eq,
@@ -360,6 +369,7 @@ struct fdf_ctx {
   TimingRec tim[FDF_KERNEL_COUNT];
   bool have_density = false;
   int density_auto = 0;
+  double* pinned = nullptr;   // 3 kMaxBins doubles of page-locked host memory for the spectra's bins
 };
 
 namespace {
@@ -533,27 +543,31 @@ int build_grid(fdf_ctx* c, int field, double a, int buf = 0) {
   return launched(c, "grid build");
 }
 
-// Two device tables of segments, one per buffer copy.
+// Two device tables of segments, one per buffer copy, stored by kernels from
+// their arguments: nothing waits for the stream.
 int upload_segments(fdf_ctx* c) {
   if (!c->seg_dirty) return FDF_OK;
+  static_assert(sizeof(Segment) % 8 == 0, "whole words");
   const size_t table = align_up((size_t)c->cfg.max_species * sizeof(Segment));
-  for (int copy = 0; copy < 2; ++copy) {
-    std::vector<Segment> segs;
-    for (auto& s : c->species) {
-      Segment g = s.seg[copy];
-      g.grid = c->fields[s.field].grid;
-      g.grid2 = c->fields[s.field].grid2;
-      g.m = s.m;
-      segs.push_back(g);
+  constexpr size_t per = kStoreWords * 8 / sizeof(Segment);
+  StoreArgs st;
+  for (int copy = 0; copy < 2; ++copy)
+    for (size_t i = 0; i < c->species.size(); i += per) {
+      const size_t n = std::min(per, c->species.size() - i);
+      for (size_t k = 0; k < n; ++k) {
+        const SpeciesRec& s = c->species[i + k];
+        Segment g = s.seg[copy];
+        g.grid = c->fields[s.field].grid;
+        g.grid2 = c->fields[s.field].grid2;
+        g.m = s.m;
+        std::memcpy((char*)st.w + k * sizeof(Segment), &g, sizeof(g));
+      }
+      st.dst = (uint64_t*)(c->ws + c->lay.seg + copy * table + i * sizeof(Segment));
+      st.n = (int32_t)(n * sizeof(Segment) / 8);
+      launch_store(st, c->stream);
     }
-    int rc = hip_check(c, hipMemcpyAsync(c->ws + c->lay.seg + copy * table, segs.data(),
-                                         segs.size() * sizeof(Segment), hipMemcpyHostToDevice, c->stream),
-                       "segment upload");
-    if (rc) return rc;
-  }
-  int rc = hip_check(c, hipStreamSynchronize(c->stream), "segment upload");
   c->seg_dirty = false;
-  return rc;
+  return launched(c, "segment upload");
 }
 
 // LDS bytes per 4-wave push block that leave room for exactly `waves` blocks
@@ -1259,7 +1273,9 @@ int fdf_attach_workspace(fdf_ctx* c, void* dptr, size_t bytes) {
   c->ws_bytes = bytes;
   fill_twiddles(c);
   char* st = nullptr;
-  const int rc = static_scratch(c, &st);   // set-up of the no-allocation entry point's scratch
+  int rc = static_scratch(c, &st);   // set-up of the no-allocation entry point's scratch
+  if (!rc && !c->pinned)
+    rc = hip_check(c, hipHostMalloc((void**)&c->pinned, 3 * kMaxBins * sizeof(double)), "page-locked bins");
   if (rc) return rc;
   return fdf_reset(c);
 }
@@ -1282,6 +1298,7 @@ int fdf_destroy(fdf_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   clear_graphs(c);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+  if (c->pinned) (void)hipHostFree(c->pinned);
   for (auto& t : c->tim) {
     for (auto& e : t.pending) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
     for (auto& e : t.pool) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
@@ -1865,8 +1882,8 @@ static int power_spectrum(fdf_ctx* c, const int32_t* sp, int32_t ns, int32_t nbi
   timing_end(c, FDF_KERNEL_OUTPUT, ev);
   rc = launched(c, "power spectrum");
   if (rc) return rc;
-  std::vector<double> hb(3 * nbins);
-  rc = hip_check(c, hipMemcpyAsync(hb.data(), b.bins, hb.size() * 8, hipMemcpyDeviceToHost, c->stream), "bins");
+  double* const hb = c->pinned;
+  rc = hip_check(c, hipMemcpyAsync(hb, b.bins, 3 * nbins * sizeof(double), hipMemcpyDeviceToHost, c->stream), "bins");
   if (!rc) rc = hip_check(c, hipStreamSynchronize(c->stream), "bins");
   if (rc) return rc;
   for (int i = 0; i < nbins; ++i) {
@@ -1928,41 +1945,30 @@ int fdf_read_state(fdf_ctx* c, int32_t sid, double* hx, double* hq) {
   if (!c) return FDF_ERR_ARG;
   if (sid < 0 || sid >= (int)c->species.size()) return fail(c, FDF_ERR_ARG, "bad species id");
   const SpeciesRec& s = c->species[sid];
-  const Segment& g = s.seg[s.cur];
-  const int64_t n = s.n;
-  const bool f64 = c->cfg.precision == FDF_PREC_FP64;
-  int rc = hip_check(c, hipStreamSynchronize(c->stream), "sync");
-  if (rc) return rc;
-  std::vector<uint32_t> id(n);
-  rc = hip_check(c, hipMemcpy(id.data(), g.id, n * 4, hipMemcpyDeviceToHost), "read ids");
-  if (rc) return rc;
-  std::vector<double> bd(f64 ? n : 0);
-  std::vector<float> bf(f64 ? 0 : n), bc(f64 ? 0 : n);
-  std::vector<uint32_t> bu(f64 ? 0 : n);
-  for (int d = 0; d < 3; ++d) {
-    if (hx) {
-      if (f64) {
-        rc = hip_check(c, hipMemcpy(bd.data(), g.xd[d], n * 8, hipMemcpyDeviceToHost), "read x");
-        for (int64_t i = 0; i < n && !rc; ++i) hx[3 * (size_t)id[i] + d] = bd[i];
-      } else {
-        rc = hip_check(c, hipMemcpy(bu.data(), g.xu[d], n * 4, hipMemcpyDeviceToHost), "read x");
-        for (int64_t i = 0; i < n && !rc; ++i) hx[3 * (size_t)id[i] + d] = (double)bu[i] * (c->cfg.box_mpc * 0x1p-32);
-      }
+  // a kernel puts the state in id order in the FFT scratch (FP32: below the
+  // density copy), in slices of ids that fit
+  ReadStateArgs a{};
+  a.seg = s.seg[s.cur];
+  a.fp64 = c->cfg.precision == FDF_PREC_FP64;
+  a.box = c->cfg.box_mpc;
+  a.out = (double*)(c->ws + c->lay.scratch);
+  const size_t room = a.fp64 ? c->lay.scratch_bytes : density_copy_offset(c);
+  const int64_t slice = (int64_t)(room / (3 * sizeof(double)));
+  for (int m = 0; m < 2; ++m) {
+    double* h = m ? hq : hx;
+    if (!h) continue;
+    a.momenta = m;
+    for (a.first = 0; a.first < s.n; a.first += slice) {
+      a.count = std::min<int64_t>(slice, s.n - a.first);
+      launch_read_state(a, c->stream);
+      int rc = launched(c, "read state");
+      if (!rc)
+        rc = hip_check(c, hipMemcpyAsync(h + 3 * a.first, a.out, (size_t)a.count * 3 * sizeof(double),
+                                         hipMemcpyDeviceToHost, c->stream), "read state");
+      if (rc) return rc;
     }
-    if (rc) return rc;
-    if (hq) {
-      if (f64) {
-        rc = hip_check(c, hipMemcpy(bd.data(), g.qd[d], n * 8, hipMemcpyDeviceToHost), "read q");
-        for (int64_t i = 0; i < n && !rc; ++i) hq[3 * (size_t)id[i] + d] = bd[i];
-      } else {
-        rc = hip_check(c, hipMemcpy(bf.data(), g.q0f[d], n * 4, hipMemcpyDeviceToHost), "read q0");
-        if (!rc) rc = hip_check(c, hipMemcpy(bc.data(), g.dqf[d], n * 4, hipMemcpyDeviceToHost), "read dq");
-        for (int64_t i = 0; i < n && !rc; ++i) hq[3 * (size_t)id[i] + d] = (double)bf[i] + (double)bc[i];
-      }
-    }
-    if (rc) return rc;
   }
-  return FDF_OK;
+  return hip_check(c, hipStreamSynchronize(c->stream), "sync");
 }
 
 int fdf_read_grid(fdf_ctx* c, int32_t field_id, int32_t slot, double* h) {

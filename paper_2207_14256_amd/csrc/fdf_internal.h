@@ -245,6 +245,26 @@ struct CopyArgs {
   int64_t words[10];
 };
 
+// State in binary64 by id: out[3 (id - first) + axis] for the ids in [first,
+// first + count).
+struct ReadStateArgs {
+  Segment seg;
+  int32_t fp64;
+  int32_t momenta;         // 0: positions [Mpc], 1: momenta [eV]
+  double box;
+  int64_t first, count;
+  double* out;
+};
+
+// Words stored by a kernel from its own arguments (a small upload that waits
+// for nothing).
+constexpr int kStoreWords = 384;
+struct StoreArgs {
+  uint64_t* dst;
+  int32_t n;
+  uint64_t w[kStoreWords];
+};
+
 struct SampleArgs {
   Segment seg;
   int32_t fp64;
@@ -343,6 +363,8 @@ void launch_fixed_to_real(const FixedToRealArgs& a, hipStream_t s);
 void launch_bins_finalize(const double* bins, int nbins, double* out, hipStream_t s);
 void launch_power_spectrum(const PkArgs& a, hipStream_t s);
 void launch_bin(const PkArgs& a, hipStream_t s);   // bins planes bin_plane (and + 1) into a.bins
+void launch_read_state(const ReadStateArgs& a, hipStream_t s);
+void launch_store(const StoreArgs& a, hipStream_t s);
 void launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
 int push_chunk_particles(int ppt);
 void launch_sort(const SortArgs& a, hipStream_t s);        // rank pass, scan and move pass

@@ -315,6 +315,26 @@ __global__ void __launch_bounds__(256) k_force_terms(TermArgs a) {
   if (threadIdx.x < 4) atomicAdd(&a.out[threadIdx.x], red[threadIdx.x][0]);
 }
 
+__global__ void __launch_bounds__(256) k_read_state(ReadStateArgs a) {
+  const double scale = a.box * 0x1p-32;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.seg.n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t k = (int64_t)a.seg.id[i] - a.first;
+    if (k < 0 || k >= a.count) continue;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      double v;
+      if (a.momenta) v = a.fp64 ? a.seg.qd[d][i] : (double)a.seg.q0f[d][i] + (double)a.seg.dqf[d][i];
+      else v = a.fp64 ? a.seg.xd[d][i] : (double)a.seg.xu[d][i] * scale;
+      a.out[3 * k + d] = v;
+    }
+  }
+}
+
+__global__ void k_store(StoreArgs a) {
+  for (int i = threadIdx.x; i < a.n; i += blockDim.x) a.dst[i] = a.w[i];
+}
+
 __global__ void k_fill_zero(uint4* p, size_t n16) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16;
        i += (size_t)gridDim.x * blockDim.x)
@@ -365,6 +385,14 @@ void launch_deposit_max(const OutputArgs& a, hipStream_t s) {
 
 void launch_fixed_to_real(const FixedToRealArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_fixed_to_real, dim3(grid_for(a.n / 4, 256)), dim3(256), 0, s, a);
+}
+
+void launch_read_state(const ReadStateArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_read_state, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
+}
+
+void launch_store(const StoreArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_store, dim3(1), dim3(128), 0, s, a);
 }
 
 // Zero a 16-byte aligned buffer whose size is a multiple of 16 with a plain
