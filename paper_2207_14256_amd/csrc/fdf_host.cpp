@@ -947,11 +947,18 @@ struct LaunchMember {
 // particles, 24 steps: 75 us with 256 blocks of 4 per thread, 46 us with 1024
 // of 1 per thread).
 constexpr int64_t kMinPushBlocks = 2048;
-// Particles per thread of a re-sorting push of several steps: the gathers of
-// the steps then outweigh the scatter, and more of them in flight per wave pay
-// (512^3 particles, 6.4 steps per launch: 9.73, 9.42 and 9.10 ms with 1, 2 and
-// 4; the one-step launch 4.04 ms with 1, slower with 4).
-constexpr int kSortPushPptSteps = 4;
+// LDS reserved per block of a wide or re-sorting push so that a CU holds one
+// block of 1024 particles.  Over several steps the gathers are bound by the
+// address unit and the 32 KB L1, whose hits come from particles that are
+// neighbours in the order: 1024 of them touch about 33 KB of a bfloat16 mesh,
+// and a second block on the CU, from elsewhere in the order, evicts it.
+// 512^3 particles, 6.4 steps per re-sorting launch: 9.73, 9.42 and 9.10 ms with
+// 1, 2 and 4 particles per thread and as many blocks as fit, 8.77, 9.21 and
+// 13.1 ms with one block; one step: 4.16 -> 4.09 ms with 1 per thread;
+// super-steps on 256^3: 2.89 -> 2.30 ms.  Sparse species
+// (below half a particle per mesh cell) touch more lines per particle and want
+// fewer waves: 100 M on 13 meshes of 256^3, 6.36 ms with 2 per thread, 6.7 with 1.
+constexpr int kOneBlockReserve = 90 * 1024;
 
 // One launch over the members (at most kMaxJobs), all standing at the same
 // launch index (pa.step[0]) and all fused or all plain.
@@ -966,16 +973,29 @@ int run_launch(fdf_ctx* c, PushArgs& pa, const std::vector<LaunchMember>& member
   for (auto& m : members) total += c->species[m.species].n;
   int longest = 1;
   for (auto& m : members) longest = std::max(longest, m.plan.span);
-  if (fused) pa.ppt = longest > 1 ? kSortPushPptSteps : c->sort_push_ppt;
-  else pa.ppt = pa.fp64 || pa.eom != FDF_EOM_SEPARABLE ? 1 : c->ppt;
-  while (pa.ppt > 1 && total < kMinPushBlocks * push_chunk_particles(pa.ppt)) pa.ppt /= 2;
-  const int64_t per = fused ? kSortBlock : push_chunk_particles(pa.ppt);
+  const bool one_each = pa.fp64 || pa.eom != FDF_EOM_SEPARABLE;   // kernels of one particle per thread
+  // wide blocks: for launches of several steps that can give every CU one
+  const bool wide = longest > 1 && !pa.tsc && pa.eom == FDF_EOM_SEPARABLE && total >= 256 * kPushWideBlock;
+  std::vector<char> mesh(c->fields.size(), 0);
+  for (auto& m : members) mesh[c->species[m.species].field] = 1;
+  int64_t meshes = 0;
+  for (char r : mesh) meshes += r;
+  const int64_t cells = meshes * (int64_t)c->cfg.grid_n * c->cfg.grid_n * c->cfg.grid_n;
+  if (fused) {
+    pa.ppt = longest > 1 ? (2 * total < cells ? 2 : 1) : c->sort_push_ppt;
+  } else {
+    pa.block = wide ? kPushWideBlock : kPushBlock;
+    pa.ppt = wide || one_each ? 1 : c->ppt;
+    pa.lds_reserve = wide ? kOneBlockReserve : push_lds_reserve(c->push_waves);
+  }
+  while (pa.ppt > 1 && total < kMinPushBlocks * kPushBlock * pa.ppt) pa.ppt /= 2;
+  if (fused) pa.lds_reserve = pa.ppt <= 2 ? kOneBlockReserve : 0;
+  const int64_t per = fused ? kSortBlock : pa.block * pa.ppt;
   const SortArgs sa = sort_args(c, c->species[members[0].species], 0.0, 0.0);
   pa.key_out = (uint32_t*)(c->ws + c->lay.sort_key);
   pa.key_mask = 0;
   pa.key_fine_bits = sa.fine_bits;
   int64_t blocks = 0, base = 0;
-  std::vector<char> mesh(c->fields.size(), 0);
   for (auto& m : members) {
     const SpeciesRec& s = c->species[m.species];
     const int j = b.njobs++;
@@ -993,7 +1013,6 @@ int run_launch(fdf_ctx* c, PushArgs& pa, const std::vector<LaunchMember>& member
     pa.nsteps[j] = (int8_t)m.plan.span;
     blocks += (s.n + per - 1) / per;
     base += s.n;
-    mesh[s.field] = 1;
   }
   b.job_block[b.njobs] = blocks;
   pa.grid_blocks = batch_grid(b);
@@ -1006,7 +1025,6 @@ int run_launch(fdf_ctx* c, PushArgs& pa, const std::vector<LaunchMember>& member
     timing_begin(c, FDF_KERNEL_SORT, &ev);
     launch_sort_rank_batch(a, stream_of(c));
     timing_end(c, FDF_KERNEL_SORT, ev);
-    pa.lds_reserve = 0;   // the cap on resident waves is the plain push's; this kernel runs at full occupancy
     pa.sort_src = a.src;
     pa.sort_rank = a.rank;
     pa.sort_bucket = a.bucket;
@@ -1016,14 +1034,11 @@ int run_launch(fdf_ctx* c, PushArgs& pa, const std::vector<LaunchMember>& member
     launch_push_sort(pa, stream_of(c));
     timing_end(c, cls, ev);
   } else {
-    pa.lds_reserve = push_lds_reserve(c->push_waves);
     timing_begin(c, cls, &ev);
     launch_push(pa, stream_of(c));
     timing_end(c, cls, ev);
   }
-  int64_t meshes = 0;
-  for (char r : mesh) meshes += r;
-  timing_work(c, cls, 0, pa.step, 0, meshes * (int64_t)c->cfg.grid_n * c->cfg.grid_n * c->cfg.grid_n * (pa.blend ? 2 : 1));
+  timing_work(c, cls, 0, pa.step, 0, cells * (pa.blend ? 2 : 1));
   for (auto& m : members) {
     SpeciesRec& s = c->species[m.species];
     timing_work(c, cls, s.n, pa.step, m.plan.span, 0);

@@ -163,6 +163,10 @@ inline int64_t batch_grid(const SpeciesBatch& sb) {
   return 8 * most;
 }
 
+// Threads per block of a plain push.  The wide block (CIC, separable form) is
+// for launches of several steps.
+constexpr int kPushBlock = 256, kPushWideBlock = 1024;
+
 // One leapfrog step of a launch: the kick at its time point and the drift to
 // the next one (do_drift = 0: a kick alone, the last step of a call).
 struct PushStep {
@@ -190,7 +194,8 @@ struct PushArgs {
   int32_t G;
   int32_t eom;             // 0: separable form (fdf_config.eom), else a form of fdf_push_eom.hip
   double box;              // L
-  int32_t ppt;             // particles per thread (re-sorting push: 1, 2 or 4)
+  int32_t block;           // plain push: threads per block, kPushBlock or kPushWideBlock
+  int32_t ppt;             // particles per thread (re-sorting push: 1, 2 or 4; wide blocks: 1)
   int32_t persistent;      // 0: one block per chunk; > 0: this many blocks (a multiple of 8) loop
   int64_t grid_blocks;     // batch_grid of the batch
   int32_t tsc;             // 1: TSC (r = 2) force interpolation, 0: CIC
@@ -366,7 +371,6 @@ void launch_bin(const PkArgs& a, hipStream_t s);   // bins planes bin_plane (and
 void launch_read_state(const ReadStateArgs& a, hipStream_t s);
 void launch_store(const StoreArgs& a, hipStream_t s);
 void launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
-int push_chunk_particles(int ppt);
 void launch_sort(const SortArgs& a, hipStream_t s);        // rank pass, scan and move pass
 void launch_sort_move(const SortArgs& a, hipStream_t s);   // the move pass alone
 void launch_copy(const CopyArgs& a, hipStream_t s);

@@ -261,7 +261,7 @@ __device__ __forceinline__ uint32_t next_key(const PushArgs& a, int j, const uin
   return sort_key::key_f32(xu, q, ma, ts, a.key_tau[j] != 0.0, 32 - a.log2g, a.key_fine_bits);
 }
 
-template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32>
+template <int NSLOT, int BLOCK, int PPT, bool BLEND, bool TSC, bool OFF32>
 __device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t b) {
   const Segment* sgp;
   int job;
@@ -269,7 +269,7 @@ __device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t b) {
   if (!block_chunk(a, b, &sgp, &job, &chunk)) return;
   const Segment& sg = *sgp;
   // chunk-relative arrays: a uniform base and a 32-bit lane index
-  const int64_t c0 = chunk * (int64_t)(kBlock * PPT);
+  const int64_t c0 = chunk * (int64_t)(BLOCK * PPT);
   const int64_t left = sg.n - c0;
   uint32_t* X[3];
   const float* Q0[3];
@@ -283,10 +283,10 @@ __device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t b) {
   // stored, so the loads and updates are straight-line code.
   uint32_t xu[PPT][3];
   float dq[PPT][3], q0[PPT][3];
-  const uint32_t last = (uint32_t)min<int64_t>(left - 1, (int64_t)(PPT * kBlock - 1));
+  const uint32_t last = (uint32_t)min<int64_t>(left - 1, (int64_t)(PPT * BLOCK - 1));
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
-    const uint32_t i = min(threadIdx.x + (uint32_t)(p * kBlock), last);
+    const uint32_t i = min(threadIdx.x + (uint32_t)(p * BLOCK), last);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       xu[p][d] = ldnt(&X[d][i]);
@@ -298,7 +298,7 @@ __device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t b) {
   const bool moved = a.step[0].do_drift != 0;   // only the last step may be a kick alone
 #pragma unroll
   for (int p = 0; p < PPT; ++p) {
-    const uint32_t i = threadIdx.x + (uint32_t)(p * kBlock);
+    const uint32_t i = threadIdx.x + (uint32_t)(p * BLOCK);
     if ((int64_t)i >= left) break;
     if (moved) {
 #pragma unroll
@@ -311,7 +311,7 @@ __device__ __forceinline__ void push_chunk_f32(const PushArgs& a, int64_t b) {
     uint32_t* K = a.key_out + a.batch.job_slot[job] + c0;
 #pragma unroll
     for (int p = 0; p < PPT; ++p) {
-      const uint32_t i = threadIdx.x + (uint32_t)(p * kBlock);
+      const uint32_t i = threadIdx.x + (uint32_t)(p * BLOCK);
       if ((int64_t)i >= left) break;
       K[i] = next_key(a, job, xu[p], q0[p], dq[p]);
     }
@@ -456,7 +456,7 @@ __device__ __forceinline__ void gather_stencil_f64(const void* grid, const uint3
   }
 }
 
-template <int NSLOT, bool BLEND, bool TSC, bool OFF32>
+template <int NSLOT, int BLOCK, bool BLEND, bool TSC, bool OFF32>
 __device__ __forceinline__ void push_chunk_f64(const PushArgs& a, int64_t b) {
 #pragma clang fp contract(off)
   constexpr int NP = Stencil<TSC>::N;
@@ -471,7 +471,7 @@ __device__ __forceinline__ void push_chunk_f64(const PushArgs& a, int64_t b) {
   const void* gridA = (BLEND && a.grid_sel) ? sg.grid2 : sg.grid;
   const void* gridB = (BLEND && a.grid_sel) ? sg.grid : sg.grid2;
   // chunk-relative arrays: a uniform base and a 32-bit lane index
-  const int64_t c0 = chunk * (int64_t)kBlock;
+  const int64_t c0 = chunk * (int64_t)BLOCK;
   const int64_t left = sg.n - c0;
   double* X[3];
   double* Q[3];
@@ -534,50 +534,55 @@ __device__ __forceinline__ void push_chunk_f64(const PushArgs& a, int64_t b) {
 // Chunk loop.  One block per chunk, or (persistent) a fixed grid whose
 // blocks stride over the chunks; either way each XCD (block id mod 8) walks a
 // contiguous eighth of every species' chunks.
-template <int NSLOT, int PPT, bool BLEND, bool TSC, bool OFF32>
-__global__ void __launch_bounds__(kBlock) k_push_f32(PushArgs a) {
-  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x) push_chunk_f32<NSLOT, PPT, BLEND, TSC, OFF32>(a, b);
+template <int NSLOT, int BLOCK, int PPT, bool BLEND, bool TSC, bool OFF32>
+__global__ void __launch_bounds__(BLOCK) k_push_f32(PushArgs a) {
+  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x)
+    push_chunk_f32<NSLOT, BLOCK, PPT, BLEND, TSC, OFF32>(a, b);
 }
 
-template <int NSLOT, bool BLEND, bool TSC, bool OFF32>
-__global__ void __launch_bounds__(kBlock) k_push_f64(PushArgs a) {
-  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x) push_chunk_f64<NSLOT, BLEND, TSC, OFF32>(a, b);
+template <int NSLOT, int BLOCK, bool BLEND, bool TSC, bool OFF32>
+__global__ void __launch_bounds__(BLOCK) k_push_f64(PushArgs a) {
+  for (int64_t b = blockIdx.x; b < a.grid_blocks; b += gridDim.x)
+    push_chunk_f64<NSLOT, BLOCK, BLEND, TSC, OFF32>(a, b);
 }
 
-// Block count and LDS reserve of a plain push; byte offsets of the mesh fit 32 bits?
+// Grid of a plain push, its LDS reserve, and whether the byte offsets of the
+// mesh fit 32 bits.
 struct PushLaunch {
-  dim3 grid, block;
+  dim3 grid;
   bool off32;
   explicit PushLaunch(const PushArgs& a)
-      : grid((unsigned)(a.persistent ? a.persistent : a.grid_blocks)), block(kBlock),
+      : grid((unsigned)(a.persistent ? a.persistent : a.grid_blocks)),
         off32((uint64_t)a.G * a.G * a.G * (uint64_t)(a.nslot * (a.fp64 ? 8 : 2)) <= (1ull << 32)) {}
 };
 
-template <int PPT, bool BLEND, bool TSC>
+template <int BLOCK, int PPT, bool BLEND, bool TSC>
 void push_launch(const PushArgs& a, hipStream_t s) {
   const PushLaunch l(a);
+  const dim3 block(BLOCK);
   if (l.off32) {
-    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
-    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
-    else hipLaunchKernelGGL((k_push_f32<4, PPT, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, BLOCK, PPT, BLEND, TSC, true>), l.grid, block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, BLOCK, PPT, BLEND, TSC, true>), l.grid, block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f32<4, BLOCK, PPT, BLEND, TSC, true>), l.grid, block, a.lds_reserve, s, a);
   } else {
-    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, PPT, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
-    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, PPT, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
-    else hipLaunchKernelGGL((k_push_f32<4, PPT, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f32<8, BLOCK, PPT, BLEND, TSC, false>), l.grid, block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f32<6, BLOCK, PPT, BLEND, TSC, false>), l.grid, block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f32<4, BLOCK, PPT, BLEND, TSC, false>), l.grid, block, a.lds_reserve, s, a);
   }
 }
 
-template <bool BLEND, bool TSC>
+template <int BLOCK, bool BLEND, bool TSC>
 void push_launch_f64(const PushArgs& a, hipStream_t s) {
   const PushLaunch l(a);
+  const dim3 block(BLOCK);
   if (l.off32) {
-    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
-    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
-    else hipLaunchKernelGGL((k_push_f64<4, BLEND, TSC, true>), l.grid, l.block, a.lds_reserve, s, a);
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, BLOCK, BLEND, TSC, true>), l.grid, block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, BLOCK, BLEND, TSC, true>), l.grid, block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f64<4, BLOCK, BLEND, TSC, true>), l.grid, block, a.lds_reserve, s, a);
   } else {
-    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
-    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
-    else hipLaunchKernelGGL((k_push_f64<4, BLEND, TSC, false>), l.grid, l.block, a.lds_reserve, s, a);
+    if (a.nslot == 8) hipLaunchKernelGGL((k_push_f64<8, BLOCK, BLEND, TSC, false>), l.grid, block, a.lds_reserve, s, a);
+    else if (a.nslot == 6) hipLaunchKernelGGL((k_push_f64<6, BLOCK, BLEND, TSC, false>), l.grid, block, a.lds_reserve, s, a);
+    else hipLaunchKernelGGL((k_push_f64<4, BLOCK, BLEND, TSC, false>), l.grid, block, a.lds_reserve, s, a);
   }
 }
 
@@ -606,27 +611,37 @@ void push_sort_launch(const PushArgs& a, hipStream_t s) {
 template <int PPT>
 void push_ppt(const PushArgs& a, hipStream_t s) {
   if (a.tsc) {
-    if (a.blend) push_launch<PPT, true, true>(a, s);
-    else push_launch<PPT, false, true>(a, s);
+    if (a.blend) push_launch<kBlock, PPT, true, true>(a, s);
+    else push_launch<kBlock, PPT, false, true>(a, s);
   } else {
-    if (a.blend) push_launch<PPT, true, false>(a, s);
-    else push_launch<PPT, false, false>(a, s);
+    if (a.blend) push_launch<kBlock, PPT, true, false>(a, s);
+    else push_launch<kBlock, PPT, false, false>(a, s);
   }
 }
 
 void push_f64(const PushArgs& a, hipStream_t s) {
   if (a.tsc) {
-    if (a.blend) push_launch_f64<true, true>(a, s);
-    else push_launch_f64<false, true>(a, s);
+    if (a.blend) push_launch_f64<kBlock, true, true>(a, s);
+    else push_launch_f64<kBlock, false, true>(a, s);
   } else {
-    if (a.blend) push_launch_f64<true, false>(a, s);
-    else push_launch_f64<false, false>(a, s);
+    if (a.blend) push_launch_f64<kBlock, true, false>(a, s);
+    else push_launch_f64<kBlock, false, false>(a, s);
   }
+}
+
+// Wide blocks: launches of several steps, CIC.
+void push_wide_f64(const PushArgs& a, hipStream_t s) {
+  if (a.blend) push_launch_f64<kWideBlock, true, false>(a, s);
+  else push_launch_f64<kWideBlock, false, false>(a, s);
+}
+
+void push_wide(const PushArgs& a, hipStream_t s) {
+  if (a.blend) push_launch<kWideBlock, 1, true, false>(a, s);
+  else push_launch<kWideBlock, 1, false, false>(a, s);
 }
 
 }  // namespace
 
-int push_chunk_particles(int ppt) { return kBlock * ppt; }
 
 void launch_push_sort(const PushArgs& a, hipStream_t s) {
   if (a.tsc) {
@@ -640,7 +655,12 @@ void launch_push_sort(const PushArgs& a, hipStream_t s) {
 
 void launch_push(const PushArgs& a, hipStream_t s) {
   if (a.eom != 0) { launch_push_eom(a, s); return; }
-  if (a.fp64) { push_f64(a, s); return; }
+  if (a.fp64) {
+    if (a.block == kWideBlock) push_wide_f64(a, s);
+    else push_f64(a, s);
+    return;
+  }
+  if (a.block == kWideBlock) { push_wide(a, s); return; }
   switch (a.ppt) {
     case 1: push_ppt<1>(a, s); break;
     case 2: push_ppt<2>(a, s); break;

@@ -7,7 +7,7 @@
 namespace fdf {
 namespace push_detail {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = kPushBlock, kWideBlock = kPushWideBlock;
 
 // The species (its segment in the copy that holds its state), job and
 // block-sized chunk of block b of a launch; false: a block without work.
