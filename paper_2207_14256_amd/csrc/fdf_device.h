@@ -51,15 +51,23 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // ---------------------------------------------------------------------------
 // complex helpers
 // ---------------------------------------------------------------------------
+// Workgroup barrier that orders LDS alone: global loads, stores and atomics
+// still in flight need no order against it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <typename R> struct cplx { R x, y; };
 
+// The product with b.x is the fused one, written out: left to the compiler the
+// choice, and with it the last bit, depends on the code around the call.
+__device__ __forceinline__ float fma_of(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+__device__ __forceinline__ double fma_of(double x, double y, double z) { return __builtin_fma(x, y, z); }
 template <typename R>
 __device__ __forceinline__ cplx<R> cmul(cplx<R> a, cplx<R> b) {
-  return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+  return {fma_of(a.x, b.x, -(a.y * b.y)), fma_of(a.y, b.x, a.x * b.y)};
 }
 template <typename R>
 __device__ __forceinline__ cplx<R> cmulc(cplx<R> a, cplx<R> b) {  // a * conj(b)
-  return {a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y};
+  return {fma_of(a.x, b.x, a.y * b.y), fma_of(a.y, b.x, -(a.x * b.y))};
 }
 template <typename R>
 __device__ __forceinline__ cplx<R> cadd(cplx<R> a, cplx<R> b) { return {a.x + b.x, a.y + b.y}; }

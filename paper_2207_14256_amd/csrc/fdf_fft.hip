@@ -78,57 +78,132 @@ __device__ __forceinline__ void bfly(cplx<R>* v) {
   else bfly2<INV>(v);
 }
 
-// ------------------------------------------------------------ LDS stages --
-// buf holds NB lines of length N with element n of line b at buf[n*NB + b].
-// tw is the global table e^{-2 pi i m / G}; the length-N root of unity
-// W_N^m is tw[m * TWS] with TWS = G / N.
-template <typename R, int N, int NB, int NT, bool INV, int NS, int RAD, int TWS>
-__device__ __forceinline__ void fft_stage(cplx<R>* buf, const cplx<R>* __restrict__ tw) {
-  constexpr int NBF = NB * (N / RAD);
-  constexpr int PER = (NBF + NT - 1) / NT;
-  cplx<R> v[PER][RAD];
-  const int tid = threadIdx.x;
+// ------------------------------------------------------------- LDS lines --
+// NB lines of length N, transformed together by NT threads that hold their
+// elements in registers: every stage works on registers and the lines pass
+// through LDS only between two stages, so that the caller reads its input
+// straight into the first stage's registers and takes its results out of the
+// last stage's (two exchanges and four barriers for 256 = 8 8 4).  The barriers
+// order LDS alone; global loads and stores stay in flight across them.
+// tw is the global table e^{-2 pi i m / G}; the length-N root of unity W_N^m
+// is tw[m * TWS] with TWS = G / N.  HOLD keeps a thread's twiddles in
+// registers (once per block instead of once per line group).
+// Element n of line b is at buf[at(n, b)] of kSize elements: rows of NB, with
+// a spare row after every eight, because the first stage's results are written
+// at a stride of 8 rows.  XL is for callers whose neighbouring threads hold
+// neighbouring elements of one line: the row bits that pick the bank group are
+// mixed with the next higher ones and the line bits with those above.
+template <typename R, int N, int NB, int NT, bool INV, int TWS, bool HOLD, bool XL = false>
+struct Lines {
+  static constexpr int E = NB * N / NT > 8 ? NB * N / NT : 8;   // elements per thread
+  static constexpr int ROW = NB * (int)sizeof(cplx<R>);
+  static constexpr int Q = ROW >= 256 ? 1 : ROW <= 32 ? 8 : 256 / ROW;   // rows per sweep of the banks
+  static constexpr int QSH = Q == 8 ? 3 : Q == 4 ? 2 : Q == 2 ? 1 : 0;
+  static constexpr int radix(int ns) { return N / ns >= 8 ? 8 : N / ns; }
+  static constexpr int per(int ns) { return (NB * (N / radix(ns)) + NT - 1) / NT; }
+  static constexpr bool whole(int ns) { return (NB * (N / radix(ns))) % NT == 0; }
+  // the twiddles of a stage are the same for all of a thread's butterflies
+  static constexpr bool shared(int ns) { return NT % NB == 0 && (NT / NB) % ns == 0; }
+  static constexpr int tw_count(int ns) { return (radix(ns) - 1) * (shared(ns) ? 1 : per(ns)); }
+  static constexpr int tw_offset(int ns) {
+    int o = 0;
+    for (int q = radix(1); q < ns; q *= radix(q)) o += tw_count(q);
+    return o;
+  }
+
+  static constexpr int kSize = XL ? N * NB : (N + N / 8) * NB;
+  static __device__ __forceinline__ int at(unsigned n, unsigned b) {
+    if constexpr (XL) return (n ^ ((n >> 3) & (Q - 1))) * NB + (b ^ ((n >> QSH) & (NB - 1)));
+    else return (n + n / 8) * NB + b;
+  }
+  // at(n + dn, b), dn a constant: a fixed distance where a whole number of eights apart
+  static __device__ __forceinline__ int at(unsigned n, int dn, unsigned b) {
+    return !XL && dn % 8 == 0 ? at(n, b) + (dn + dn / 8) * NB : at(n + dn, b);
+  }
+
+  // Register i of a thread holds element tid / NB + dn of line tid % NB as the
+  // stage that follows NS points expects it: f(dn, i), where dn is a constant
+  // once the loops are unrolled, so that addresses are a scalar part and one
+  // vector offset per thread.
+  template <int NS, typename F> static __device__ __forceinline__ void inputs(int tid, F f) {
+    static_assert(NT % NB == 0, "a thread keeps its line");
+    constexpr int RAD = radix(NS);
 #pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int t = tid + p * NT;
-    if (NBF % NT == 0 || t < NBF) {
-      const int b = t % NB, j = t / NB;
+    for (int p = 0; p < per(NS); ++p) {
+      if (whole(NS) || tid + p * NT < NB * (N / RAD)) {
 #pragma unroll
-      for (int r = 0; r < RAD; ++r) v[p][r] = buf[(j + r * (N / RAD)) * NB + b];
+        for (int r = 0; r < RAD; ++r) f(p * (NT / NB) + r * (N / RAD), p * RAD + r);
+      }
     }
   }
-  __syncthreads();
+  template <typename F> static __device__ __forceinline__ void first(int tid, F f) { inputs<1>(tid, f); }
+  static __device__ __forceinline__ void first(cplx<R>* v, int tid, const cplx<R>* buf) {
+    first(tid, [&](int dn, int i) { v[i] = buf[at(tid / NB, dn, tid % NB)]; });
+  }
+
+  struct Twiddles {
+    const cplx<R>* __restrict__ tw;
+    cplx<R> w[HOLD && tw_offset(N) > 0 ? tw_offset(N) : 1];
+    template <int NS> __device__ __forceinline__ void fetch(int tid) {
+      if constexpr (NS < N) {
+        if constexpr (NS > 1) {
+          constexpr int RAD = radix(NS), O = tw_offset(NS);
 #pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int t = tid + p * NT;
-    if (NBF % NT == 0 || t < NBF) {
-      const int b = t % NB, j = t / NB;
-      const int k = j % NS;
-      if (NS > 1) {
+          for (int p = 0; p < (shared(NS) ? 1 : per(NS)); ++p) {
+            if (!whole(NS) && tid + p * NT >= NB * (N / RAD)) continue;
+            const int k = ((tid + p * NT) / NB) % NS;
 #pragma unroll
-        for (int r = 1; r < RAD; ++r) {
-          cplx<R> w = tw[(r * k * (N / (NS * RAD))) * TWS];
-          v[p][r] = INV ? cmulc(v[p][r], w) : cmul(v[p][r], w);
+            for (int r = 1; r < RAD; ++r) w[O + p * (RAD - 1) + r - 1] = tw[(r * k * (N / (NS * RAD))) * TWS];
+          }
+        }
+        fetch<NS * radix(NS)>(tid);
+      }
+    }
+    __device__ __forceinline__ Twiddles(const cplx<R>* t, int tid) : tw(t) {
+      if constexpr (HOLD) fetch<1>(tid);
+    }
+    template <int NS> __device__ __forceinline__ cplx<R> get(int p, int r, int k) const {
+      constexpr int RAD = radix(NS), O = tw_offset(NS);
+      if constexpr (HOLD) return w[O + (shared(NS) ? 0 : p) * (RAD - 1) + r - 1];
+      else return tw[(r * k * (N / (NS * RAD))) * TWS];
+    }
+  };
+
+  // v: the first stage's inputs; sink(dn, z) gets element tid / NB + dn of line
+  // tid % NB.  Every read of buf is behind the last barrier, so that the next
+  // call may follow at once.
+  template <int NS = 1, typename F>
+  static __device__ __forceinline__ void run(cplx<R>* v, int tid, cplx<R>* buf, const Twiddles& w, F sink) {
+    constexpr int RAD = radix(NS);
+#pragma unroll
+    for (int p = 0; p < per(NS); ++p) {
+      if (whole(NS) || tid + p * NT < NB * (N / RAD)) {
+        const int b = tid % NB, j = tid / NB + p * (NT / NB);
+        const int k = j % NS;
+        if constexpr (NS > 1) {
+#pragma unroll
+          for (int r = 1; r < RAD; ++r) {
+            const cplx<R> z = w.template get<NS>(p, r, k);
+            v[p * RAD + r] = INV ? cmulc(v[p * RAD + r], z) : cmul(v[p * RAD + r], z);
+          }
+        }
+        bfly<RAD, INV>(v + p * RAD);
+        const int base = (j / NS) * NS * RAD + k;
+#pragma unroll
+        for (int r = 0; r < RAD; ++r) {
+          if constexpr (NS * RAD < N) buf[NS == 1 && !XL ? at(base, b) + r * NB : at(base, r * NS, b)] = v[p * RAD + r];
+          else sink(p * (NT / NB) + r * NS, v[p * RAD + r]);   // j < NS: base = j
         }
       }
-      bfly<RAD, INV>(v[p]);
-      const int base = (j / NS) * NS * RAD + k;
-#pragma unroll
-      for (int r = 0; r < RAD; ++r) buf[(base + r * NS) * NB + b] = v[p][r];
+    }
+    if constexpr (NS * RAD < N) {
+      lds_barrier();
+      inputs<NS * RAD>(tid, [&](int dn, int i) { v[i] = buf[at(tid / NB, dn, tid % NB)]; });
+      lds_barrier();
+      run<NS * RAD>(v, tid, buf, w, sink);
     }
   }
-  __syncthreads();
-}
-
-template <typename R, int N, int NB, int NT, bool INV, int TWS, int NS = 1>
-__device__ __forceinline__ void fft_lines(cplx<R>* buf, const cplx<R>* __restrict__ tw) {
-  if constexpr (NS < N) {
-    constexpr int REM = N / NS;
-    constexpr int RAD = REM >= 8 ? 8 : REM;
-    fft_stage<R, N, NB, NT, INV, NS, RAD, TWS>(buf, tw);
-    fft_lines<R, N, NB, NT, INV, TWS, NS * RAD>(buf, tw);
-  }
-}
+};
 
 // ---------------------------------------------------------- block shapes --
 template <typename R, int G> struct Shape {
@@ -136,7 +211,11 @@ template <typename R, int G> struct Shape {
   static constexpr int NB0 = 65536 / (G * CS);
   static constexpr int NB = NB0 > 16 ? 16 : (NB0 < 1 ? 1 : NB0);     // columns per strided block
   static constexpr int NBC = NB > G / 2 ? G / 2 : NB;
-  static constexpr int NBX = NBC;                                    // columns per X-pass block
+  static constexpr int NTS0 = NBC * G / 16;                          // 16 elements per thread
+  static constexpr int NTS = NTS0 < 64 ? 64 : NTS0;                  // threads per strided block
+  static constexpr int NTX0 = NBC * G < 256 ? NBC * G : 256;          // inverse X pass: at least
+  static constexpr int NTX1 = CS > 8 ? (2 * NTS > 1024 ? 1024 : 2 * NTS) : NTS;   // binary64: 8 elements
+  static constexpr int NTX = NTX1 < NTX0 ? NTX0 : NTX1;
   static constexpr int NT = 256;
   static constexpr int M = G / 2;
   static constexpr int NL0 = 1024 / G;
@@ -146,101 +225,119 @@ template <typename R, int G> struct Shape {
 
 __device__ __forceinline__ int signed_index(int i, int G) { return i < G / 2 ? i : i - G; }
 
-// Fourier-stage multiplier of one slot at wave numbers (nx, ny, nz).
-__device__ __forceinline__ void slot_multiplier(int kind, int nx, int ny, int nz, double kf,
-                                                const Transfer& tr, double& re, double& im) {
-  re = 0.0; im = 0.0;
-  const double k2 = kf * kf * (double)(nx * nx + ny * ny + nz * nz);
-  if (k2 == 0.0 || kind == SK_ZERO) return;
+// Transfer function of one slot at k^2 (times i k_a for the gradients).
+enum TransferKind : int32_t { TK_ZERO, TK_PHIDOT, TK_PHI, TK_PSI, TK_PHI_PSI };
+__device__ __forceinline__ int transfer_kind(int kind) {
+  switch (kind) {
+    case SK_DX_PSI: case SK_DY_PSI: case SK_DZ_PSI: case SK_PSI: return TK_PSI;
+    case SK_DX_PHI: case SK_DY_PHI: case SK_DZ_PHI: case SK_PHI: return TK_PHI;
+    case SK_PHIDOT: return TK_PHIDOT;
+    case SK_PHI_PSI: return TK_PHI_PSI;
+    default: return TK_ZERO;
+  }
+}
+__device__ __forceinline__ double transfer(int tk, double k2, const Transfer& tr) {
+  if (k2 == 0.0 || tk == TK_ZERO) return 0.0;
+  if (tk == TK_PHIDOT) return tr.c_phidot / k2;
   const double tphi = tr.c_phi / k2;
-  if (kind == SK_PHIDOT) { re = tr.c_phidot / k2; return; }
-  if (kind == SK_PHI) { re = tphi; return; }
-  double t = tphi;
-  if (kind == SK_DX_PSI || kind == SK_DY_PSI || kind == SK_DZ_PSI || kind == SK_PSI || kind == SK_PHI_PSI)
-    t = tphi * (1.0 - tr.slip_amp * exp(-sqrt(k2) / tr.slip_k));
-  if (kind == SK_PSI) { re = t; return; }
-  if (kind == SK_PHI_PSI) { re = tphi + t; return; }
-  int n = (kind == SK_DX_PSI || kind == SK_DX_PHI) ? nx
-        : (kind == SK_DY_PSI || kind == SK_DY_PHI) ? ny : nz;
-  im = kf * (double)n * t;   // i k_a T
+  if (tk == TK_PHI) return tphi;
+  const double tpsi = tphi * (1.0 - tr.slip_amp * exp(-sqrt(k2) / tr.slip_k));
+  return tk == TK_PSI ? tpsi : tphi + tpsi;
 }
 
 // ------------------------------------------------------------------ X pass --
-// delta_0 is read again for every field (from L2 after the first) rather
-// than held in registers across the fields: the multipliers' binary64
-// arithmetic then leaves room for several waves per SIMD.
+// The transfer function of a thread's modes is kept over the slots that share
+// it (three gradient components, as a rule): its binary64 square root,
+// exponential and division are the pass's longest arithmetic.  16 elements per
+// thread in binary32 (8 in binary64), the modes, their transfer function and
+// the twiddles in registers: two waves per SIMD, and still faster than with the
+// modes read again (198 us) or the twiddles (172 us).
+// 7 slots of 256^3 in binary32 (0.54 GB): 249 us with the lines in LDS through
+// every stage and a transfer function per slot, 160 us.  6 slots of 512^3:
+// 2.14 -> 1.21 ms.  The binary64 form: 350 -> 301 us.  Splitting the slots over
+// several X-Y launch pairs, so that the second pass finds its planes in the
+// memory-side cache, takes from the Y pass what the X pass loses.
 template <typename R, int G>
-__global__ void __launch_bounds__(256) k_xpass_inverse(GridBuildArgs a) {
+__global__ void __launch_bounds__((Shape<R, G>::NTX)) k_xpass_inverse(GridBuildArgs a) {
   using S = Shape<R, G>;
-  constexpr int NB = S::NBX, NT = S::NT, M = S::M;
-  constexpr int PER = (G * NB + NT - 1) / NT;
-  __shared__ cplx<R> buf[G * NB];
-  const int nzb = M / NB;
+  constexpr int NB = S::NBC, M = S::M;
+  constexpr bool kHold = sizeof(R) == 4;   // binary64: registers run out
+  using L = Lines<R, G, NB, S::NTX, true, 1, kHold>;
+  __shared__ union { cplx<R> lines[L::kSize]; double t[G * NB]; } lds;
+  cplx<R>* const buf = lds.lines;
+  double* const tbuf = lds.t;
+  const int nzb = M / NB, tid = threadIdx.x;
   const int iy = blockIdx.x / nzb, iz0 = (blockIdx.x % nzb) * NB;
-  const cplx<R>* __restrict__ din = (const cplx<R>*)a.delta_k;
-  const cplx<R>* __restrict__ tw = (const cplx<R>*)a.twiddle;
-  cplx<R>* scr = (cplx<R>*)a.scratch;
+  const cplx<R>* __restrict__ din = (const cplx<R>*)a.delta_k + (size_t)iy * M + iz0;
+  cplx<R>* const scr = (cplx<R>*)a.scratch + (size_t)iy * M + iz0;
+  const uint32_t at = (uint32_t)(tid / NB) * (G * M) + tid % NB;
   const size_t plane = (size_t)G * G * M;
-  const int ny = signed_index(iy, G);
+  const typename L::Twiddles tw((const cplx<R>*)a.twiddle, tid);
+  const int ny = signed_index(iy, G), nz = iz0 + tid % NB;
+  cplx<R> d[kHold ? L::E : 1], v[L::E];
+  double t[L::E];
+  if constexpr (kHold) L::first(tid, [&](int dn, int i) { d[i] = (din + (size_t)dn * (G * M))[at]; });
+  int held = -1;
+#pragma unroll 1
   for (int f = 0; f < a.nfft; ++f) {
-    const int kind = a.kind[f];
+    const int kind = a.kind[f], tk = transfer_kind(kind);
+    int n0 = tid / NB;
+    asm volatile("" : "+v"(n0));   // the wave numbers stay in the loop: E of them would be held across it
+    if (tk != held) {
+      // evaluated in a loop, through the idle buffer: side by side in
+      // registers, the evaluations would leave room for one wave per SIMD
 #pragma unroll 2
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((G * NB) % NT == 0 || e < G * NB) {
-        const int ix = e / NB, b = e % NB;
-        const cplx<R> d = din[((size_t)ix * G + iy) * M + iz0 + b];
-        double re, im;
-        slot_multiplier(kind, signed_index(ix, G), ny, iz0 + b, a.kf, a.tr, re, im);
-        const double dx = (double)d.x, dy = (double)d.y;
-        buf[ix * NB + b] = {(R)(re * dx - im * dy), (R)(re * dy + im * dx)};
+      for (int e = tid; e < G * NB; e += S::NTX) {
+        const int nx = signed_index(e / NB, G);
+        tbuf[e] = transfer(tk, a.kf * a.kf * (double)(nx * nx + ny * ny + nz * nz), a.tr);
       }
+      lds_barrier();
+      L::first(tid, [&](int dn, int i) { t[i] = tbuf[tid + dn * NB]; });
+      lds_barrier();
+      held = tk;
     }
-    __syncthreads();
-    fft_lines<R, G, NB, NT, true, 1>(buf, tw);
-#pragma unroll 4
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((G * NB) % NT == 0 || e < G * NB) {
-        const int ix = e / NB, b = e % NB;
-        scr[f * plane + ((size_t)ix * G + iy) * M + iz0 + b] = buf[ix * NB + b];
+    // multiplier re + i im = T or i k_a T, without branches: re = T or 0, and
+    // the gradient's wave number n_a = ax n_x + na (0 for T itself)
+    const int ax = kind == SK_DX_PSI || kind == SK_DX_PHI;
+    const int na = kind == SK_DY_PSI || kind == SK_DY_PHI ? ny : kind == SK_DZ_PSI || kind == SK_DZ_PHI ? nz : 0;
+    const double one = kind >= SK_DX_PSI && kind <= SK_DZ_PHI ? 0.0 : 1.0;
+    L::first(tid, [&](int dn, int i) {
+      cplx<R> z;
+      if constexpr (kHold) {
+        asm("" : "+v"(d[i].x), "+v"(d[i].y));   // nor are the modes held in binary64
+        z = d[i];
       }
-    }
-    __syncthreads();
+      else z = (din + (size_t)dn * (G * M))[at];
+      const double re = one * t[i], im = a.kf * (double)(ax * signed_index(n0 + dn, G) + na) * t[i];
+      const double dx = (double)z.x, dy = (double)z.y;
+      v[i] = {(R)(re * dx - im * dy), (R)(re * dy + im * dx)};
+      if (kHold && i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    });
+    cplx<R>* const out = scr + f * plane;
+    L::run(v, tid, buf, tw, [&](int dn, cplx<R> z) { (out + (size_t)dn * (G * M))[at] = z; });
   }
 }
 
 // ------------------------------------------------- Y pass (either direction) --
-// blocks over (field h, ix, z-column block); lines along y; in place.
+// blocks over (field h, ix, z-column block); lines along y; in place.  7 planes
+// of 256^3 in binary32 (0.94 GB): 350 -> 176 us with one LDS exchange between
+// two stages instead of LDS in front of and behind every stage; what is left is
+// the rate of a copy.  6 planes of 512^3 ran at that rate before (1.40 ms, 1.44).
 template <typename R, int G, bool INV>
-__global__ void __launch_bounds__(256) k_ypass(cplx<R>* scr, const cplx<R>* __restrict__ tw) {
+__global__ void __launch_bounds__((Shape<R, G>::NTS)) k_ypass(cplx<R>* scr, const cplx<R>* __restrict__ twiddle) {
   using S = Shape<R, G>;
-  constexpr int NB = S::NBC, NT = S::NT, M = S::M;
-  constexpr int PER = (G * NB + NT - 1) / NT;
-  __shared__ cplx<R> buf[G * NB];
-  const int nzb = M / NB;
+  constexpr int NB = S::NBC, M = S::M;
+  using L = Lines<R, G, NB, S::NTS, INV, 1, true>;
+  __shared__ cplx<R> buf[L::kSize];
+  const int nzb = M / NB, tid = threadIdx.x;
   const int blk = blockIdx.x;
   const int izb = blk % nzb, ix = (blk / nzb) % G, f = blk / (nzb * G);
-  const int iz0 = izb * NB;
-  cplx<R>* base = scr + (size_t)f * G * G * M + (size_t)ix * G * M + iz0;
-#pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int e = threadIdx.x + p * NT;
-    if ((G * NB) % NT == 0 || e < G * NB) {
-      const int iy = e / NB, b = e % NB;
-      buf[iy * NB + b] = base[(size_t)iy * M + b];
-    }
-  }
-  __syncthreads();
-  fft_lines<R, G, NB, NT, INV, 1>(buf, tw);
-#pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int e = threadIdx.x + p * NT;
-    if ((G * NB) % NT == 0 || e < G * NB) {
-      const int iy = e / NB, b = e % NB;
-      base[(size_t)iy * M + b] = buf[iy * NB + b];
-    }
-  }
+  cplx<R>* const base = scr + (size_t)f * G * G * M + (size_t)ix * G * M + izb * NB;
+  const uint32_t at = (uint32_t)(tid / NB) * M + tid % NB;
+  cplx<R> v[L::E];
+  L::first(tid, [&](int dn, int i) { v[i] = (base + (size_t)dn * M)[at]; });
+  const typename L::Twiddles tw(twiddle, tid);
+  L::run(v, tid, buf, tw, [&](int dn, cplx<R> z) { (base + (size_t)dn * M)[at] = z; });
 }
 
 // ------------------------------------------------ Z pass: C2R + slot packing --
@@ -293,76 +390,54 @@ template <> __device__ __forceinline__ void store_cell<8, GT_F64, double>(void* 
   o[3] = make_double2(v[6], v[7]);
 }
 
+// Half-length pre-processing of one line's pair (k, M - k), 0 < k < M / 2; the
+// pair of k = 0 is made of the two elements that are their own partners, k = 0
+// (whose partner X[M], a Nyquist mode, is zero) and k = M / 2.
+// Z[k] = (X[k] + conj X[M-k]) + i e^{2 pi i k/G} (X[k] - conj X[M-k])
+template <typename R>
+__device__ __forceinline__ cplx<R> c2r_element(cplx<R> xk, cplx<R> xm, cplx<R> w) {
+  cplx<R> s = {xk.x + xm.x, xk.y - xm.y};          // X[k] + conj X[M-k]
+  cplx<R> d = {xk.x - xm.x, xk.y + xm.y};          // X[k] - conj X[M-k]
+  cplx<R> wd = cmulc(d, w);                        // d e^{+2 pi i k/G}
+  return {s.x - wd.y, s.y + wd.x};                 // s + i wd
+}
+
 // blocks over (ix, y-line block of NL lines)
 template <typename R, int G, int NSLOT, int OT>
 __global__ void __launch_bounds__(256) k_zpass_c2r(GridBuildArgs a) {
   using S = Shape<R, G>;
-  constexpr int NL = S::NL, NT = S::NT, M = S::M;
-  constexpr int PER = (M * NL + NT - 1) / NT;
+  constexpr int NL = S::NL, NT = S::NT, M = S::M, H = M / 2;
+  using L = Lines<R, M, NL, NT, true, 2, true, true>;
   __shared__ cplx<R> buf[M * NL];
   __shared__ R stage[NL * G * NSLOT];
-  const int nyb = G / NL;
+  const int nyb = G / NL, tid = threadIdx.x;
   const int ix = blockIdx.x / nyb, iy0 = (blockIdx.x % nyb) * NL;
-  const cplx<R>* __restrict__ tw = (const cplx<R>*)a.twiddle;
-  const cplx<R>* scr = (const cplx<R>*)a.scratch;
+  const cplx<R>* __restrict__ twiddle = (const cplx<R>*)a.twiddle;
+  const cplx<R>* scr = (const cplx<R>*)a.scratch + ((size_t)ix * G + iy0) * M;
   const size_t plane = (size_t)G * G * M;
-  for (int e = threadIdx.x; e < NL * G * NSLOT; e += NT) stage[e] = (R)0;
+  const typename L::Twiddles tw(twiddle, tid);
+  for (int e = tid; e < NL * G * NSLOT; e += NT) stage[e] = (R)0;
+  lds_barrier();
   for (int f = 0; f < a.nfft; ++f) {
     const int slot = a.slot[f];
-    cplx<R> x[PER];
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {   // coalesced: consecutive threads, consecutive k
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) {
-        const int line = e / M, k = e % M;
-        x[p] = scr[f * plane + ((size_t)ix * G + iy0 + line) * M + k];
-      }
+    for (int e = tid; e < H * NL; e += NT) {   // coalesced: consecutive threads, consecutive k
+      const int line = e / H, k = e % H, m = k ? M - k : H;
+      const cplx<R> xk = scr[f * plane + line * M + k], xm = scr[f * plane + line * M + m];
+      buf[L::at(k, line)] = c2r_element(xk, k ? xm : cplx<R>{(R)0, (R)0}, twiddle[k]);
+      buf[L::at(m, line)] = c2r_element(xm, k ? xk : xm, twiddle[m]);
     }
-    __syncthreads();   // previous field's results have left buf
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) {
-        const int line = e / M, k = e % M;
-        buf[k * NL + line] = x[p];
-      }
-    }
-    __syncthreads();
-    // Z[k] = (X[k] + conj X[M-k]) + i e^{2 pi i k/G} (X[k] - conj X[M-k]), X[M] = 0
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) {
-        const int line = e / M, k = e % M;
-        cplx<R> xk = x[p];
-        cplx<R> xm = k ? buf[(M - k) * NL + line] : cplx<R>{(R)0, (R)0};
-        cplx<R> s = {xk.x + xm.x, xk.y - xm.y};          // X[k] + conj X[M-k]
-        cplx<R> d = {xk.x - xm.x, xk.y + xm.y};          // X[k] - conj X[M-k]
-        cplx<R> w = tw[k];                               // e^{-2 pi i k/G}
-        cplx<R> wd = cmulc(d, w);                        // d e^{+2 pi i k/G}
-        x[p] = {s.x - wd.y, s.y + wd.x};                 // s + i wd
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) {
-        const int line = e / M, k = e % M;
-        buf[k * NL + line] = x[p];
-      }
-    }
-    __syncthreads();
-    fft_lines<R, M, NL, NT, true, 2>(buf, tw);
-    for (int e = threadIdx.x; e < M * NL; e += NT) {
-      const int line = e / M, m = e % M;
-      cplx<R> z = buf[m * NL + line];
+    lds_barrier();
+    cplx<R> v[L::E];
+    L::first(v, tid, buf);
+    lds_barrier();
+    L::run(v, tid, buf, tw, [&](int dn, cplx<R> z) {
+      const int m = tid / NL + dn, line = tid % NL;
       stage[(line * G + 2 * m) * NSLOT + slot] = z.x;
       stage[(line * G + 2 * m + 1) * NSLOT + slot] = z.y;
-    }
+    });
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < NL * G; e += NT) {
+  lds_barrier();
+  for (int e = tid; e < NL * G; e += NT) {
     const int line = e / G, iz = e % G;
     const size_t cell = (size_t)mesh_x(ix, G) + mesh_y(iy0 + line, G) + mesh_z(iz);   // bricked layout
     store_cell<NSLOT, OT, R>(a.out, cell, &stage[e * NSLOT]);
@@ -374,44 +449,37 @@ __global__ void __launch_bounds__(256) k_zpass_c2r(GridBuildArgs a) {
 template <typename R, int G>
 __global__ void __launch_bounds__(256) k_zpass_r2c(PkArgs a) {
   using S = Shape<R, G>;
-  constexpr int NL = S::NL, NT = S::NT, M = S::M;
-  constexpr int PER = (M * NL + NT - 1) / NT;
+  constexpr int NL = S::NL, NT = S::NT, M = S::M, H = M / 2;
+  using L = Lines<R, M, NL, NT, false, 2, sizeof(R) == 4, true>;
   __shared__ cplx<R> buf[M * NL];
-  const int nyb = G / NL;
+  const int nyb = G / NL, tid = threadIdx.x;
   const int blk = blockIdx.x;
   const int h = blk / (G * nyb);
   const int ix = (blk / nyb) % G, iy0 = (blk % nyb) * NL;
-  const cplx<R>* __restrict__ tw = (const cplx<R>*)a.twiddle;
-  const cplx<R>* src = (const cplx<R>*)(h ? a.grid_b : a.grid_a);   // reals read in pairs
-  cplx<R>* dst = (cplx<R>*)a.scratch + (size_t)h * G * G * M;
-  for (int e = threadIdx.x; e < M * NL; e += NT) {
-    const int line = e / M, m = e % M;
-    buf[m * NL + line] = src[((size_t)ix * G + iy0 + line) * M + m];   // z[m] = x[2m] + i x[2m+1]
-  }
-  __syncthreads();
-  fft_lines<R, M, NL, NT, false, 2>(buf, tw);
+  const cplx<R>* __restrict__ twiddle = (const cplx<R>*)a.twiddle;
+  const size_t row0 = ((size_t)ix * G + iy0) * M;
+  const cplx<R>* src = (const cplx<R>*)(h ? a.grid_b : a.grid_a) + row0;   // reals read in pairs
+  cplx<R>* dst = (cplx<R>*)a.scratch + (size_t)h * G * G * M + row0;
+  for (int e = tid; e < M * NL; e += NT) buf[L::at(e % M, e / M)] = src[e];   // z[m] = x[2m] + i x[2m+1]
+  const typename L::Twiddles tw(twiddle, tid);
+  lds_barrier();
+  cplx<R> v[L::E];
+  L::first(v, tid, buf);
+  lds_barrier();
+  L::run(v, tid, buf, tw, [&](int dn, cplx<R> z) { buf[L::at(tid / NL + dn, tid % NL)] = z; });
+  lds_barrier();
   // X[k] = (Z[k] + conj Z[M-k])/2 - (i/2) e^{-2 pi i k/G} (Z[k] - conj Z[M-k]),  Z[M] = Z[0]
-  cplx<R> x[PER];
-#pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int e = threadIdx.x + p * NT;
-    if ((M * NL) % NT == 0 || e < M * NL) {
-      const int line = e / M, k = e % M;
-      cplx<R> zk = buf[k * NL + line];
-      cplx<R> zm = buf[((M - k) % M) * NL + line];
-      cplx<R> s = {zk.x + zm.x, zk.y - zm.y};
-      cplx<R> d = {zk.x - zm.x, zk.y + zm.y};
-      cplx<R> wd = cmul(d, tw[k]);                     // d e^{-2 pi i k/G}
-      x[p] = {(R)0.5 * (s.x + wd.y), (R)0.5 * (s.y - wd.x)};   // s/2 - (i/2) wd
-    }
-  }
-#pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int e = threadIdx.x + p * NT;
-    if ((M * NL) % NT == 0 || e < M * NL) {
-      const int line = e / M, k = e % M;
-      dst[((size_t)ix * G + iy0 + line) * M + k] = x[p];
-    }
+  auto element = [&](cplx<R> zk, cplx<R> zm, cplx<R> w) -> cplx<R> {
+    cplx<R> s = {zk.x + zm.x, zk.y - zm.y};
+    cplx<R> d = {zk.x - zm.x, zk.y + zm.y};
+    cplx<R> wd = cmul(d, w);                           // d e^{-2 pi i k/G}
+    return {(R)0.5 * (s.x + wd.y), (R)0.5 * (s.y - wd.x)};   // s/2 - (i/2) wd
+  };
+  for (int e = tid; e < H * NL; e += NT) {
+    const int line = e / H, k = e % H, m = k ? M - k : H;
+    const cplx<R> zk = buf[L::at(k, line)], zm = buf[L::at(m, line)];
+    dst[line * M + k] = element(zk, k ? zm : zk, twiddle[k]);
+    dst[line * M + m] = element(zm, k ? zk : zm, twiddle[m]);
   }
 }
 
@@ -420,45 +488,35 @@ __global__ void __launch_bounds__(256) k_zpass_r2c(PkArgs a) {
 // Momentum spectrum: Theta = sum_a i k_a J_a(k), one axis per call, summed
 // into planes 2 (and 3).
 template <typename R, int G>
-__global__ void __launch_bounds__(256) k_xpass_accum(PkArgs a) {
+__global__ void __launch_bounds__((Shape<R, G>::NTS)) k_xpass_accum(PkArgs a) {
   using S = Shape<R, G>;
-  constexpr int NB0 = S::NBC / 2 > 0 ? S::NBC / 2 : 1;
-  constexpr int NB = NB0, NT = S::NT, M = S::M;
-  __shared__ cplx<R> buf[G * NB];
-  const int nzb = M / NB;
-  const int halves = a.auto_mode ? 1 : 2;
+  constexpr int NB = S::NBC, M = S::M;
+  using L = Lines<R, G, NB, S::NTS, false, 1, true>;
+  __shared__ cplx<R> buf[L::kSize];
+  const int nzb = M / NB, tid = threadIdx.x;
   const int h = blockIdx.x / (G * nzb);
   const int blk = blockIdx.x % (G * nzb);
   const int iy = blk / nzb, iz0 = (blk % nzb) * NB;
-  const cplx<R>* __restrict__ tw = (const cplx<R>*)a.twiddle;
-  cplx<R>* scr = (cplx<R>*)a.scratch;
   const size_t plane = (size_t)G * G * M;
-  if (h >= halves) return;
-  for (int e = threadIdx.x; e < G * NB; e += NT) {
-    const int ix = e / NB, b = e % NB;
-    buf[ix * NB + b] = scr[h * plane + ((size_t)ix * G + iy) * M + iz0 + b];
-  }
-  __syncthreads();
-  fft_lines<R, G, NB, NT, false, 1>(buf, tw);
-  const int ny = signed_index(iy, G);
+  cplx<R>* const src = (cplx<R>*)a.scratch + h * plane + (size_t)iy * M + iz0;
+  const uint32_t at = (uint32_t)(tid / NB) * (G * M) + tid % NB;
+  cplx<R> v[L::E];
+  L::first(tid, [&](int dn, int i) { v[i] = (src + (size_t)dn * (G * M))[at]; });
+  const typename L::Twiddles tw((const cplx<R>*)a.twiddle, tid);
   if (a.deriv_axis < 0) {   // each block owns its columns: in place is safe
-    for (int e = threadIdx.x; e < G * NB; e += NT) {
-      const int ix = e / NB, b = e % NB;
-      scr[h * plane + ((size_t)ix * G + iy) * M + iz0 + b] = buf[ix * NB + b];
-    }
+    L::run(v, tid, buf, tw, [&](int dn, cplx<R> z) { (src + (size_t)dn * (G * M))[at] = z; });
     return;
   }
-  cplx<R>* acc = scr + (2 + h) * plane;
-  for (int e = threadIdx.x; e < G * NB; e += NT) {
-    const int ix = e / NB, b = e % NB;
-    const int n = a.deriv_axis == 0 ? signed_index(ix, G) : a.deriv_axis == 1 ? ny : iz0 + b;
-    const R kn = (R)(a.kf * (double)n);
-    const cplx<R> v = buf[ix * NB + b];
-    const cplx<R> t = {-kn * v.y, kn * v.x};          // i k_axis v
-    const size_t gi = ((size_t)ix * G + iy) * M + iz0 + b;
-    if (a.accum_first) acc[gi] = t;
-    else acc[gi] = {acc[gi].x + t.x, acc[gi].y + t.y};
-  }
+  cplx<R>* const acc = src + 2 * plane;
+  const int ny = signed_index(iy, G);
+  L::run(v, tid, buf, tw, [&](int dn, cplx<R> z) {
+    const int na = a.deriv_axis == 0 ? signed_index(tid / NB + dn, G) : a.deriv_axis == 1 ? ny : iz0 + tid % NB;
+    const R kn = (R)(a.kf * (double)na);
+    const cplx<R> t = {-kn * z.y, kn * z.x};          // i k_axis z
+    cplx<R>* const q = (acc + (size_t)dn * (G * M)) + at;
+    if (a.accum_first) *q = t;
+    else *q = {q->x + t.x, q->y + t.y};
+  });
 }
 
 // Log binning of planes bin_plane (and bin_plane + 1), laid out [kx][ky][kz]:
@@ -570,107 +628,105 @@ __global__ void k_bin_sums(PkArgs a) {
 
 // bfloat16 meshes: one block = 2 x-values by 4 y-lines (8 z-lines), so that
 // it writes whole halves of 4^3-cell bricks (32 cells of 2 NSLOT bytes: whole
-// 128-byte lines, one vector store per cell) instead of fragments of lines
-// shared with blocks on other XCDs.  Element e of a field's 8 lines is
-// (line e % 8, frequency e / 8) throughout, so that every LDS access of the
-// half-length transform's pre-processing is conflict-free; the results are
-// staged as bfloat16 pairs (the same rounding as the per-cell stores above)
-// in per-slot rows padded to spread the 8 lines over the banks.
+// 128-byte lines, vector stores per cell) instead of fragments of lines
+// shared with blocks on other XCDs.  M threads hold one field's 8 lines, 8
+// elements each (8 threads, 4 elements for M = 4), and F fields are transformed at a time, so that every thread
+// has a butterfly in the radix-8 stages; the next fields' lines are loaded
+// meanwhile.  The results are staged as bfloat16 pairs (the same rounding as
+// the per-cell stores above) in per-slot rows padded to spread the 8 lines
+// over the banks.  7 slots of 256^3 (0.74 GB): 298 us with a field at a time
+// (half of the threads idle in the radix-8 stages, nine barriers per field, and
+// reads of 8 lines per wave instead of 512 bytes of one), 165 us, the rate of a
+// copy.  6 slots of 512^3: 1.94 -> 1.34 ms.
 template <int NSLOT> struct CellWords;
 template <> struct CellWords<8> { using T = uint4; };
 template <> struct CellWords<6> { using T = uint3; };
 template <> struct CellWords<4> { using T = uint2; };
 
+template <int G> struct BfShape {
+  static constexpr int M = G / 2, NL = 8;
+  static constexpr int T = M < NL ? NL : M;                // threads per field
+  static constexpr int F0 = 256 / T;
+  static constexpr int F = F0 > 8 ? 8 : F0 < 2 ? 2 : F0;   // fields at a time
+  static constexpr int NT = T * F;
+};
+
 template <int G, int NSLOT>
-__global__ void __launch_bounds__(256) k_zpass_c2r_bf16(GridBuildArgs a) {
+__global__ void __launch_bounds__(BfShape<G>::NT) k_zpass_c2r_bf16(GridBuildArgs a) {
   using R = float;
-  constexpr int M = G / 2, NT = 256, NL = 8;
-  constexpr int PER = (M * NL + NT - 1) / NT;
+  using S = BfShape<G>;
+  constexpr int M = S::M, NL = S::NL, NT = S::NT, T = S::T, F = S::F, H = M / 2;
+  constexpr int PP = H * NL / T;                    // pairs (k, M - k) per thread
+  using L = Lines<R, M, NL, T, true, 2, true, true>;
   constexpr int SW = (G + 16) / 2;                  // 32-bit words per staged row (line, slot)
-  __shared__ cplx<R> buf[M * NL];
+  __shared__ cplx<R> lines[F * M * NL];
   __shared__ uint32_t stage[NSLOT * NL * SW];
   const int nyb = G / 4;
   const int ix0 = (blockIdx.x / nyb) * 2, iy0 = (blockIdx.x % nyb) * 4;
-  const cplx<R>* __restrict__ tw = (const cplx<R>*)a.twiddle;
-  const cplx<R>* scr = (const cplx<R>*)a.scratch;
+  const cplx<R>* __restrict__ twiddle = (const cplx<R>*)a.twiddle;
   const size_t plane = (size_t)G * G * M;
-  for (int e = threadIdx.x; e < NSLOT * NL * SW; e += NT) stage[e] = 0u;
-  // line l = 4 (x offset) + (y offset); the next field's lines are loaded
-  // while this field is transformed
-  auto load = [&](int f, cplx<R>* v) {
+  const int tf = threadIdx.x % T, f0 = threadIdx.x / T;
+  cplx<R>* const buf = lines + f0 * (M * NL);
+  // a thread's pairs (k, m): the same k in every T/H-th line; line
+  // l = 4 (x offset) + (y offset)
+  const int k = tf % H, m = k ? M - k : H;
+  const cplx<R> wk = twiddle[k], wm = twiddle[m];
+  const typename L::Twiddles tw(twiddle, tf);
+  const cplx<R>* const scr = (const cplx<R>*)a.scratch + ((size_t)ix0 * G + iy0) * M;
+  cplx<R> xk[PP], xm[PP];
+  auto load = [&](int f) {
+    if (f >= a.nfft) return;
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) {
-        const int line = e % NL, k = e / NL;
-        v[p] = scr[f * plane + ((size_t)(ix0 + (line >> 2)) * G + iy0 + (line & 3)) * M + k];
-      }
+    for (int p = 0; p < PP; ++p) {
+      const int line = tf / H + (T / H) * p;
+      const cplx<R>* const src = scr + f * plane + ((size_t)(line >> 2) * G + (line & 3)) * M;
+      xk[p] = src[k];
+      xm[p] = src[m];
     }
   };
-  cplx<R> xn[PER];
-  if (a.nfft > 0) load(0, xn);
-  for (int f = 0; f < a.nfft; ++f) {
-    const int slot = a.slot[f];
-    cplx<R> x[PER];
+  load(f0);
+  for (int e = threadIdx.x; e < NSLOT * NL * SW; e += NT) stage[e] = 0u;
+  lds_barrier();
+#pragma unroll 1
+  for (int fb = 0; fb < a.nfft; fb += F) {
+    const int f = fb + f0;
 #pragma unroll
-    for (int p = 0; p < PER; ++p) x[p] = xn[p];
-    if (f + 1 < a.nfft) load(f + 1, xn);
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) buf[e] = x[p];
+    for (int p = 0; p < PP; ++p) {
+      const int line = tf / H + (T / H) * p;
+      buf[L::at(k, line)] = c2r_element(xk[p], k ? xm[p] : cplx<R>{0.f, 0.f}, wk);
+      buf[L::at(m, line)] = c2r_element(xm[p], k ? xk[p] : xm[p], wm);
     }
-    __syncthreads();
-    // Z[k] = (X[k] + conj X[M-k]) + i e^{2 pi i k/G} (X[k] - conj X[M-k]), X[M] = 0
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) {
-        const int line = e % NL, k = e / NL;
-        cplx<R> xk = x[p];
-        cplx<R> xm = k ? buf[(M - k) * NL + line] : cplx<R>{(R)0, (R)0};
-        cplx<R> s = {xk.x + xm.x, xk.y - xm.y};
-        cplx<R> d = {xk.x - xm.x, xk.y + xm.y};
-        cplx<R> w = tw[k];
-        cplx<R> wd = cmulc(d, w);
-        x[p] = {s.x - wd.y, s.y + wd.x};
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int e = threadIdx.x + p * NT;
-      if ((M * NL) % NT == 0 || e < M * NL) buf[e] = x[p];
-    }
-    __syncthreads();
-    fft_lines<R, M, NL, NT, true, 2>(buf, tw);
-#pragma unroll 4
-    for (int e = threadIdx.x; e < M * NL; e += NT) {
-      const int line = e % NL, m = e / NL;
-      const cplx<R> z = buf[e];
-      stage[(slot * NL + line) * SW + m] = f32_to_bf16_bits(z.x) | (f32_to_bf16_bits(z.y) << 16);
-    }
-    __syncthreads();   // buf is rewritten by the next field
+    load(f + F);
+    lds_barrier();
+    cplx<R> v[L::E];
+    L::first(v, tf, buf);
+    lds_barrier();
+    const int slot = f < a.nfft ? a.slot[f] : -1;
+    L::run(v, tf, buf, tw, [&](int dn, cplx<R> z) {
+      if (slot >= 0) stage[(slot * NL + tf % NL) * SW + tf / NL + dn] = f32_to_bf16_bits(z.x) | (f32_to_bf16_bits(z.y) << 16);
+    });
   }
-  // brick j along z: cells base(j) + c, c = 16 dx + 4 dy + dz in [0, 32)
+  lds_barrier();
+  // brick j along z: cells base(j) + c, c = 16 dx + 4 dy + dz in [0, 32), two at a time
   using W = typename CellWords<NSLOT>::T;
-  const uint16_t* st = (const uint16_t*)stage;
   W* out = (W*)a.out;
   const size_t base0 = (size_t)mesh_x(ix0, G) + mesh_y(iy0, G);
 #pragma unroll 2
-  for (int t = threadIdx.x; t < (G / 4) * 32; t += NT) {
-    const int j = t >> 5, c = t & 31;
-    const int line = (c >> 4) * 4 + ((c >> 2) & 3), iz = 4 * j + (c & 3);
-    uint32_t wv[NSLOT / 2];
+  for (int t = threadIdx.x; t < (G / 4) * 16; t += NT) {
+    const int j = t >> 4, c = (t & 15) * 2;
+    const int line = (c >> 4) * 4 + ((c >> 2) & 3);
+    const uint32_t* const st = stage + line * SW + 2 * j + ((c & 3) >> 1);
+    uint32_t lo[NSLOT / 2], hi[NSLOT / 2];
 #pragma unroll
-    for (int q = 0; q < NSLOT / 2; ++q)
-      wv[q] = (uint32_t)st[2 * ((2 * q) * NL * SW + line * SW) + iz] |
-              ((uint32_t)st[2 * ((2 * q + 1) * NL * SW + line * SW) + iz] << 16);
-    W v;
-    if constexpr (NSLOT == 8) v = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-    else if constexpr (NSLOT == 6) v = make_uint3(wv[0], wv[1], wv[2]);
-    else v = make_uint2(wv[0], wv[1]);
-    out[base0 + mesh_z(4 * j) + c] = v;
+    for (int q = 0; q < NSLOT / 2; ++q) {
+      const uint32_t w0 = st[(2 * q) * NL * SW], w1 = st[(2 * q + 1) * NL * SW];
+      lo[q] = (w0 & 0xFFFFu) | (w1 << 16);
+      hi[q] = (w0 >> 16) | (w1 & 0xFFFF0000u);
+    }
+    W* const o = out + base0 + mesh_z(4 * j) + c;
+    if constexpr (NSLOT == 8) { o[0] = make_uint4(lo[0], lo[1], lo[2], lo[3]); o[1] = make_uint4(hi[0], hi[1], hi[2], hi[3]); }
+    else if constexpr (NSLOT == 6) { o[0] = make_uint3(lo[0], lo[1], lo[2]); o[1] = make_uint3(hi[0], hi[1], hi[2]); }
+    else { o[0] = make_uint2(lo[0], lo[1]); o[1] = make_uint2(hi[0], hi[1]); }
   }
 }
 
@@ -679,8 +735,8 @@ template <typename R, int G>
 void build_grids_g(const GridBuildArgs& a, hipStream_t s) {
   using S = Shape<R, G>;
   const int nzb = S::M / S::NBC;
-  hipLaunchKernelGGL((k_xpass_inverse<R, G>), dim3(G * (S::M / S::NBX)), dim3(S::NT), 0, s, a);
-  hipLaunchKernelGGL((k_ypass<R, G, true>), dim3(a.nfft * G * nzb), dim3(S::NT), 0, s,
+  hipLaunchKernelGGL((k_xpass_inverse<R, G>), dim3(G * nzb), dim3(S::NTX), 0, s, a);
+  hipLaunchKernelGGL((k_ypass<R, G, true>), dim3(a.nfft * G * nzb), dim3(S::NTS), 0, s,
                      (cplx<R>*)a.scratch, (const cplx<R>*)a.twiddle);
   const int nyb = G / S::NL;
   const dim3 zg(G * nyb);
@@ -688,9 +744,9 @@ void build_grids_g(const GridBuildArgs& a, hipStream_t s) {
     if constexpr (G <= 512) {   // the staged outputs of 8 lines fit in LDS
       if (a.out_type == GT_BF16) {
         const dim3 zb((G / 2) * (G / 4));
-        if (a.nslot == 8) hipLaunchKernelGGL((k_zpass_c2r_bf16<G, 8>), zb, dim3(S::NT), 0, s, a);
-        else if (a.nslot == 6) hipLaunchKernelGGL((k_zpass_c2r_bf16<G, 6>), zb, dim3(S::NT), 0, s, a);
-        else hipLaunchKernelGGL((k_zpass_c2r_bf16<G, 4>), zb, dim3(S::NT), 0, s, a);
+        if (a.nslot == 8) hipLaunchKernelGGL((k_zpass_c2r_bf16<G, 8>), zb, dim3(BfShape<G>::NT), 0, s, a);
+        else if (a.nslot == 6) hipLaunchKernelGGL((k_zpass_c2r_bf16<G, 6>), zb, dim3(BfShape<G>::NT), 0, s, a);
+        else hipLaunchKernelGGL((k_zpass_c2r_bf16<G, 4>), zb, dim3(BfShape<G>::NT), 0, s, a);
         return;
       }
     }
@@ -716,10 +772,9 @@ void power_spectrum_g(const PkArgs& a, hipStream_t s) {
   const int nyb = G / S::NL;
   hipLaunchKernelGGL((k_zpass_r2c<R, G>), dim3(halves * G * nyb), dim3(S::NT), 0, s, a);
   const int nzb = S::M / S::NBC;
-  hipLaunchKernelGGL((k_ypass<R, G, false>), dim3(halves * G * nzb), dim3(S::NT), 0, s,
+  hipLaunchKernelGGL((k_ypass<R, G, false>), dim3(halves * G * nzb), dim3(S::NTS), 0, s,
                      (cplx<R>*)a.scratch, (const cplx<R>*)a.twiddle);
-  constexpr int NBb = S::NBC / 2 > 0 ? S::NBC / 2 : 1;
-  hipLaunchKernelGGL((k_xpass_accum<R, G>), dim3(halves * G * (S::M / NBb)), dim3(S::NT), 0, s, a);
+  hipLaunchKernelGGL((k_xpass_accum<R, G>), dim3(halves * G * nzb), dim3(S::NTS), 0, s, a);
 }
 
 template <typename R, int G>

@@ -152,10 +152,6 @@ __global__ void __launch_bounds__(256) k_deposit_max(OutputArgs a) {
 // particle (8 waves per SIMD hide the binary64 weights' and the table's
 // latencies; a bigger table with one block per CU: 7.9 ms).
 
-// Workgroup barrier that orders LDS alone: the mesh atomics still in flight
-// need no order against it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <typename V, bool PRE, int NT, int R, int LOGS>
 __global__ void __launch_bounds__(NT, 4) k_deposit_lds(OutputArgs a) {
   constexpr uint32_t S = 1u << LOGS, kEmpty = 0xFFFFFFFFu;
