@@ -608,21 +608,33 @@ __global__ void __launch_bounds__(256) k_bin_fixed(PkArgs a) {
       if (h) atomicAdd(&a.acc[(2 + 2 * k) * nb + b], h);
     }
   }
-}
-
-// Exact sums -> [count][sum |k|][sum P] in binary64.
-__global__ void k_bin_sums(PkArgs a) {
-  const int nb = a.nbins;
-  int e2;
-  frexpf(__uint_as_float(*a.max_bits), &e2);
+  // the block that adds last turns the exact sums into binary64: bins gets
+  // [count][sum |k|][sum P], means [mean |k|][mean P][count] where it is asked
+  // for (NaN for an empty bin).  The sums are only ever touched by agent-scope
+  // atomics, which bypass the caches: they need no cache write-back (a release
+  // fence) before the ticket, only to have been carried out.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  __shared__ bool last;
+  if (threadIdx.x == 0) last = atomicAdd(a.ticket, 1u) == gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
   const double q = ldexp(1.0, e2 - 61);
+  auto sum = [&](int k) { return __hip_atomic_load(&a.acc[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-    const double nsum = ((double)a.acc[2 * nb + b] * 18446744073709551616.0 + (double)a.acc[nb + b]) / kNScale;
-    const double psum = ((double)(long long)a.acc[4 * nb + b] * 18446744073709551616.0 +
-                         (double)a.acc[3 * nb + b]) * q;
-    a.bins[b] = (double)a.acc[b];
-    a.bins[nb + b] = a.kf * nsum;
+    const double nsum = ((double)sum(2 * nb + b) * 18446744073709551616.0 + (double)sum(nb + b)) / kNScale;
+    const double psum = ((double)(long long)sum(4 * nb + b) * 18446744073709551616.0 +
+                         (double)sum(3 * nb + b)) * q;
+    const double cnt = (double)sum(b), ksum = a.kf * nsum;
+    a.bins[b] = cnt;
+    a.bins[nb + b] = ksum;
     a.bins[2 * nb + b] = psum;
+    if (a.means) {
+      const double nan = __longlong_as_double(0x7ff8000000000000LL);
+      a.means[b] = cnt > 0 ? ksum / cnt : nan;
+      a.means[nb + b] = cnt > 0 ? psum / cnt : nan;
+      a.means[2 * nb + b] = cnt;
+    }
   }
 }
 
@@ -783,7 +795,6 @@ void bin_g(const PkArgs& a, hipStream_t s) {
   const size_t blocks = std::min<size_t>((plane + 255) / 256, 2048);
   hipLaunchKernelGGL((k_bin_max<R, G>), dim3((unsigned)blocks), dim3(256), 0, s, a);
   hipLaunchKernelGGL((k_bin_fixed<R, G>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_bin_sums, dim3(1), dim3(256), 0, s, a);
 }
 
 template <typename R>

@@ -62,6 +62,12 @@ struct GridBuildArgs {
   void* out;               // [G^3][nslot] of out_type
 };
 
+struct FillArgs {
+  static constexpr int kBuffers = 3;
+  void* ptr[kBuffers];       // 16-byte aligned
+  size_t bytes[kBuffers];    // multiples of 16; 0: none
+};
+
 struct PkArgs {
   int32_t G;
   int32_t fp64;
@@ -75,8 +81,10 @@ struct PkArgs {
   double* bins;            // [3][nbins]: count, sum |k|, sum P, written by the binning
   unsigned long long* acc; // [5][nbins] exact bin sums: count, sum |n| (128-bit fixed point,
                            // lo and hi words), sum P (128-bit fixed point, lo and signed hi)
-                           // (zeroed by the caller, with *max_bits)
+                           // (zeroed by the caller, with *max_bits and *ticket)
   uint32_t* max_bits;      // binary32 bits of the largest |P| of a mode (the P quantum)
+  uint32_t* ticket;        // blocks of the binning that have added their sums
+  double* means;           // [3][nbins]: mean |k|, mean P, count; may be null
   double kf;
   int32_t deriv_axis;      // -1: transform the halves in place (planes 0, 1); 0-2: multiply by
                            // i k_axis and add into scratch planes 2 (and 3)
@@ -365,12 +373,17 @@ void launch_weights(const OutputArgs& a, hipStream_t s);
 void launch_deposit(const OutputArgs& a, hipStream_t s);
 void launch_deposit_max(const OutputArgs& a, hipStream_t s);   // FP32 form, before launch_deposit
 void launch_fixed_to_real(const FixedToRealArgs& a, hipStream_t s);
-void launch_bins_finalize(const double* bins, int nbins, double* out, hipStream_t s);
 void launch_power_spectrum(const PkArgs& a, hipStream_t s);
 void launch_bin(const PkArgs& a, hipStream_t s);   // bins planes bin_plane (and + 1) into a.bins
 void launch_read_state(const ReadStateArgs& a, hipStream_t s);
 void launch_store(const StoreArgs& a, hipStream_t s);
-void launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
+void launch_fill_zero(const FillArgs& a, hipStream_t s);   // every buffer in one launch
+inline void launch_fill_zero(void* ptr, size_t bytes, hipStream_t s) {
+  FillArgs a{};
+  a.ptr[0] = ptr;
+  a.bytes[0] = bytes;
+  launch_fill_zero(a, s);
+}
 void launch_sort(const SortArgs& a, hipStream_t s);        // rank pass, scan and move pass
 void launch_sort_move(const SortArgs& a, hipStream_t s);   // the move pass alone
 void launch_copy(const CopyArgs& a, hipStream_t s);

@@ -234,18 +234,6 @@ __global__ void k_fixed_to_real(FixedToRealArgs a) {
   }
 }
 
-// Bin sums [count][sum |k|][sum P] -> [mean |k|][mean P][count]; an empty
-// bin's means are NaN.
-__global__ void k_bins_finalize(const double* bins, int nbins, double* out) {
-  const double nan = __longlong_as_double(0x7ff8000000000000LL);
-  for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-    const double cnt = bins[b];
-    out[b] = cnt > 0 ? bins[nbins + b] / cnt : nan;
-    out[nbins + b] = cnt > 0 ? bins[2 * nbins + b] / cnt : nan;
-    out[2 * nbins + b] = cnt;
-  }
-}
-
 // Squared magnitudes of -eps grad psi, -(q^2/eps) grad phi, q (q . grad phi)/eps
 // and q phidot at the particle's CIC-interpolated mesh values, summed per
 // block in LDS and added to a.out.
@@ -331,10 +319,12 @@ __global__ void k_store(StoreArgs a) {
   for (int i = threadIdx.x; i < a.n; i += blockDim.x) a.dst[i] = a.w[i];
 }
 
-__global__ void k_fill_zero(uint4* p, size_t n16) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16;
-       i += (size_t)gridDim.x * blockDim.x)
-    p[i] = make_uint4(0, 0, 0, 0);
+__global__ void k_fill_zero(FillArgs a) {
+#pragma unroll
+  for (int b = 0; b < FillArgs::kBuffers; ++b)
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < a.bytes[b] / 16;
+         i += (size_t)gridDim.x * blockDim.x)
+      ((uint4*)a.ptr[b])[i] = make_uint4(0, 0, 0, 0);
 }
 
 int grid_for(size_t n, int block) {
@@ -354,12 +344,21 @@ void launch_force_terms(const TermArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_force_terms, dim3(std::min(grid_for((size_t)a.seg.n, 256), 4096)), dim3(256), 0, s, a);
 }
 
+template <typename V, int NT, int LOGS>
+void deposit_nt(const OutputArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)((a.seg.n + NT - 1) / NT));
+  if (a.pre_ic) hipLaunchKernelGGL((k_deposit_lds<V, true, NT, 1, LOGS>), grid, dim3(NT), 0, s, a);
+  else hipLaunchKernelGGL((k_deposit_lds<V, false, NT, 1, LOGS>), grid, dim3(NT), 0, s, a);
+}
+
+// Below half a block of 1024 per CU the deposit is as long as one block takes:
+// blocks of 256 use four times the CUs.  32 K particles: 23.8 us with 1024, 15.2
+// with 256 (binary64 28 and 22); 128 K: 16.8 and 17.0; 2 M (binary64): 261 and
+// 306; 16.7 M: 817 and 1135.
 template <typename V>
 void deposit(const OutputArgs& a, hipStream_t s) {
-  constexpr int NT = 1024, R = 1, LOGS = 10;
-  const dim3 grid((unsigned)((a.seg.n + NT * R - 1) / (NT * R)));
-  if (a.pre_ic) hipLaunchKernelGGL((k_deposit_lds<V, true, NT, R, LOGS>), grid, dim3(NT), 0, s, a);
-  else hipLaunchKernelGGL((k_deposit_lds<V, false, NT, R, LOGS>), grid, dim3(NT), 0, s, a);
+  if (a.seg.n < 128 * 1024) deposit_nt<V, 256, 9>(a, s);
+  else deposit_nt<V, 1024, 10>(a, s);
 }
 
 void launch_deposit(const OutputArgs& a, hipStream_t s) {
@@ -367,10 +366,6 @@ void launch_deposit(const OutputArgs& a, hipStream_t s) {
   // the empty key in 32 bits
   if (a.fp64) deposit<double>(a, s);
   else deposit<unsigned long long>(a, s);
-}
-
-void launch_bins_finalize(const double* bins, int nbins, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_bins_finalize, dim3(1), dim3(256), 0, s, bins, nbins, out);
 }
 
 void launch_deposit_max(const OutputArgs& a, hipStream_t s) {
@@ -391,12 +386,12 @@ void launch_store(const StoreArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_store, dim3(1), dim3(128), 0, s, a);
 }
 
-// Zero a 16-byte aligned buffer whose size is a multiple of 16 with a plain
+// Zero 16-byte aligned buffers whose sizes are multiples of 16 with a plain
 // kernel (no memset node, so the work may be captured in a graph).
-void launch_fill_zero(void* ptr, size_t bytes, hipStream_t s) {
-  const size_t n16 = bytes / 16;
-  if (!n16) return;
-  hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(n16, 256)), dim3(256), 0, s, (uint4*)ptr, n16);
+void launch_fill_zero(const FillArgs& a, hipStream_t s) {
+  size_t most = 0;
+  for (size_t b : a.bytes) most = std::max(most, b);
+  hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(most / 16, 256)), dim3(256), 0, s, a);
 }
 
 }  // namespace fdf

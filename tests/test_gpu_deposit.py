@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("mode", ["cross", "auto"])
-@pytest.mark.parametrize("n", [2, 1023, 1024, 1025, 6001])
+@pytest.mark.parametrize("n", [2, 255, 257, 1023, 1024, 1025, 6001, 131071, 131073])
 @pytest.mark.parametrize("prec,grid_n", [("fp64", 8), ("fp64", 64), ("fp32", 8), ("fp32", 64)])
 def test_density_matches_oracle_deposit(prec, grid_n, n, mode):
     cfg = workloads.small("c3", grid_n=grid_n, n_side=1, n_steps=6, precision=prec, box_mpc=600.0, z_begin=60.0,
