@@ -171,6 +171,10 @@ inline int64_t batch_grid(const SpeciesBatch& sb) {
   return 8 * most;
 }
 
+// A launch holds fewer than 2^32 threads: kernels of one particle per thread
+// loop over a grid of at most this many, or are launched again for the rest.
+constexpr int64_t kMaxGridThreads = (int64_t)1 << 31;
+
 // Threads per block of a plain push.  The wide block (CIC, separable form) is
 // for launches of several steps.
 constexpr int kPushBlock = 256, kPushWideBlock = 1024;
@@ -320,6 +324,7 @@ struct PreIcArgs {
 
 struct OutputArgs {
   Segment seg;
+  int64_t first;           // first particle of a deposit launch
   int32_t fp64;
   int32_t G;
   int32_t pre_ic;          // p regenerated from (seed, id) instead of q0

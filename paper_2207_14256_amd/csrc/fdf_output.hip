@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(NT, 4) k_deposit_lds(OutputArgs a) {
     if constexpr (kFixed) atomicAdd(d, v);
     else unsafeAtomicAdd(d, v);
   };
-  const int64_t i0 = (int64_t)blockIdx.x * (NT * R) + threadIdx.x;
+  const int64_t i0 = a.first + (int64_t)blockIdx.x * (NT * R) + threadIdx.x;
 #pragma unroll 1
   for (int r = 0; r < R; ++r) {
     const int64_t i = i0 + r * NT;
@@ -346,9 +346,12 @@ void launch_force_terms(const TermArgs& a, hipStream_t s) {
 
 template <typename V, int NT, int LOGS>
 void deposit_nt(const OutputArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)((a.seg.n + NT - 1) / NT));
-  if (a.pre_ic) hipLaunchKernelGGL((k_deposit_lds<V, true, NT, 1, LOGS>), grid, dim3(NT), 0, s, a);
-  else hipLaunchKernelGGL((k_deposit_lds<V, false, NT, 1, LOGS>), grid, dim3(NT), 0, s, a);
+  OutputArgs p = a;
+  for (p.first = 0; p.first < a.seg.n; p.first += kMaxGridThreads) {
+    const dim3 grid((unsigned)((std::min(a.seg.n - p.first, kMaxGridThreads) + NT - 1) / NT));
+    if (a.pre_ic) hipLaunchKernelGGL((k_deposit_lds<V, true, NT, 1, LOGS>), grid, dim3(NT), 0, s, p);
+    else hipLaunchKernelGGL((k_deposit_lds<V, false, NT, 1, LOGS>), grid, dim3(NT), 0, s, p);
+  }
 }
 
 // Below half a block of 1024 per CU the deposit is as long as one block takes:

@@ -552,7 +552,7 @@ struct PushLaunch {
   dim3 grid;
   bool off32;
   explicit PushLaunch(const PushArgs& a)
-      : grid((unsigned)(a.persistent ? a.persistent : a.grid_blocks)),
+      : grid((unsigned)(a.persistent ? a.persistent : std::min(a.grid_blocks, kMaxGridThreads / a.block))),
         off32((uint64_t)a.G * a.G * a.G * (uint64_t)(a.nslot * (a.fp64 ? 8 : 2)) <= (1ull << 32)) {}
 };
 

@@ -293,7 +293,7 @@ __global__ void __launch_bounds__(kBlock) k_push_eom_f64(PushArgs a) {
 
 template <bool BLEND, bool TSC>
 void eom_launch(const PushArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)(a.persistent ? a.persistent : a.grid_blocks)), block(kBlock);
+  const dim3 grid((unsigned)(a.persistent ? a.persistent : std::min(a.grid_blocks, kMaxGridThreads / kBlock))), block(kBlock);
   if (a.fp64) {
     if (a.nslot == 8) hipLaunchKernelGGL((k_push_eom_f64<8, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
     else hipLaunchKernelGGL((k_push_eom_f64<4, BLEND, TSC>), grid, block, a.lds_reserve, s, a);
