@@ -1142,7 +1142,7 @@ bool place_species(fdf_ctx* c, SpeciesRec& s) {
     a.count = (uint32_t*)(c->ws + c->lay.sort_count);
     a.scan_scratch = (uint32_t*)(c->ws + c->lay.sort_scan);
     a.key = (uint32_t*)(c->ws + c->lay.sort_bucket);
-    a.rank = (uint32_t*)(c->ws + c->lay.sort_rank);
+    a.binned = (uint32_t*)(c->ws + c->lay.sort_rank);
   } else {
     // the FFT scratch and the density halves behind it
     const size_t count = align_up((size_t)a.nkeys * 4), scan = align_up(sort_scan_scratch_words(a.nkeys) * 4);
@@ -1152,7 +1152,7 @@ bool place_species(fdf_ctx* c, SpeciesRec& s) {
     a.count = (uint32_t*)p;
     a.scan_scratch = (uint32_t*)(p + count);
     a.key = (uint32_t*)(p + count + scan);
-    a.rank = (uint32_t*)(p + count + scan + list);
+    a.binned = (uint32_t*)(p + count + scan + list);
   }
   launch_place_species(a, c->stream);
   return true;

@@ -58,26 +58,110 @@ __global__ void k_field_gen(FieldGenArgs a) {
 // Spatial order at creation.  Sampling is a function of seed and id, so the
 // ids alone are ordered, by a counting sort over the tiles of the sampled
 // positions, before any state is written: no particle is moved.  The positions
-// are random, so every atomic and every id write goes to a line of its own,
-// which bounds both passes (134 M particles on 512^3: 6.9 ms, 19 G atomics/s,
-// and 4.7 ms; sampling first and moving the ids of a first sort took 6.1 ms
-// more).
-__global__ void __launch_bounds__(256) k_place_count(PlaceArgs a) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.seg.n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const u64x4 wp = philox4x64((uint64_t)i, 0, 0, 0, a.seed, kStreamPosition);
-    uint32_t c[3];
-    for (int d = 0; d < 3; ++d) c[d] = (uint32_t)(wp.v[d] >> 32) >> a.cell_shift;
-    const uint32_t k = sort_key::morton_key(c, a.fine_bits) >> (3 * a.fine_bits);
-    a.key[i] = k;
-    a.rank[i] = atomicAdd(&a.count[k], 1u);
-  }
+// are random, so a counting sort over all tiles at once sends every atomic and
+// every id to a memory transaction of its own (134 M particles on 512^3: 6.9 ms
+// for the ranks, 4.7 ms for the ids).  Two levels instead: the ids go to bins
+// of consecutive tiles first, a block's share of a bin together, and each bin is
+// then ordered by one block with its tile counts in LDS.
+// 134 M particles on 512^3: 1.15 ms (tiles and counts), 0.94 (to the bins), 2.47
+// (the bins), 4.6 ms for 11.6; 16.7 M on 256^3: 0.45 ms for 1.35.
+constexpr int kPlaceThreads = 1024;
+constexpr int kPlaceIds = 16384;         // ids of a scatter block, at most
+constexpr int kPlaceBins = 4096;         // bins, at most
+constexpr int kPlaceTiles = 16384;       // tiles of a bin, at most
+
+__device__ __forceinline__ uint32_t place_key(const PlaceArgs& a, uint64_t id) {
+  const u64x4 wp = philox4x64(id, 0, 0, 0, a.seed, kStreamPosition);
+  uint32_t c[3];
+  for (int d = 0; d < 3; ++d) c[d] = (uint32_t)(wp.v[d] >> 32) >> a.cell_shift;
+  return sort_key::morton_key(c, a.fine_bits) >> (3 * a.fine_bits);
 }
 
-__global__ void __launch_bounds__(256) k_place_ids(PlaceArgs a) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.seg.n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    a.seg.id[(size_t)a.count[a.key[i]] + a.rank[i]] = (uint32_t)i;
+// In-place exclusive scan of v[0, n), n a multiple of 1024 or less than it, by
+// a block of 1024 threads.
+__device__ __forceinline__ void block_scan(uint32_t* v, int n) {
+  __shared__ uint32_t wave[kPlaceThreads / 64];
+  const int per = n > kPlaceThreads ? n / kPlaceThreads : 1, first = (int)threadIdx.x * per;
+  uint32_t sum = 0;
+  for (int k = 0; k < per && first + k < n; ++k) sum += v[first + k];
+  uint32_t x = sum;   // inclusive over the wave
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(x, off);
+    if ((threadIdx.x & 63) >= (unsigned)off) x += y;
+  }
+  if ((threadIdx.x & 63) == 63) wave[threadIdx.x >> 6] = x;
+  lds_barrier();
+  uint32_t base = x - sum;
+  for (unsigned w = 0; w < threadIdx.x >> 6; ++w) base += wave[w];
+  for (int k = 0; k < per && first + k < n; ++k) {
+    const uint32_t c = v[first + k];
+    v[first + k] = base;
+    base += c;
+  }
+  lds_barrier();
+}
+
+// Tile of every id, and the number of ids of each bin.
+__global__ void __launch_bounds__(kPlaceThreads) k_place_count(PlaceArgs a) {
+  __shared__ uint32_t count[kPlaceBins];
+  for (int b = threadIdx.x; b < a.nbins; b += kPlaceThreads) count[b] = 0;
+  lds_barrier();
+  for (int64_t i = blockIdx.x * (int64_t)kPlaceThreads + threadIdx.x; i < a.seg.n;
+       i += (int64_t)gridDim.x * kPlaceThreads) {
+    const uint32_t k = place_key(a, (uint64_t)i);
+    a.key[i] = k;
+    atomicAdd(&count[k >> a.tile_bits], 1u);
+  }
+  lds_barrier();
+  for (int b = threadIdx.x; b < a.nbins; b += kPlaceThreads)
+    if (count[b]) atomicAdd(&a.count[b], count[b]);
+}
+
+// Ids to their bins: a block orders its ids by bin in LDS and reserves a range
+// of every bin (a.count: the bins' starts, advanced to their ends).
+__global__ void __launch_bounds__(kPlaceThreads) k_place_scatter(PlaceArgs a) {
+  __shared__ uint32_t ids[kPlaceIds];
+  __shared__ uint16_t bin[kPlaceIds];
+  __shared__ uint32_t next[kPlaceBins];    // slot of the bin's next id
+  __shared__ uint32_t shift[kPlaceBins];   // from the slot to the place in the bin
+  const int64_t first = blockIdx.x * (int64_t)a.block_ids;
+  const int n = (int)(a.seg.n - first < a.block_ids ? a.seg.n - first : a.block_ids);
+  for (int b = threadIdx.x; b < a.nbins; b += kPlaceThreads) next[b] = 0;
+  lds_barrier();
+  for (int i = threadIdx.x; i < n; i += kPlaceThreads) atomicAdd(&next[a.key[first + i] >> a.tile_bits], 1u);
+  lds_barrier();
+  for (int b = threadIdx.x; b < a.nbins; b += kPlaceThreads)
+    if (next[b]) shift[b] = atomicAdd(&a.count[b], next[b]);
+  lds_barrier();
+  block_scan(next, a.nbins);
+  for (int b = threadIdx.x; b < a.nbins; b += kPlaceThreads) shift[b] -= next[b];
+  lds_barrier();
+  for (int i = threadIdx.x; i < n; i += kPlaceThreads) {
+    const uint32_t b = a.key[first + i] >> a.tile_bits, s = atomicAdd(&next[b], 1u);
+    ids[s] = (uint32_t)(first + i);
+    bin[s] = (uint16_t)b;
+  }
+  lds_barrier();
+  for (int s = threadIdx.x; s < n; s += kPlaceThreads) a.binned[(uint32_t)(shift[bin[s]] + s)] = ids[s];
+}
+
+// One block per bin: its ids in the order of their tiles.
+__global__ void __launch_bounds__(kPlaceThreads) k_place_ids(PlaceArgs a) {
+  __shared__ uint32_t next[kPlaceTiles];
+  const int tiles = 1 << a.tile_bits;
+  const int64_t start = blockIdx.x ? a.count[blockIdx.x - 1] : 0;
+  const int64_t end = (int)blockIdx.x == a.nbins - 1 ? a.seg.n : (int64_t)a.count[blockIdx.x];
+  for (int t = threadIdx.x; t < tiles; t += kPlaceThreads) next[t] = 0;
+  lds_barrier();
+  for (int64_t i = start + threadIdx.x; i < end; i += kPlaceThreads) {
+    const uint32_t t = place_key(a, a.binned[i]) & (tiles - 1);
+    a.key[i] = t;
+    atomicAdd(&next[t], 1u);
+  }
+  lds_barrier();
+  block_scan(next, tiles);
+  for (int64_t i = start + threadIdx.x; i < end; i += kPlaceThreads)
+    a.seg.id[start + atomicAdd(&next[a.key[i]], 1u)] = a.binned[i];
 }
 
 // Particle sample: uniform positions on the 2^-32 L lattice, |q| from
@@ -175,11 +259,27 @@ void launch_sample_species(const SampleArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_sample, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
 }
 
-void launch_place_species(const PlaceArgs& a, hipStream_t s) {
-  launch_fill_zero(a.count, ((size_t)a.nkeys * 4 + 15) / 16 * 16, s);
-  hipLaunchKernelGGL(k_place_count, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
-  launch_scan_exclusive(a.count, a.nkeys, a.scan_scratch, s);
-  hipLaunchKernelGGL(k_place_ids, dim3(grid_for((size_t)a.seg.n, 256)), dim3(256), 0, s, a);
+void launch_place_species(const PlaceArgs& args, hipStream_t s) {
+  PlaceArgs a = args;
+  // Bins of no more tiles than a block counts and of about 4096 ids, fewer where
+  // that leaves CUs without a bin (32 K ids: 17 us in bins of 4096, 6 in
+  // bins of 512).
+  int bins = (int)std::max<int64_t>(1, a.nkeys / kPlaceTiles);
+  const int64_t per = std::min<int64_t>(4096, std::max<int64_t>(512, a.seg.n / 256));
+  while (bins < kPlaceBins && bins < a.nkeys && bins * per < a.seg.n) bins *= 2;
+  a.nbins = bins;
+  a.tile_bits = 0;
+  while (((int64_t)bins << a.tile_bits) < a.nkeys) ++a.tile_bits;
+  // a block per CU at least
+  const int64_t share = (a.seg.n / 256 + kPlaceThreads - 1) / kPlaceThreads * kPlaceThreads;
+  a.block_ids = (int32_t)std::min<int64_t>(kPlaceIds, std::max<int64_t>(share, kPlaceThreads));
+  launch_fill_zero(a.count, ((size_t)bins * 4 + 15) / 16 * 16, s);
+  const int64_t blocks = (a.seg.n + kPlaceThreads - 1) / kPlaceThreads;
+  hipLaunchKernelGGL(k_place_count, dim3((unsigned)std::min<int64_t>(blocks, 512)), dim3(kPlaceThreads), 0, s, a);
+  launch_scan_exclusive(a.count, bins, a.scan_scratch, s);
+  hipLaunchKernelGGL(k_place_scatter, dim3((unsigned)((a.seg.n + a.block_ids - 1) / a.block_ids)), dim3(kPlaceThreads),
+                     0, s, a);
+  hipLaunchKernelGGL(k_place_ids, dim3((unsigned)bins), dim3(kPlaceThreads), 0, s, a);
 }
 
 void launch_pre_ic(const PreIcArgs& a, hipStream_t s) {

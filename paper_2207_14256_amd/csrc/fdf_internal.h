@@ -299,10 +299,14 @@ struct PlaceArgs {
   int32_t cell_shift;      // 32 - log2(G)
   int32_t fine_bits;       // log2 of the tile side in cells
   int64_t nkeys;           // number of tiles
-  uint32_t* count;         // [nkeys]
+  uint32_t* count;         // [nkeys] (one per bin is used)
   uint32_t* scan_scratch;  // sort_scan_scratch_words(nkeys) words
-  uint32_t* key;           // [n]
-  uint32_t* rank;          // [n]
+  uint32_t* key;           // [n] tiles
+  uint32_t* binned;        // [n] ids by bin
+  // set by the launch
+  int32_t nbins;           // bins of 2^tile_bits consecutive tiles
+  int32_t tile_bits;
+  int32_t block_ids;       // ids of a scatter block
 };
 
 struct FieldGenArgs {
