@@ -166,8 +166,9 @@ typedef struct fdf_info {
 /* Launch and sort parameters (picked by the autotuner or set by hand).  None
  * changes results: the push is per particle and the sort only permutes. */
 typedef struct fdf_tuning {
-  int32_t particles_per_thread;  /* FP32 separable push: at most 1, 2, 4 or 8 (fewer
-                                    when too few particles to fill the chip) */
+  int32_t particles_per_thread;  /* FP32 separable push of one step: at most 1, 2, 4
+                                    or 8 (fewer when too few particles to fill the
+                                    chip); pushes of several steps take 1 */
   int32_t sort_tiles;            /* sort buckets per axis: a power of two <= min(G, 256);
                                     particles are ordered by the Morton index of
                                     their bucket, then of their cell inside it;
@@ -194,8 +195,8 @@ typedef struct fdf_tuning {
                                     sorted order (no separate move pass; results
                                     bit-identical; the default); 0: rank + move
                                     passes, then the push */
-  int32_t push_waves;            /* plain push launch (not one that carries out a
-                                    re-sort): at most this many resident waves per
+  int32_t push_waves;            /* plain push launch of one step (not one that
+                                    carries out a re-sort): at most this many resident waves per
                                     SIMD (2-8; enforced by reserving LDS per block),
                                     fewer waves keeping more of each block's mesh
                                     neighbourhood in cache; 0: as many as the
@@ -203,7 +204,8 @@ typedef struct fdf_tuning {
   int32_t sort_push_ppt;         /* one-step push that carries out a re-sort:
                                     particles per thread (1, 2 or 4; 0 selects 4)
                                     of its 1024-particle blocks (pushes of
-                                    several steps take 4) */
+                                    several steps take 1, or 2 on meshes with
+                                    less than one particle in two cells) */
   int32_t sort_keys_push;        /* 1 (the default): FP32 separable form -- a push
                                     that is followed by a re-sorting push in the
                                     same fdf_step call also writes the particles'

@@ -2,7 +2,7 @@
 //
 // Inverse direction (grid build, sec. 2.1 "potential grids"): delta_0(k) is
 // multiplied by the transfer functions and i k_a, then transformed by three
-// LDS-resident passes:
+// passes, in registers with LDS between the stages:
 //   X pass  : strided C2C along x, fused with the Fourier-stage multipliers;
 //             one block = NB consecutive z-columns of one y row, all x;
 //   Y pass  : strided C2C along y, in place;
