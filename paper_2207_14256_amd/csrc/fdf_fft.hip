@@ -642,10 +642,11 @@ __global__ void __launch_bounds__(256) k_bin_fixed(PkArgs a) {
 // it writes whole halves of 4^3-cell bricks (32 cells of 2 NSLOT bytes: whole
 // 128-byte lines, vector stores per cell) instead of fragments of lines
 // shared with blocks on other XCDs.  M threads hold one field's 8 lines, 8
-// elements each (8 threads, 4 elements for M = 4), and F fields are transformed at a time, so that every thread
-// has a butterfly in the radix-8 stages; the next fields' lines are loaded
-// meanwhile.  The results are staged as bfloat16 pairs (the same rounding as
-// the per-cell stores above) in per-slot rows padded to spread the 8 lines
+// elements each (8 threads, 4 elements for M = 4), and F fields are transformed
+// at a time, so that every thread has a butterfly in the radix-8 stages; the
+// next fields' lines are loaded meanwhile.  The results are staged as bfloat16
+// pairs (the same rounding as the per-cell stores above) in per-slot rows
+// padded to spread the 8 lines
 // over the banks.  7 slots of 256^3 (0.74 GB): 298 us with a field at a time
 // (half of the threads idle in the radix-8 stages, nine barriers per field, and
 // reads of 8 lines per wave instead of 512 bytes of one), 165 us, the rate of a
