@@ -560,6 +560,7 @@ int upload_segments(fdf_ctx* c) {
         g.grid = c->fields[s.field].grid;
         g.grid2 = c->fields[s.field].grid2;
         g.m = s.m;
+        g.seed = s.seed;
         std::memcpy((char*)st.w + k * sizeof(Segment), &g, sizeof(g));
       }
       st.dst = (uint64_t*)(c->ws + c->lay.seg + copy * table + i * sizeof(Segment));
@@ -628,13 +629,14 @@ size_t density_copy_offset(const fdf_ctx* c) {
   return 4 * (G * G * (G / 2)) * 8;
 }
 
-// Sampling of a species by the ids its segment g holds.
+// Sampling of a species by the ids its segment g holds, within a step: the seed
+// comes from the segment table, which is stored before every step.
 SampleArgs resample_args(fdf_ctx* c, const SpeciesRec& s, const Segment& g) {
   SampleArgs sa{};
   sa.seg = g;
   sa.fp64 = c->cfg.precision == FDF_PREC_FP64;
   sa.by_id = 1;
-  sa.seed = s.seed;
+  sa.seed_at = &((const Segment*)(c->ws + c->lay.seg))[&s - c->species.data()].seed;
   sa.box = c->cfg.box_mpc;
   sa.t_nu = t_nu_ev();
   return sa;

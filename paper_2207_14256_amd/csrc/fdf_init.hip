@@ -170,14 +170,15 @@ __global__ void __launch_bounds__(kPlaceThreads) k_place_ids(PlaceArgs a) {
 __global__ void k_sample(SampleArgs a) {
   const int64_t n = a.seg.n;
   const double T = a.t_nu;
+  const uint64_t seed = a.seed_at ? *a.seed_at : a.seed;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const uint64_t id = a.by_id ? (uint64_t)a.seg.id[i] : (uint64_t)i;
-    const u64x4 wp = philox4x64(id, 0, 0, 0, a.seed, kStreamPosition);
+    const u64x4 wp = philox4x64(id, 0, 0, 0, seed, kStreamPosition);
     uint32_t xu[3];
     for (int d = 0; d < 3; ++d) xu[d] = (uint32_t)(wp.v[d] >> 32);
     float qf[3];
-    sample_momentum(a.seed, id, T, qf);
+    sample_momentum(seed, id, T, qf);
     if (a.fp64) {
       const double scale = a.box * 0x1p-32;
       for (int d = 0; d < 3; ++d) {

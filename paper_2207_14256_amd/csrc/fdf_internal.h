@@ -108,6 +108,7 @@ struct Segment {
   const void* grid2;       // second grid set (super-steps), or null
   double m;                // mass [eV]
   int64_t n;               // particles
+  uint64_t seed;           // of the sample (device table)
 };
 
 // Particles per block of the sort's rank pass.
@@ -287,6 +288,8 @@ struct SampleArgs {
   int32_t fp64;
   int32_t by_id;           // 1: slot i takes the particle seg.id[i] (ids kept); 0: slot i is id i
   uint64_t seed;
+  const uint64_t* seed_at; // not null: the seed is read from here.  A captured launch is replayed on
+                           // species of other seeds, so no argument of a step holds one
   double box;
   double t_nu;             // k_B T [eV]
 };

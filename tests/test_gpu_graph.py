@@ -1,0 +1,35 @@
+"""Captured step sequences: a replay must do what the same call does without
+the capture, on whatever the context holds by then."""
+import numpy as np
+import pytest
+
+from paper_2207_14256_amd import fastdf, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _job(ctx, cfg, seeds):
+    """Reset, fields, species of these seeds, 12 steps: every state and weight."""
+    ctx.reset()
+    fields = [ctx.add_field(s) for s in cfg["fields"]]
+    species = [ctx.init_species(fields[0], sp["m"], sp["n"], seed) for sp, seed in zip(cfg["species"], seeds)]
+    ctx.step(12)
+    return [v for s in species for v in ctx.read_state(s)] + [ctx.weights(s).cpu().numpy() for s in species]
+
+
+@pytest.mark.parametrize("sort_every", [0, 5])
+@pytest.mark.parametrize("prec,grid_n", [("fp64", 64), ("fp32", 128)])
+def test_replay_with_other_seeds(prec, grid_n, sort_every):
+    """A mesh above 4 MiB whose first interval drifts more than 3 cells: the
+    untouched species is re-ordered, and sampled again, by the captured steps.
+    The seeds differ in their low or in their high words."""
+    cfg = workloads.small("c3", grid_n=grid_n, n_side=1, n_steps=12, precision=prec, box_mpc=6.25 * grid_n, z_begin=300.0,
+                          z_end=40.0, sort_every=sort_every, sort_cells=0.0)
+    cfg["species"] = [dict(field=0, m=0.05, n=20011, n_side=1), dict(field=0, m=0.02, n=3001, n_side=1)]
+    plain, graph = fastdf.Context(cfg), fastdf.Context(cfg)
+    graph.set_tuning(use_graph=1)
+    for seeds in ((31, 1 << 60), (32, 1 << 60), (31, (1 << 60) + 1), (31 + (1 << 40), 1 << 60), (31, 1 << 60)):
+        for a, b in zip(_job(graph, cfg, seeds), _job(plain, cfg, seeds)):
+            assert np.array_equal(a, b), seeds
+    plain.close()
+    graph.close()
