@@ -319,6 +319,7 @@ struct GraphRec {
   int n = 0;
   std::vector<double> layout;      // fields and species that fix every device pointer
   HostStepState before, after;
+  bool builds_grids = false;       // overwrites the FFT scratch and with it the last density
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -1660,6 +1661,7 @@ int step_graph(fdf_ctx* c, int32_t n) {
     if (g.n == n && g.before == before && g.layout == layout) {
       int rc = hip_check(c, hipGraphLaunch(g.exec, c->stream), "graph launch");
       if (!rc) apply_state(c, g.after);
+      if (!rc && g.builds_grids) c->have_density = false;
       return rc;
     }
   }
@@ -1675,7 +1677,11 @@ int step_graph(fdf_ctx* c, int32_t n) {
   int rc = hip_check(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal), "begin capture");
   if (rc) return rc;
   c->launch_stream = c->cap_stream;
+  const bool density = c->have_density;
+  c->have_density = true;   // a grid build clears it
   const int rc_enq = enqueue_steps(c, n);
+  g.builds_grids = !c->have_density;
+  c->have_density = density && !g.builds_grids;
   c->launch_stream = nullptr;
   rc = hip_check(c, hipStreamEndCapture(c->cap_stream, &g.graph), "end capture");
   if (rc_enq || rc) {

@@ -33,3 +33,35 @@ def test_replay_with_other_seeds(prec, grid_n, sort_every):
             assert np.array_equal(a, b), seeds
     plain.close()
     graph.close()
+
+
+@pytest.mark.parametrize("tol", [0.0, 0.01])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_density_after_replayed_grid_builds(prec, tol):
+    """A step that builds meshes overwrites the last density's buffers: it
+    cannot be read afterwards, whether the step was enqueued, captured or
+    replayed.  A step that builds none leaves it as it was."""
+    cfg = workloads.small("c3", grid_n=16, n_side=9, n_steps=40, precision=prec, box_mpc=400.0, z_begin=1e5,
+                          z_end=500.0, sort_every=0, sort_cells=0.0, model="radmat", omega_r=1e-4, superstep_tol=tol)
+    ctx = fastdf.Context(cfg)
+    ctx.set_tuning(use_graph=1)
+    for _ in range(3):   # captured, then replayed
+        _, _, species = fastdf.setup_workload(cfg, ctx=ctx, tuning=dict())
+        ctx.step(20)
+        ctx.power_spectrum(species, 4)
+        ctx.read_density(0)
+        ctx.step(20)
+        with pytest.raises(fastdf.FastDFError):
+            ctx.read_density(0)
+    ctx.close()
+    cfg = dict(cfg, model="poisson", omega_r=0.0, superstep_tol=0.0)
+    ctx = fastdf.Context(cfg)
+    ctx.set_tuning(use_graph=1)
+    for _ in range(3):
+        _, _, species = fastdf.setup_workload(cfg, ctx=ctx, tuning=dict())
+        ctx.step(20)
+        ctx.power_spectrum(species, 4)
+        before = ctx.read_density(0)
+        ctx.step(20)
+        assert np.array_equal(ctx.read_density(0), before)
+    ctx.close()
