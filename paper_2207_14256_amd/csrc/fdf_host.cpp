@@ -1287,6 +1287,7 @@ int fdf_attach_workspace(fdf_ctx* c, void* dptr, size_t bytes) {
   if (!c) return FDF_ERR_ARG;
   if (!dptr || ((uintptr_t)dptr % kAlign) != 0) return fail(c, FDF_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   if (bytes < c->lay.total) return fail(c, FDF_ERR_WORKSPACE, "workspace too small");
+  clear_graphs(c);   // captured launches hold addresses of the workspace before
   c->ws = (char*)dptr;
   c->ws_bytes = bytes;
   fill_twiddles(c);

@@ -1,7 +1,10 @@
 """Captured step sequences: a replay must do what the same call does without
 the capture, on whatever the context holds by then."""
+import ctypes
+
 import numpy as np
 import pytest
+import torch
 
 from paper_2207_14256_amd import fastdf, workloads
 
@@ -64,4 +67,23 @@ def test_density_after_replayed_grid_builds(prec, tol):
         before = ctx.read_density(0)
         ctx.step(20)
         assert np.array_equal(ctx.read_density(0), before)
+    ctx.close()
+
+
+def test_workspace_replaced():
+    """Captured steps belong to the workspace they were captured in."""
+    cfg = workloads.small("c3", grid_n=16, n_side=9, n_steps=12, precision="fp32", box_mpc=400.0, z_begin=300.0,
+                          z_end=40.0, sort_every=5, sort_cells=0.0)
+    cfg["species"] = [dict(field=0, m=0.05, n=2011, n_side=1), dict(field=0, m=0.02, n=301, n_side=1)]
+    ctx = fastdf.Context(cfg)
+    ctx.set_tuning(use_graph=1)
+    ref = _job(ctx, cfg, (5, 6))
+    first = ctx.workspace                # stays allocated
+    ctx.workspace = torch.empty_like(first)
+    ctx._check(ctx.lib.fdf_attach_workspace(ctx.ctx, ctypes.c_void_p(ctx.workspace.data_ptr()),
+                                            ctx.workspace.numel()), "fdf_attach_workspace")
+    held = first.clone()
+    for a, b in zip(_job(ctx, cfg, (5, 6)), ref):
+        assert np.array_equal(a, b)
+    assert torch.equal(first, held)
     ctx.close()
