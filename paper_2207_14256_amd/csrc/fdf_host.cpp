@@ -803,11 +803,14 @@ struct SortCadence {
 };
 constexpr int kNeverDue = 1 << 30;
 
-int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
+// Looks `most` steps ahead at most and says kNeverDue beyond: a caller that only
+// asks whether a launch's span reaches that far must not walk a long schedule to
+// its end at every launch (20 000 steps, three species: 0.12 ms a call).
+int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m, int most = kNeverDue) {
   const int dir = p.n > 0 ? 1 : -1;
   if (s.cells > 0) {
     double cells = s.drift_cells, dr, ah;
-    for (int k = 1; p.drift(u, &dr, &ah); ++k, u += dir) {
+    for (int k = 1; k <= most && p.drift(u, &dr, &ah); ++k, u += dir) {
       cells += typical_drift_cells(c, dr, ah, m);
       if (cells >= s.cells) return k;
     }
@@ -826,11 +829,14 @@ constexpr double kPlacedDrift = 3.0;
 
 bool sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
   if (s.placed && (s.cells > 0 || s.every > 0)) {
-    const int dir = p.n > 0 ? 1 : -1, len = steps_until_due(c, p, s, u, m);
+    const int dir = p.n > 0 ? 1 : -1;
+    const int len = s.cells > 0 ? kNeverDue : steps_until_due(c, p, s, u, m);
     double dr, ah, cells = 0.0;
-    for (int k = 0; k + 1 < len && cells <= kPlacedDrift && p.drift(u + dir * k, &dr, &ah); ++k)
+    for (int k = 1; k < len && p.drift(u + dir * (k - 1), &dr, &ah); ++k) {
       cells += typical_drift_cells(c, dr, ah, m);
-    if (cells > kPlacedDrift) return true;
+      if (s.cells > 0 && cells >= s.cells) break;   // the interval ends here
+      if (cells > kPlacedDrift) return true;
+    }
   }
   if (s.cells > 0) return !s.sorted || s.drift_cells >= s.cells;
   return s.every > 0 && u % s.every == 0 && s.order_time != u;
@@ -909,7 +915,7 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
     }
     now = s.restart(u);
   }
-  const int d = steps_until_due(c, p, now, u, m);
+  const int d = steps_until_due(c, p, now, u, m, room);
   if (d < rem) {               // due again within the call
     l.span = std::min(d, room);
     if (fusable && l.span == d) {
