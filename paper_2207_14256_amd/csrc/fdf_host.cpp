@@ -1977,19 +1977,70 @@ int fdf_power_spectrum_noalloc(fdf_ctx* c, const int32_t* sp, int32_t ns, int32_
   return launched(c, "power spectrum (static scratch)");
 }
 
+// State of a species that is in the order of its ids, array by array.
+static int read_state_arrays(fdf_ctx* c, const SpeciesRec& s, double* hx, double* hq) {
+  const Segment& g = s.seg[s.cur];
+  const bool f64 = c->cfg.precision == FDF_PREC_FP64;
+  const int64_t piece = std::min<int64_t>(s.n, 1 << 20);
+  std::vector<double> d(f64 ? piece : 0);
+  std::vector<float> q0(f64 ? 0 : piece), dq(f64 ? 0 : piece);
+  std::vector<uint32_t> u(f64 ? 0 : piece);
+  auto get = [&](auto& to, const auto* from, int64_t n) {
+    return hip_check(c, hipMemcpy(to.data(), from, n * sizeof(*from), hipMemcpyDeviceToHost), "read state");
+  };
+  int rc = hip_check(c, hipStreamSynchronize(c->stream), "sync");
+  for (int64_t i0 = 0; i0 < s.n; i0 += piece) {
+    const int64_t n = std::min(piece, s.n - i0);
+    for (int k = 0; k < 3; ++k) {
+      if (hx && !rc) {
+        double* const h = hx + 3 * i0 + k;
+        rc = f64 ? get(d, g.xd[k] + i0, n) : get(u, g.xu[k] + i0, n);
+        for (int64_t i = 0; i < n; ++i) h[3 * i] = f64 ? d[i] : (double)u[i] * (c->cfg.box_mpc * 0x1p-32);
+      }
+      if (hq && !rc) {
+        double* const h = hq + 3 * i0 + k;
+        rc = f64 ? get(d, g.qd[k] + i0, n) : get(q0, g.q0f[k] + i0, n);
+        if (!f64 && !rc) rc = get(dq, g.dqf[k] + i0, n);
+        for (int64_t i = 0; i < n; ++i) h[3 * i] = f64 ? d[i] : (double)q0[i] + (double)dq[i];
+      }
+      if (rc) return rc;
+    }
+  }
+  return rc;
+}
+
+// Ids of a slice below which fdf_read_state copies the arrays instead of reading
+// several slices (a slice costs a launch, a copy and a scan of all ids for the
+// positions and again for the momenta).  1 M particles, slices against arrays:
+// 341 ids (8^3, FP32) 96 and 6.1 ms, 2730 (16^3, FP32) 21 and 6.1, 9557 (16^3,
+// FP64) 7.6 and 6.4, 21845 (32^3, FP32) 4.6 and 6.1, 76458 (32^3, FP64) 3.2 and
+// 6.4; 10 K particles in 341 1.03 and 0.25.
+constexpr int64_t kReadSliceIds = 16384;
+
 int fdf_read_state(fdf_ctx* c, int32_t sid, double* hx, double* hq) {
   if (!c) return FDF_ERR_ARG;
   if (sid < 0 || sid >= (int)c->species.size()) return fail(c, FDF_ERR_ARG, "bad species id");
   const SpeciesRec& s = c->species[sid];
-  // a kernel puts the state in id order in the FFT scratch (FP32: below the
-  // density copy), in slices of ids that fit
+  // A kernel puts the state in id order: in the species' other copy, which holds
+  // nothing between the steps, or without one in the FFT scratch (FP32: below
+  // the density copy), in slices of ids that fit.  The scratch grows with the
+  // mesh alone, so a small one takes many slices; a species there is in id
+  // order (nothing re-orders it on a mesh that the L2 holds) and its arrays can
+  // be copied instead.
   ReadStateArgs a{};
   a.seg = s.seg[s.cur];
   a.fp64 = c->cfg.precision == FDF_PREC_FP64;
   a.box = c->cfg.box_mpc;
   a.out = (double*)(c->ws + c->lay.scratch);
-  const size_t room = a.fp64 ? c->lay.scratch_bytes : density_copy_offset(c);
+  size_t room = a.fp64 ? c->lay.scratch_bytes : density_copy_offset(c);
+  if (c->cfg.sort_every > 0) {
+    const Segment& o = s.seg[s.cur ^ 1];   // its arrays, from the first to the ids, in one piece
+    char* const first = a.fp64 ? (char*)o.xd[0] : (char*)o.xu[0];
+    a.out = (double*)first;
+    room = (size_t)((char*)(o.id + s.n) - first);
+  }
   const int64_t slice = (int64_t)(room / (3 * sizeof(double)));
+  if (s.n > slice && slice < kReadSliceIds && !s.sorted) return read_state_arrays(c, s, hx, hq);
   for (int m = 0; m < 2; ++m) {
     double* h = m ? hq : hx;
     if (!h) continue;
