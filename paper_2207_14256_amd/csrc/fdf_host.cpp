@@ -296,6 +296,7 @@ struct SpeciesRec {
   bool placed = false;     // that order is the one of its creation, without a prediction
   int order_time = -1;     // integer time from which its current order is meant to be used (-1: none)
   double drift_cells = 0;  // typical drift since that time, in mesh cells
+  int waited = 0;          // gathers that its first order in place has waited for
 };
 
 // A captured step sequence: the host state it was captured from and the host
@@ -303,7 +304,7 @@ struct SpeciesRec {
 struct HostStepState {
   int step_index = 0;
   std::vector<int> ints;           // per species: copy of its state, sorted, placed, order time,
-                                   // pristine; per field: two super-step set tags
+                                   // pristine, waited; per field: two super-step set tags
   std::vector<double> drift_cells; // per species
   std::vector<double> grid_a;      // per field; NaN = no grid
   bool operator==(const HostStepState& o) const {
@@ -797,9 +798,11 @@ struct SortCadence {
   bool placed;
   int order_time;
   double drift_cells;
+  int waited;                // gathers that its first order in place has waited for
   double cells;              // adaptive threshold (0: fixed cadence)
   int every;                 // fixed cadence (0: never)
-  SortCadence restart(int time) const { return SortCadence{true, false, time, 0.0, cells, every}; }
+  bool in_place;             // re-sorts in place, which the caller has not asked for
+  SortCadence restart(int time) const { return SortCadence{true, false, time, 0.0, 0, cells, every, in_place}; }
 };
 constexpr int kNeverDue = 1 << 30;
 
@@ -827,7 +830,19 @@ int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, 
 // those at its start.
 constexpr double kPlacedDrift = 3.0;
 
-bool sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m) {
+// A first order in place costs about four gathers of a state in no order, so a
+// call of fewer than kInPlaceGathers does not make one: 2 M particles in a given
+// order on 128^3, one step (two gathers), FP32 640 us with it and 300 without,
+// FP64 963 and 604; five steps 717 and 827, 1281 and 1760.  Short calls one after
+// the other make it once kInPlaceWait gathers have gone by, or at the second
+// call if the order is that of the species' creation.
+constexpr int kInPlaceGathers = 6, kInPlaceWait = 12;
+
+enum class Due { kNo, kWaits, kNow };   // kWaits: for a later call
+
+// gathers: those left in the call, from integer time u on.
+Due sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m, int gathers) {
+  const bool pays = !s.in_place || gathers >= kInPlaceGathers;
   if (s.placed && (s.cells > 0 || s.every > 0)) {
     const int dir = p.n > 0 ? 1 : -1;
     const int len = s.cells > 0 ? kNeverDue : steps_until_due(c, p, s, u, m);
@@ -835,11 +850,12 @@ bool sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double
     for (int k = 1; k < len && p.drift(u + dir * (k - 1), &dr, &ah); ++k) {
       cells += typical_drift_cells(c, dr, ah, m);
       if (s.cells > 0 && cells >= s.cells) break;   // the interval ends here
-      if (cells > kPlacedDrift) return true;
+      if (cells > kPlacedDrift) return pays || s.waited > 0 ? Due::kNow : Due::kWaits;
     }
   }
-  if (s.cells > 0) return !s.sorted || s.drift_cells >= s.cells;
-  return s.every > 0 && u % s.every == 0 && s.order_time != u;
+  if (s.cells > 0 && !s.sorted) return pays || s.waited >= kInPlaceWait ? Due::kNow : Due::kWaits;
+  if (s.cells > 0) return s.drift_cells >= s.cells ? Due::kNow : Due::kNo;
+  return s.every > 0 && u % s.every == 0 && s.order_time != u ? Due::kNow : Due::kNo;
 }
 
 // Adaptive threshold of the re-sorts in place.  They cost two passes more than
@@ -850,9 +866,10 @@ bool sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double
 constexpr double kInPlaceCells = 10.0;
 
 SortCadence cadence_of(fdf_ctx* c, const SpeciesRec& s) {
-  SortCadence r{s.sorted, s.placed, s.order_time, s.drift_cells, c->sort_cells, c->sort_every};
+  SortCadence r{s.sorted, s.placed, s.order_time, s.drift_cells, s.waited, c->sort_cells, c->sort_every, false};
   InPlaceRoom room;
-  if (in_place_room(c, s.n, &room)) r.cells = kInPlaceCells;
+  r.in_place = in_place_room(c, s.n, &room);
+  if (r.in_place) r.cells = kInPlaceCells;
   return r;
 }
 
@@ -883,6 +900,7 @@ SortPrediction sort_prediction(fdf_ctx* c, const StepPlan& p, const SortCadence&
 // What the next launch does for a species standing at launch index j.
 struct LaunchPlan {
   int span = 1;              // steps carried out
+  bool waits = false;        // a first order in place is left to a later call
   bool sort_first = false;   // rank and move passes before it (sort_passes of them)
   int sort_passes = 0;
   bool fused = false;        // the push writes the state in sorted order for the interval after it
@@ -901,7 +919,9 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
                        c->cfg.eom == FDF_EOM_SEPARABLE;
   double dr, ah;
   SortCadence now = s;
-  if (sort_due(c, p, s, u, m)) {
+  const Due due = sort_due(c, p, s, u, m, rem + 1);
+  l.waits = due == Due::kWaits;
+  if (due == Due::kNow) {
     // a first sort takes two passes (the second orders cells in buckets)
     const bool first = !s.sorted;
     const bool ride = fusable && p.drift(u + dir, &dr, &ah);   // steps follow that use the new order
@@ -915,7 +935,7 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
     }
     now = s.restart(u);
   }
-  const int d = steps_until_due(c, p, now, u, m, room);
+  const int d = l.waits ? kNeverDue : steps_until_due(c, p, now, u, m, room);
   if (d < rem) {               // due again within the call
     l.span = std::min(d, room);
     if (fusable && l.span == d) {
@@ -932,7 +952,8 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
 SortCadence after_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, const LaunchPlan& l, double m, int j) {
   const int dir = p.n > 0 ? 1 : -1, u = p.time(j);
   SortCadence r = s;
-  r.placed = false;
+  r.placed = s.placed && l.waits;
+  if (l.waits) r.waited += l.span;
   if (l.sort_first) r = s.restart(u);
   double dr, ah;
   for (int k = 0; k < l.span && j + k < p.nabs(); ++k)
@@ -1590,6 +1611,7 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
         s.placed = after.placed;
         s.order_time = after.order_time;
         s.drift_cells = after.drift_cells;
+        s.waited = after.waited;
         keyed[i] = m.writes_keys;
         at[i] = jn;
         longest = std::max(longest, m.plan.span);
@@ -1628,7 +1650,7 @@ HostStepState host_state(fdf_ctx* c) {
   HostStepState h;
   h.step_index = c->step_index;
   for (auto& s : c->species) {
-    h.ints.insert(h.ints.end(), {s.cur, s.sorted ? 1 : 0, s.placed ? 1 : 0, s.order_time, s.pristine ? 1 : 0});
+    h.ints.insert(h.ints.end(), {s.cur, s.sorted ? 1 : 0, s.placed ? 1 : 0, s.order_time, s.pristine ? 1 : 0, s.waited});
     h.drift_cells.push_back(s.drift_cells);
   }
   for (auto& f : c->fields) {
@@ -1642,12 +1664,13 @@ HostStepState host_state(fdf_ctx* c) {
 void apply_state(fdf_ctx* c, const HostStepState& h) {
   c->step_index = h.step_index;
   const int* v = h.ints.data();
-  for (size_t i = 0; i < c->species.size(); ++i, v += 5) {
+  for (size_t i = 0; i < c->species.size(); ++i, v += 6) {
     c->species[i].cur = v[0];
     c->species[i].sorted = v[1] != 0;
     c->species[i].placed = v[2] != 0;
     c->species[i].order_time = v[3];
     c->species[i].pristine = v[4] != 0;
+    c->species[i].waited = v[5];
     c->species[i].drift_cells = h.drift_cells[i];
   }
   for (size_t i = 0; i < c->fields.size(); ++i, v += 2) {
