@@ -989,6 +989,14 @@ constexpr int64_t kMinPushBlocks = 2048;
 // (below half a particle per mesh cell) touch more lines per particle and want
 // fewer waves: 100 M on 13 meshes of 256^3, 6.36 ms with 2 per thread, 6.7 with 1.
 constexpr int kOneBlockReserve = 90 * 1024;
+// Super-steps with TSC on 8 slots above 4 GiB of mesh (64-bit gather addresses):
+// with one particle per thread, 1024 threads of it, the re-sorting push keeps 44
+// registers in memory.  560 M particles on 1024^3, 5 launches: 1077, 614 and 560
+// ms with 1, 2 and 4 per thread; 60 M (sparse) 221 ms with 2, 173 with 4.  Below
+// 4 GiB the same kernel keeps 2 there: 60 M on 256^3 130, 131 and 141 ms.
+bool wide_blended_gather(const PushArgs& a) {
+  return a.blend && a.tsc && a.nslot == 8 && (uint64_t)a.G * a.G * a.G * 16 > (1ull << 32);
+}
 
 // One launch over the members (at most kMaxJobs), all standing at the same
 // launch index (pa.step[0]) and all fused or all plain.
@@ -1012,14 +1020,14 @@ int run_launch(fdf_ctx* c, PushArgs& pa, const std::vector<LaunchMember>& member
   for (char r : mesh) meshes += r;
   const int64_t cells = meshes * (int64_t)c->cfg.grid_n * c->cfg.grid_n * c->cfg.grid_n;
   if (fused) {
-    pa.ppt = longest > 1 ? (2 * total < cells ? 2 : 1) : c->sort_push_ppt;
+    pa.ppt = longest == 1 ? c->sort_push_ppt : wide_blended_gather(pa) ? 4 : 2 * total < cells ? 2 : 1;
   } else {
     pa.block = wide ? kPushWideBlock : kPushBlock;
     pa.ppt = wide || one_each ? 1 : c->ppt;
     pa.lds_reserve = wide ? kOneBlockReserve : push_lds_reserve(c->push_waves);
   }
   while (pa.ppt > 1 && total < kMinPushBlocks * kPushBlock * pa.ppt) pa.ppt /= 2;
-  if (fused) pa.lds_reserve = pa.ppt <= 2 ? kOneBlockReserve : 0;
+  if (fused) pa.lds_reserve = pa.ppt <= 2 || (longest > 1 && wide_blended_gather(pa)) ? kOneBlockReserve : 0;
   const int64_t per = fused ? kSortBlock : pa.block * pa.ppt;
   const SortArgs sa = sort_args(c, c->species[members[0].species], 0.0, 0.0);
   pa.key_out = (uint32_t*)(c->ws + c->lay.sort_key);

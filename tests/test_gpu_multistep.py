@@ -54,3 +54,19 @@ def test_spans_with_time_dependent_grids(model, tol):
         got, _, _ = _states(cfg, 40, **tuning)
         for (xa, qa), (xb, qb) in zip(ref, got):
             assert np.array_equal(xa, xb) and np.array_equal(qa, qb)
+
+
+def test_blended_tsc_above_4_gib_of_mesh():
+    """Super-steps with TSC on a 1024^3 mesh of 16-byte cells (64-bit gather
+    addresses), re-sorting launches of several steps with 4 particles per
+    thread: states of a never-sorted run, bit for bit."""
+    cfg = workloads.small("c3", grid_n=1024, n_side=1, n_steps=16, box_mpc=1000.0, z_begin=1e4, z_end=5757.0,
+                          sort_every=1, sort_cells=0.0, interp_order=2, model="radmat", omega_r=1e-4,
+                          superstep_tol=0.05)
+    n = 4 * 2048 * 256 + 517
+    cfg["species"] = [dict(field=0, m=0.1, n=n, n_side=1, seed=5)]
+    ref, _, _ = _states(cfg, 16, sort_every=0)
+    got, _, passes = _states(cfg, 16, sort_every=5)
+    assert passes[0] <= 5 * n          # launches of several steps
+    for (xa, qa), (xb, qb) in zip(ref, got):
+        assert np.array_equal(xa, xb) and np.array_equal(qa, qb)
