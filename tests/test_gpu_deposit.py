@@ -38,3 +38,25 @@ def test_density_matches_oracle_deposit(prec, grid_n, n, mode):
     scale = np.abs(stats.binned_power(ref[0], ref[0], 600.0, 4)[1][sel]).max()
     assert np.abs(p - ref_p[1])[sel].max() <= (1e-10 if prec == "fp64" else 1e-4) * scale
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [64000, 140001])
+def test_fp32_spectra_do_not_depend_on_the_order(n):
+    """Particles in the order of their ids (a context without re-sorts on a
+    mesh that the L2 holds): a deposit block touches more lines than its table
+    holds, and part of its contributions takes the mesh atomics directly.  The
+    spectra are those of sorted particles, bit for bit."""
+    cfg = workloads.small("c3", grid_n=32, n_side=1, n_steps=40, box_mpc=600.0, z_begin=100.0, z_end=10.0,
+                          sort_every=0, sort_cells=0.0)
+    cfg["species"] = [dict(field=0, m=0.1, n=n, n_side=1, seed=41)]
+    out = []
+    for sort_every in (0, 3):
+        ctx, _, species = fastdf.setup_workload(dict(cfg, sort_every=sort_every))
+        ctx.timing()
+        ctx.step(40)
+        assert (ctx.read_timing("sort")[1] > 0) == (sort_every > 0)
+        out.append([v for mode in ("cross", "auto") for quantity in ("density", "momentum")
+                    for v in ctx.power_spectrum(species, 20, mode, quantity)])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b, equal_nan=True)
