@@ -4,7 +4,9 @@ Candidates are timed on the device through the C ABI's own HIP-event timers:
 
   1. launch shape -- particles per thread and the cap on resident waves per
      SIMD, then the particles per thread of the push fused with a re-sort --
-     over the full schedule, scored by the time of both push kernels;
+     over the full schedule, scored by the time of both push kernels; only
+     those that the workload's launches follow (launches of several steps
+     have a shape of their own: launch_shapes);
   2. sort policy -- bucket size and the drift threshold of the adaptive
      cadence -- over the full schedule, since the cost of a stale order and the
      number of re-sorts both depend on how far the particles travel;
@@ -18,6 +20,7 @@ device architecture, mesh size, particles per cell, precision and number of
 species.  None of the parameters changes results (the push is per particle
 and the sort only permutes), only speed.
 """
+import itertools
 import json
 import os
 import time
@@ -44,6 +47,22 @@ def load_cache(path=CACHE_PATH):
 
 def cached_tuning(cfg, path=CACHE_PATH):
     return load_cache(path).get(cache_key(cfg))
+
+
+def launch_shapes(cfg):
+    """The launch-shape candidates of a workload: (particles per thread, caps on
+    resident waves, particles per thread of the re-sorting push), each with one
+    entry, the default, where no launch of any weight follows it.  The numbers
+    are those of the launch planning in fdf_host.cpp."""
+    n = sum(int(sp.get("n", sp["n_side"] ** 3)) for sp in cfg["species"])
+    separable = cfg.get("eom", "separable") == "separable"
+    one_step = cfg["model"] == "radmat" and not cfg.get("superstep_tol", 0.0) > 0   # the meshes change at each
+    # separable CIC launches of several steps take blocks of 1024 threads from 262 144 particles on
+    plain = one_step or not separable or cfg.get("interp_order", 1) == 2 or n < 256 * 1024
+    # more than one particle per thread: FP32 separable form, at least 2048 blocks of them
+    several = plain and separable and cfg["precision"] == "fp32" and n >= 2 * 2048 * 256
+    resort = one_step and separable and cfg["precision"] == "fp32" and cfg.get("sort_every", 0) > 0
+    return (1, 2, 4, 8) if several else (4,), (0, 2, 3, 4) if plain else (0,), (1, 2, 4) if resort else (1,)
 
 
 def _run(ctx, cfg, tuning, steps):
@@ -76,24 +95,24 @@ def autotune(cfg, path=CACHE_PATH, log=print, full_schedule=True):
     #    timed over the whole schedule (the mesh locality of the gathers, and
     #    with it the best shape, changes as the particles disperse), scored
     #    by the time of both push kernels together.
-    best, best_ms = None, float("inf")
+    ppts, caps, sort_ppts = launch_shapes(cfg)
+    best, best_ms = base, float("inf")
     steps = cfg["n_steps"] if full_schedule else min(40, cfg["n_steps"])
-    for ppt in (1, 2, 4, 8):
-        for waves in (0, 2, 3, 4):
-            t = dict(base, particles_per_thread=ppt, push_waves=waves)
-            r = _run(ctx, cfg, t, steps)
-            log("[autotune] ppt=%d push_waves=%d: push %.3f ms per launch, %.1f ms both push kernels" % (
-                ppt, waves, r["push_ms"], r["push_total_ms"]))
-            if r["push_total_ms"] < best_ms:
-                best, best_ms = t, r["push_total_ms"]
+    shapes = list(itertools.product(ppts, caps))
+    for ppt, waves in shapes if len(shapes) * len(sort_ppts) > 1 else []:
+        t = dict(base, particles_per_thread=ppt, push_waves=waves)
+        r = _run(ctx, cfg, t, steps)
+        log("[autotune] ppt=%d push_waves=%d: push %.3f ms per launch, %.1f ms both push kernels" % (
+            ppt, waves, r["push_ms"], r["push_total_ms"]))
+        if r["push_total_ms"] < best_ms:
+            best, best_ms = t, r["push_total_ms"]
     #    then the particles per thread of the fused re-sort push
-    if sorting:
-        for sppt in (2, 4):
-            t = dict(best, sort_push_ppt=sppt)
-            r = _run(ctx, cfg, t, steps)
-            log("[autotune] sort_push_ppt=%d: %.1f ms both push kernels" % (sppt, r["push_total_ms"]))
-            if r["push_total_ms"] < best_ms:
-                best, best_ms = t, r["push_total_ms"]
+    for sppt in sort_ppts[1:]:
+        t = dict(best, sort_push_ppt=sppt)
+        r = _run(ctx, cfg, t, steps)
+        log("[autotune] sort_push_ppt=%d: %.1f ms both push kernels" % (sppt, r["push_total_ms"]))
+        if r["push_total_ms"] < best_ms:
+            best, best_ms = t, r["push_total_ms"]
     # 2. sort policy over the whole schedule
     if sorting and full_schedule:
         G = cfg["grid_n"]
