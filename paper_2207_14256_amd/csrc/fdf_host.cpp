@@ -834,9 +834,10 @@ constexpr double kPlacedDrift = 3.0;
 // call of fewer than kInPlaceGathers does not make one: 2 M particles in a given
 // order on 128^3, one step (two gathers), FP32 640 us with it and 300 without,
 // FP64 963 and 604; five steps 717 and 827, 1281 and 1760.  Short calls one after
-// the other make it once kInPlaceWait gathers have gone by, or at the second
-// call if the order is that of the species' creation.
-constexpr int kInPlaceGathers = 6, kInPlaceWait = 12;
+// the other make it once as many gathers have gone by (they have cost by then
+// what the order costs), or at the second call if the order is that of the
+// species' creation.
+constexpr int kInPlaceGathers = 6;
 
 enum class Due { kNo, kWaits, kNow };   // kWaits: for a later call
 
@@ -853,7 +854,7 @@ Due sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double 
       if (cells > kPlacedDrift) return pays || s.waited > 0 ? Due::kNow : Due::kWaits;
     }
   }
-  if (s.cells > 0 && !s.sorted) return pays || s.waited >= kInPlaceWait ? Due::kNow : Due::kWaits;
+  if (s.cells > 0 && !s.sorted) return pays || s.waited >= kInPlaceGathers ? Due::kNow : Due::kWaits;
   if (s.cells > 0) return s.drift_cells >= s.cells ? Due::kNow : Due::kNo;
   return s.every > 0 && u % s.every == 0 && s.order_time != u ? Due::kNow : Due::kNo;
 }
