@@ -42,3 +42,10 @@ def test_refuses_several_gpus():
     assert res.returncode != 0
     assert "one GPU" in res.stderr
     assert res.stdout.strip() == ""
+
+
+def test_bound_follows_the_steps_of_a_launch():
+    """A push of one step streams its state from HBM; over several steps HBM is
+    at a fifth of its rate, and the line must not call it the bound."""
+    assert bench.push_bound(1.0) == "hbm"
+    assert "hbm" not in bench.push_bound(6.4) and "address unit" in bench.push_bound(24.0)
