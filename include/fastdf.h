@@ -134,7 +134,9 @@ typedef struct fdf_config {
   int32_t sort_every;      /* spatial re-sort of particles every this many steps, into a second
                               copy of their state (0: no second copy and no cadence of the
                               caller's; the library re-orders the state in place, through the
-                              FFT scratch, where that pays).  The order changes no result */
+                              FFT scratch, where that pays.  A context whose particles are
+                              never to be re-ordered takes a value > 0 here and sort_every = 0,
+                              sort_cells = 0 in fdf_tuning).  The order changes no result */
   int32_t max_fields;      /* capacity: number of seeded fields (each owns one grid set) */
   int32_t max_species;     /* capacity: number of species */
   int32_t interp_order;    /* force interpolation order r (sec. 4): 0 or 1 CIC (8 points),
@@ -166,9 +168,10 @@ typedef struct fdf_info {
 /* Launch and sort parameters (picked by the autotuner or set by hand).  None
  * changes results: the push is per particle and the sort only permutes. */
 typedef struct fdf_tuning {
-  int32_t particles_per_thread;  /* FP32 separable push of one step: at most 1, 2, 4
-                                    or 8 (fewer when too few particles to fill the
-                                    chip); pushes of several steps take 1 */
+  int32_t particles_per_thread;  /* FP32 separable push of one step, or of several with
+                                    TSC: at most 1, 2, 4 or 8 (fewer when too few
+                                    particles to fill the chip); pushes of several
+                                    steps with CIC take 1 */
   int32_t sort_tiles;            /* sort buckets per axis: a power of two <= min(G, 256);
                                     particles are ordered by the Morton index of
                                     their bucket, then of their cell inside it;
@@ -195,8 +198,10 @@ typedef struct fdf_tuning {
                                     sorted order (no separate move pass; results
                                     bit-identical; the default); 0: rank + move
                                     passes, then the push */
-  int32_t push_waves;            /* plain push launch of one step (not one that
-                                    carries out a re-sort): at most this many resident waves per
+  int32_t push_waves;            /* plain push launch (not one that carries out a
+                                    re-sort) in blocks of 256 threads: one step, TSC,
+                                    the non-separable forms, or fewer than 262 144
+                                    particles.  At most this many resident waves per
                                     SIMD (2-8; enforced by reserving LDS per block),
                                     fewer waves keeping more of each block's mesh
                                     neighbourhood in cache; 0: as many as the
@@ -205,7 +210,9 @@ typedef struct fdf_tuning {
                                     particles per thread (1, 2 or 4; 0 selects 4)
                                     of its 1024-particle blocks (pushes of
                                     several steps take 1, or 2 on meshes with
-                                    less than one particle in two cells) */
+                                    less than one particle in two cells, or 4
+                                    with super-steps and TSC on 16-byte cells
+                                    above 4 GiB of mesh) */
   int32_t sort_keys_push;        /* 1 (the default): FP32 separable form -- a push
                                     that is followed by a re-sorting push in the
                                     same fdf_step call also writes the particles'

@@ -1642,7 +1642,8 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
 
 // The workspace is carved deterministically, so fields and species added in
 // the same order with the same sizes sit at the same device addresses: a graph
-// captured for one such layout replays correctly after fdf_reset + re-adding.
+// captured for one such layout replays correctly after fdf_reset + re-adding,
+// with other seeds too (a step reads them from the segment table).
 std::vector<double> layout_signature(fdf_ctx* c) {
   std::vector<double> v;
   v.push_back((double)c->fields.size());
