@@ -283,6 +283,8 @@ struct FieldRec {
   int tag[2] = {-1, -1};      // super-steps: anchor (schedule index) held by each set
 };
 
+enum { kThisCall = 1, kEarlierCall = 2 };
+
 struct SpeciesRec {
   int field = 0;
   double m = 0;
@@ -296,7 +298,7 @@ struct SpeciesRec {
   bool placed = false;     // that order is the one of its creation, without a prediction
   int order_time = -1;     // integer time from which its current order is meant to be used (-1: none)
   double drift_cells = 0;  // typical drift since that time, in mesh cells
-  int waited = 0;          // gathers that its first order in place has waited for
+  int waited = 0;          // its first order in place was left to a later call: kThisCall, kEarlierCall
 };
 
 // A captured step sequence: the host state it was captured from and the host
@@ -798,11 +800,11 @@ struct SortCadence {
   bool placed;
   int order_time;
   double drift_cells;
-  int waited;                // gathers that its first order in place has waited for
+  int waited;                // its first order in place was left to a later call: kThisCall, kEarlierCall
   double cells;              // adaptive threshold (0: fixed cadence)
   int every;                 // fixed cadence (0: never)
-  bool in_place;             // re-sorts in place, which the caller has not asked for
-  SortCadence restart(int time) const { return SortCadence{true, false, time, 0.0, 0, cells, every, in_place}; }
+  int first_order;           // gathers for which a first order is made (0: any number)
+  SortCadence restart(int time) const { return SortCadence{true, false, time, 0.0, 0, cells, every, first_order}; }
 };
 constexpr int kNeverDue = 1 << 30;
 
@@ -830,20 +832,29 @@ int steps_until_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, 
 // those at its start.
 constexpr double kPlacedDrift = 3.0;
 
-// A first order in place costs about four gathers of a state in no order, so a
-// call of fewer than kInPlaceGathers does not make one: 2 M particles in a given
-// order on 128^3, one step (two gathers), FP32 640 us with it and 300 without,
-// FP64 963 and 604; five steps 717 and 827, 1281 and 1760.  Short calls one after
-// the other make it once as many gathers have gone by (they have cost by then
-// what the order costs), or at the second call if the order is that of the
-// species' creation.
-constexpr int kInPlaceGathers = 6;
+// A first order in place pays in a call of this many gathers: its cost, over
+// what a gather gains by it.  Particles in a given order, 2 M on 128^3, us without
+// and with it:  FP32 CIC, 6 gathers 697 and 684;  FP32 TSC, 2 684 and 707, 3 992
+// and 765;  FP64 CIC, 4 1038 and 1052, 5 1294 and 1104;  FP64 TSC, 2 1584 and
+// 1220.  Its launches take as long as its passes over 270 K particles: 200 K on
+// 128^3, FP32 CIC, 6 gathers 100 and 157, 12 174 and 176.  Sparse particles share
+// few mesh lines in any order: 300 K on 256^3, 12 gathers 362 and 445, FP64 TSC
+// 1884 and 1806.  A first call of fewer leaves it to the second one, which more
+// are likely to follow.
+int first_order_gathers(const fdf_ctx* c, int64_t n) {
+  const bool f64 = c->cfg.precision == FDF_PREC_FP64;
+  const int64_t G = c->cfg.grid_n;
+  if (32 * n < G * G * G) return kMaxSpan;
+  const double large = c->cfg.interp_order == 2 ? (f64 ? 1.5 : 2.4) : (f64 ? 4.6 : 6.0);
+  return (int)std::min<double>(kMaxSpan, std::lround(large * (1.0 + 270e3 / (double)n)));
+}
 
 enum class Due { kNo, kWaits, kNow };   // kWaits: for a later call
 
 // gathers: those left in the call, from integer time u on.
 Due sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double m, int gathers) {
-  const bool pays = !s.in_place || gathers >= kInPlaceGathers;
+  const Due first = gathers >= s.first_order || s.waited == kEarlierCall ? Due::kNow : Due::kWaits;
+  if (s.cells > 0 && s.sorted && s.drift_cells >= s.cells) return Due::kNow;
   if (s.placed && (s.cells > 0 || s.every > 0)) {
     const int dir = p.n > 0 ? 1 : -1;
     const int len = s.cells > 0 ? kNeverDue : steps_until_due(c, p, s, u, m);
@@ -851,11 +862,10 @@ Due sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double 
     for (int k = 1; k < len && p.drift(u + dir * (k - 1), &dr, &ah); ++k) {
       cells += typical_drift_cells(c, dr, ah, m);
       if (s.cells > 0 && cells >= s.cells) break;   // the interval ends here
-      if (cells > kPlacedDrift) return pays || s.waited > 0 ? Due::kNow : Due::kWaits;
+      if (cells > kPlacedDrift) return first;
     }
   }
-  if (s.cells > 0 && !s.sorted) return pays || s.waited >= kInPlaceGathers ? Due::kNow : Due::kWaits;
-  if (s.cells > 0) return s.drift_cells >= s.cells ? Due::kNow : Due::kNo;
+  if (s.cells > 0) return s.sorted ? Due::kNo : first;
   return s.every > 0 && u % s.every == 0 && s.order_time != u ? Due::kNow : Due::kNo;
 }
 
@@ -867,10 +877,12 @@ Due sort_due(fdf_ctx* c, const StepPlan& p, const SortCadence& s, int u, double 
 constexpr double kInPlaceCells = 10.0;
 
 SortCadence cadence_of(fdf_ctx* c, const SpeciesRec& s) {
-  SortCadence r{s.sorted, s.placed, s.order_time, s.drift_cells, s.waited, c->sort_cells, c->sort_every, false};
+  SortCadence r{s.sorted, s.placed, s.order_time, s.drift_cells, s.waited, c->sort_cells, c->sort_every, 0};
   InPlaceRoom room;
-  r.in_place = in_place_room(c, s.n, &room);
-  if (r.in_place) r.cells = kInPlaceCells;
+  if (in_place_room(c, s.n, &room)) {
+    r.cells = kInPlaceCells;
+    r.first_order = first_order_gathers(c, s.n);
+  }
   return r;
 }
 
@@ -936,7 +948,7 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
     }
     now = s.restart(u);
   }
-  const int d = l.waits ? kNeverDue : steps_until_due(c, p, now, u, m, room);
+  const int d = l.waits && !s.sorted ? kNeverDue : steps_until_due(c, p, now, u, m, room);
   if (d < rem) {               // due again within the call
     l.span = std::min(d, room);
     if (fusable && l.span == d) {
@@ -953,8 +965,8 @@ LaunchPlan plan_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, doub
 SortCadence after_launch(fdf_ctx* c, const StepPlan& p, const SortCadence& s, const LaunchPlan& l, double m, int j) {
   const int dir = p.n > 0 ? 1 : -1, u = p.time(j);
   SortCadence r = s;
-  r.placed = s.placed && l.waits;
-  if (l.waits) r.waited += l.span;
+  r.placed = s.placed && (l.waits || j == p.nabs());   // (or a closing kick on its own)
+  if (l.waits) r.waited = kThisCall;
   if (l.sort_first) r = s.restart(u);
   double dr, ah;
   for (int k = 0; k < l.span && j + k < p.nabs(); ++k)
@@ -1512,7 +1524,10 @@ int enqueue_steps(fdf_ctx* c, int32_t n) {
   const bool tdep = c->cfg.potential_model == FDF_MODEL_RADMAT;
   int rc = FDF_OK;
   std::vector<int> used(c->fields.size(), 0);
-  for (auto& s : c->species) used[s.field] = 1;
+  for (auto& s : c->species) {
+    used[s.field] = 1;
+    if (s.waited) s.waited = kEarlierCall;
+  }
   PushArgs pa{};
   pa.fp64 = c->cfg.precision == FDF_PREC_FP64;
   pa.nslot = c->lay.nslot;
@@ -1660,7 +1675,8 @@ HostStepState host_state(fdf_ctx* c) {
   HostStepState h;
   h.step_index = c->step_index;
   for (auto& s : c->species) {
-    h.ints.insert(h.ints.end(), {s.cur, s.sorted ? 1 : 0, s.placed ? 1 : 0, s.order_time, s.pristine ? 1 : 0, s.waited});
+    h.ints.insert(h.ints.end(), {s.cur, s.sorted ? 1 : 0, s.placed ? 1 : 0, s.order_time, s.pristine ? 1 : 0,
+                                s.waited});
     h.drift_cells.push_back(s.drift_cells);
   }
   for (auto& f : c->fields) {

@@ -54,35 +54,49 @@ def test_density_stays_readable_across_reordering(prec):
     ctx.close()
 
 
-@pytest.mark.parametrize("given,calls,sorts", [
-    (True, [1], 0), (True, [4], 0), (True, [5], 1), (True, [1] * 3, 0), (True, [1] * 4, 1), (True, [3, 2], 0),
-    (True, [4, 4], 0), (True, [4, 4, 1], 1), (True, [4, 5], 1), (True, [2, -2], 0), (True, [7, -7], 1),
-    (False, [1], 0), (False, [4], 0), (False, [5], 1), (False, [1, 1], 1), (False, [4, 5], 1)])
-@pytest.mark.parametrize("prec,grid_n", [("fp64", 64), ("fp32", 128)])
-def test_order_in_place_waits_for_a_call_that_repays_it(prec, grid_n, given, calls, sorts):
+# (precision, interpolation, particles): gathers from which a first order is made
+FIRST_ORDER = {("fp32", 1, 2000003): 7, ("fp32", 2, 2000003): 3, ("fp64", 1, 2000003): 5, ("fp64", 2, 2000003): 2,
+               ("fp32", 1, 270000): 12, ("fp64", 2, 270000): 3, ("fp32", 1, 3001): 24}
+
+
+# one launch a call, and a launch a step
+MODELS = {"poisson": {}, "radmat": dict(model="radmat", omega_r=1e-4)}
+
+
+@pytest.mark.parametrize("model", sorted(MODELS))
+@pytest.mark.parametrize("given", [True, False])
+@pytest.mark.parametrize("prec,order,n", sorted(FIRST_ORDER))
+def test_order_in_place_waits_for_a_call_that_repays_it(prec, order, n, given, model):
     """A context without re-sorts: calls too short to repay a first order in
     place, of particles given by the caller or of a species whose order at
-    creation its first interval's drift outruns, do not make one; the states
-    are those of a context that never orders them."""
-    cfg = workloads.small("c3", grid_n=grid_n, n_side=1, n_steps=20, precision=prec, box_mpc=2000.0, z_begin=1e4,
-                          z_end=2e3, sort_every=0, sort_cells=0.0)
+    creation its first interval's drift outruns, leave it to the next call; the
+    states are those of a context that never orders them.  A call of k steps
+    makes k + 1 gathers."""
+    pays = FIRST_ORDER[prec, order, n]
+    calls = [([pays - 1], 1), ([pays + 1], 1), ([pays - 2], 0), ([1, 1], 1), ([1, -1], int(given or pays <= 2))]
+    cfg = workloads.small("c3", grid_n=128, n_side=1, n_steps=26, precision=prec, box_mpc=2000.0, z_begin=1e4,
+                          z_end=2e3, sort_every=0, sort_cells=0.0, interp_order=order, **MODELS[model])
     if not given:
-        # 1 to 2.5 cells a step
-        cfg.update(box_mpc=25.0 * grid_n, z_begin=100.0, z_end=25.0)
-    cfg["species"] = [dict(field=0, m=0.05, n=5003, n_side=1)]
-    xu, q = workloads.hand_placed(5003, 2000.0)
-    out = []
-    for sort_every in (0, 1):
-        ctx = fastdf.Context(dict(cfg, sort_every=sort_every))
-        if sort_every:
-            ctx.set_tuning(sort_every=0)
-        fid = ctx.add_field(cfg["fields"][0])
-        sid = ctx.set_species_state(fid, 0.05, xu, q) if given else ctx.init_species(fid, 0.05, 5003, 9)
-        ctx.timing()
-        for n in calls:
-            ctx.step(n)
-        out.append(ctx.read_state(sid) + (ctx.read_timing("sort")[1],))
+        cfg.update(box_mpc=5760.0, z_begin=100.0, z_end=17.0)   # a third of a cell a step
+    cfg["species"] = [dict(field=0, m=0.05, n=n, n_side=1)]
+    xu, q = workloads.hand_placed(n, 2000.0)
+    contexts = [fastdf.Context(dict(cfg, sort_every=sort_every)) for sort_every in (0, 1)]
+    contexts[1].set_tuning(sort_every=0)
+    for steps, sorts in calls:
+        if 0 in steps:
+            continue
+        out = []
+        for ctx in contexts:
+            ctx.reset()
+            fid = ctx.add_field(cfg["fields"][0])
+            sid = ctx.set_species_state(fid, 0.05, xu, q) if given else ctx.init_species(fid, 0.05, n, 9)
+            ctx.timing()
+            ctx.timing_reset()
+            for k in steps:
+                ctx.step(k)
+            out.append(ctx.read_state(sid) + (ctx.read_timing("sort")[1],))
+        (xa, qa, first), (xb, qb, none) = out
+        assert np.array_equal(xa, xb) and np.array_equal(qa, qb)
+        assert none == 0 and min(first, 1) == sorts, steps
+    for ctx in contexts:
         ctx.close()
-    (xa, qa, first), (xb, qb, none) = out
-    assert np.array_equal(xa, xb) and np.array_equal(qa, qb)
-    assert none == 0 and min(first, 1) == sorts
